@@ -279,9 +279,9 @@ int tgks_gp_flux_host(const tgks_params* p, const double* Wl, const double* Wr, 
  * on the host: the TENO-D flag (bit0 = delta_{3,1}, bits 1..3 = the small
  * stencils' cut-offs; Sec. 4.2) with the normal cut-offs and eps of p.
  * fast selects the evaluation: 0 from the weights of Eqs. 4.5-4.12 alone
- * (correctly rounded divisions); 2 as the 1-D and 2-D kernels do, from
- * approximate reciprocals where a margin makes the decision certain (on
- * the host the reciprocal is 1/x cut to 24 significant bits); 1 as the 3-D
+ * (correctly rounded divisions); 2 as the 1-D and 2-D kernels do, from the
+ * weights' comparisons multiplied out where a margin makes the decision
+ * certain; 1 as the 3-D
  * kernels do, from fixed ratios of the smoothness indicators where they
  * decide, else from the weights.  The shortcuts are on only for q = 7,
  * eps >= 1e-40 and cut-offs in the ranges where they are exact; elsewhere

@@ -193,26 +193,44 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
   const double idt = 1.0 / g.dx[TA];
   // own side m along the face; the partner's side at this Gauss point
   double Wg[2][NC], Dg[2][2][NC];  // [side][q], [side][axis n/t][q]
+  const double sg = m ? 1.0 : -1.0;  // sign of the lane's Gauss point
   {
     const int nr = m == 0 ? fn : fn + 1;
     const int vo = m == 0 ? 2 : 0;
+    double gV[NC][2], gD[NC][2], gN[NC][2];  // at the lane's own Gauss point and at its partner's
+    auto tangential = [&](auto mode) {
+      constexpr int MODE = decltype(mode)::value;
+      bool sure = true;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int c = perm[q];
+        double Qw[5], Qn[5];
+#pragma unroll
+        for (int r = 0; r < 5; ++r) {
+          Qw[r] = sR[c][ft + r][nr][vo];
+          Qn[r] = sR[c][ft + r][nr][vo + 1];
+        }
+        TenoPoly<double> w, n;
+        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure), fq = select_poly<MODE>(Qn, a.tt, n, sure);
+        a.TF[((long long)(m * 2 + 0) * NC + c) * nf + fidx] = (uint8_t)fw;
+        a.TF[((long long)(m * 2 + 1) * NC + c) * nf + fidx] = (uint8_t)fq;
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          const double x = gp == 0 ? sg : -sg;
+          gV[q][gp] = fma(x, w.odd, w.base);
+          gD[q][gp] = fma(x, w.od, w.ev);
+          gN[q][gp] = fma(x, n.odd, n.base);
+        }
+      }
+      return sure;
+    };
+    bool sure = false;
+    if (a.tt.fast & TENO_FILTER_OK) sure = tangential(std::integral_constant<int, SEL_FILTER>());
+    if (!sure) tangential(std::integral_constant<int, SEL_EXACT>());
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const int c = perm[q];
-      double Qw[5], Qn[5], v[2], dv[2], vn[2], dn[2];
-#pragma unroll
-      for (int r = 0; r < 5; ++r) {
-        Qw[r] = sR[c][ft + r][nr][vo];
-        Qn[r] = sR[c][ft + r][nr][vo + 1];
-      }
-      const unsigned fw = teno_flag<SEL_FILTER>(Qw, a.tt), fq = teno_flag<SEL_FILTER>(Qn, a.tt);
-      a.TF[((long long)(m * 2 + 0) * NC + c) * nf + fidx] = (uint8_t)fw;
-      a.TF[((long long)(m * 2 + 1) * NC + c) * nf + fidx] = (uint8_t)fq;
-      teno_gauss(Qw, fw, v, dv);
-      teno_gauss(Qn, fq, vn, dn);
-      const double sv = m ? v[0] : v[1], sd = m ? dv[0] : dv[1], sn = m ? vn[0] : vn[1];
-      const double rv = lane_xor<1>(sv), rd = lane_xor<1>(sd), rn = lane_xor<1>(sn);
-      const double ov = m ? v[1] : v[0], od = m ? dv[1] : dv[0], on = m ? vn[1] : vn[0];
+      const double rv = lane_xor<1>(gV[q][1]), rd = lane_xor<1>(gD[q][1]), rn = lane_xor<1>(gN[q][1]);
+      const double ov = gV[q][0], od = gD[q][0], on = gN[q][0];
       Wg[0][q] = m == 0 ? ov : rv;
       Wg[1][q] = m == 0 ? rv : ov;
       Dg[0][1][q] = (m == 0 ? od : rd) * idt;

@@ -30,12 +30,14 @@ namespace tgks {
 
 // bits of TenoCfg::fast
 constexpr int TENO_RATIO_OK = 1;   // the fixed ratios of teno_flag hold (teno_cfg)
-constexpr int TENO_FILTER_OK = 2;  // the approximate-reciprocal test of teno_flag is valid
+constexpr int TENO_FILTER_OK = 2;  // the multiplied-out comparisons of teno_select are valid
 
 struct TenoCfg {
   double ct1, ct2, eps;
   int q;
   int fast;  // TENO_RATIO_OK | TENO_FILTER_OK where they hold (teno_cfg)
+  // for the certain decisions: 4 eps, and the cut-offs times 1 +- 2^-30
+  double eps4, ct1_up, ct1_dn, ct2_up, ct2_dn;
 };
 
 // The selection parameters, with the fast bits set where teno_flag's
@@ -60,12 +62,10 @@ struct TenoCfg {
 // q = 7 and eps >= 1e-40 (b^7 and 1 / b^7 stay finite and normal).  The
 // paper's C_T1 = 1e-7, C_T2 = 1e-5 are inside.
 //
-// TENO_FILTER_OK, the weights from approximate reciprocals with a margin
-// (teno_flag): q = 7, eps >= 1e-40 and 1e-20 <= C_T1, C_T2 <= 1/2, so that
-// every b^7, weight, sum and threshold of the test is a normal number
-// (b in [eps, 1e40): b^7 and 1 / b^7 in [1e-280, 1e280]; a threshold
-// C_T s >= 1e-20 1e-280 / 2, since the small weights hold at least half of
-// the sum when the large stencil is rejected, C_T1 <= 1/2).
+// TENO_FILTER_OK, the weights' comparisons multiplied out, with a margin
+// (teno_select): q = 7, 1e-40 <= eps < 1e40 and 1e-20 <= C_T1, C_T2 <= 1/2
+// (an indicator more than 2048 times the smallest is cut there, which stands
+// for weights below 2048^-7 = 6.6e-24 of the largest: far below any cut-off).
 inline TenoCfg teno_cfg(double ct1, double ct2, double eps, int q) {
   const double d = 1e-9;
   const bool ok = q == 7 && eps >= 1e-40 && ct1 * (1.0 + d) <= 1.0 / (3.0 * 16384.0 + 1.0) &&
@@ -73,13 +73,14 @@ inline TenoCfg teno_cfg(double ct1, double ct2, double eps, int q) {
                   ct2 * (1.0 - d) >= 1.0 / (2097152.0 + 1.0);
   const bool filt = q == 7 && eps >= 1e-40 && eps < 1e40 && ct1 >= 1e-20 && ct1 <= 0.5 && ct2 >= 1e-20 &&
                     ct2 <= 0.5;
-  return TenoCfg{ct1, ct2, eps, q, (ok ? TENO_RATIO_OK : 0) | (filt ? TENO_FILTER_OK : 0)};
+  const double up = 1.0 + 0x1p-30, dn = 1.0 - 0x1p-30;
+  return TenoCfg{ct1, ct2, eps, q, (ok ? TENO_RATIO_OK : 0) | (filt ? TENO_FILTER_OK : 0),
+                 4.0 * eps, ct1 * up, ct1 * dn, ct2 * up, ct2 * dn};
 }
 
-// An approximate reciprocal: the device's one-instruction estimate (its
-// error is not assumed: teno_flag measures it by the residual 1 - x r).  On
-// the host, 1 / x with the low 29 bits of the significand cleared (relative
-// error up to 2^-23), so that host checks exercise the same error handling.
+// An approximate reciprocal: the device's one-instruction estimate.  On the
+// host, 1 / x with the low 29 bits of the significand cleared (relative error
+// up to 2^-23), so that host checks exercise the same refinement.
 TGKS_HD double rcp_approx(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   return __builtin_amdgcn_rcp(x);
@@ -108,54 +109,99 @@ TGKS_HD double recip(double x) {
   return fma(r, fma(-x, r, 1.0), r);
 }
 
+// a b + c, rounded once in double
+template <class R>
+TGKS_HD R fma_(R a, R b, R c) {
+  return a * b + c;
+}
+TGKS_HD double fma_(double a, double b, double c) { return fma(a, b, c); }
+
 // ---------------------------------------------------------------------------
-// TENO-D selection (Sec. 4.2).  q[0..4] = Q_{-2..2}.
-// flag bit0 = delta_{3,1}; if it is 0, bits 1..3 = delta_{0,2}, delta_{1,2},
-// delta_{2,2}.
+// Differences of five values Q_{-2..2} = a..e that the selection and the
+// Gauss-point values share: x = d - b; second differences t[k] of the three
+// small stencils; one-sided slopes l0 = a - 4 b + 3 c, l2 = 3 c - 4 d + e;
+// y = e - a; third and fourth differences y3, y4.  Each is evaluated in the
+// oracle's order (a product by 2 or 4 is exact, so the fma rounds as the
+// separate operations do): where the data are constant up to rounding, the
+// selection is decided by their rounding residues.
+// ---------------------------------------------------------------------------
+template <class R>
+struct TenoParts {
+  R b, c, d, x, t[3], l0, l2, y, y3, y4;
+};
+
+template <class R>
+TGKS_HD void teno_parts(const R* Q, TenoParts<R>& p) {
+#pragma clang fp contract(off)
+  const R a = Q[0], b = Q[1], c = Q[2], d = Q[3], e = Q[4];
+  const R c3 = 3.0 * c, f = fma_(R(-4.0), b, a);
+  p.b = b;
+  p.c = c;
+  p.d = d;
+  p.x = d - b;
+  p.t[0] = fma_(R(-2.0), b, a) + c;
+  p.t[1] = fma_(R(-2.0), c, b) + d;
+  p.t[2] = fma_(R(-2.0), d, c) + e;
+  p.l0 = f + c3;
+  p.l2 = fma_(R(-4.0), d, c3) + e;
+  p.y = e - a;
+  p.y3 = fma_(R(-2.0), p.x, p.y);
+  p.y4 = fma_(R(-4.0), d, f + 6.0 * c) + e;
+}
+
+// A selection: the large stencil, or the surviving small ones.
+struct TenoSel {
+  bool lg, k0, k1, k2;
+  // bit0 = delta_{3,1}; if it is 0, bits 1..3 = delta_{0,2}, delta_{1,2}, delta_{2,2}
+  TGKS_HD unsigned flag() const { return lg ? 1u : (k0 ? 2u : 0u) | (k1 ? 4u : 0u) | (k2 ? 8u : 0u); }
+};
+
+TGKS_HD TenoSel teno_sel(unsigned flag) {
+  return TenoSel{(flag & 1u) != 0, (flag & 2u) != 0, (flag & 4u) != 0, (flag & 8u) != 0};
+}
+
+// ---------------------------------------------------------------------------
+// TENO-D selection (Sec. 4.2), a function of the input bits.
 //
-// The flag is a function of the input bits: the weights gamma_k =
-// (beta_k + eps)^-7 by correctly rounded divisions, summed and compared in
-// one fixed order (SEL_EXACT).  The other modes reach the same flag, bit
-// for bit, with less work where the decision is certain, and evaluate the
-// weights exactly where it is not:
+// teno_exact: the weights gamma_k = (beta_k + eps)^-q by correctly rounded
+// divisions, summed and compared in one fixed order.  teno_select reaches
+// the same selection, bit for bit, with less work where the decision is
+// certain, and calls teno_exact where it is not:
 //
-// SEL_FILTER: approximate reciprocals r_k of p_k = b_k^7 (one instruction
-// each instead of a division) with their residuals e_k = 1 - p_k r_k (one
-// fused multiply-add, rounded once).  If sum |e_k| <= 2^-18, each r_k is
-// within a relative E = 2^-18 (1 + 2^-52) of 1/p_k, so within E + 2^-53
-// of the correctly rounded weight g_k.  The sums of the positive r_k
-// (two or three additions, same order) are then within E + 7 2^-53 of
-// the exact path's sums, and the thresholds C_T s within E + 8 2^-53.  A
-// comparison is certain when r_k clears the threshold by a factor
-// 1 -+ 2^-12 (rounded once more): r_k > tau (1 + 2^-12) gives g_k > T and
-// r_k < tau (1 - 2^-12) gives g_k < T, since 2^-12 exceeds twice E plus
-// ten rounding errors 32-fold.  Undecided inputs (within 2.4e-4 of a
-// cut-off, or a failed residual or range test) take the exact weights;
-// on the benchmarks that is rare, so wavefronts seldom split.  All
-// comparisons are evaluated (no short-circuit branches): one branch, to
-// the exact weights, remains.
+// SEL_FILTER (the 1-D and 2-D kernels): the comparisons multiplied out, no
+// division.  b_k = 4 (beta_k + eps) as sums of squares of the shared
+// differences (fused multiply-adds; every term is positive, and s1, s2 lose
+// at most what y3, y4 hold beside them, so each b_k is within 100 rounding
+// errors of the oracle's); scaled by a power of two so that the smallest of
+// b_0..b_2 is in [1, 2) and cut at 2048 (t_k); p_k = t_k^7.  With
+// P = p_0 p_1 p_2 and S = p_0 p_1 + p_1 p_2 + p_0 p_2 the weights are
+// p_j p_k / P and 1 / p_3, so
+//   gamma_3 >= C_T1 sum       <=>  P >= C_T1 (S p_3 + P),
+//   gamma_i >= C_T2 sum_{k<3} <=>  p_j p_k >= C_T2 S.
+// Both sides are within 2^-41 of the oracle's, and a comparison is certain
+// when it holds with the cut-off times 1 +- 2^-30 on either side; an
+// undecided input (within 1e-9 of a cut-off, a NaN, indicators >= 1e40)
+// takes teno_exact.  All comparisons are evaluated (bitwise operators, no
+// short-circuit branches), so that one rarely taken branch remains.
+// 105 vector instructions where four reciprocal estimates with their
+// measured residuals took 129, of which the estimates issue over four
+// cycles each.  With the branch-free Gauss-point values (teno_poly) and the
+// exact weights called instead of inlined, 20 steps of the 2-D four-quadrant
+// problem at 1024^2 take 18.2 ms (21.9 before), 2 steps of the 3-D
+// Taylor-Green vortex at 128^3 24.4 ms (25.1).
 //
-// SEL_RATIO: the fixed ratios of teno_cfg (when TENO_RATIO_OK; no
-// reciprocal at all), then the exact weights.  Smooth data keeps the large
-// stencil there; constant data (the quadratics' indicators vanish exactly,
-// the quartic's keeps a rounding residue) rejects it there with all three
-// quadratics kept.  The 3-D kernels use it (Taylor-Green vortex, smooth;
-// 2.09 ms per face launch, against 2.12 with SEL_FILTER after the ratios
-// and 2.28 with SEL_FILTER alone).  The 1-D and 2-D kernels use SEL_FILTER:
-// on the four-quadrant Riemann problem most wavefronts mix lanes that the
-// ratios decide and lanes they leave open after a few hundred steps (the
-// ratios cost 4 % over 500 steps there, SEL_FILTER saves 3.5 %).
+// SEL_RATIO (the 3-D kernels): the fixed ratios of teno_cfg first (when
+// TENO_RATIO_OK; no powers at all).  Smooth data keeps the large stencil
+// there; constant data (the quadratics' indicators vanish exactly, the
+// quartic's keeps a rounding residue) rejects it there with all three
+// quadratics kept.  Then as SEL_FILTER.
 //
-// A NaN or b >= 1e40 fails the range test (b_0 + .. + b_3 < 1e40) and
-// takes the exact path.  The ratios and margins are literals so that they
-// take no scalar registers (ratios held in the kernel arguments made the
-// 2-D face kernel spill scalar registers into vector lanes).  The
-// operation-counting type always evaluates the exact weights.
+// The operation-counting type always evaluates the exact weights.
 // ---------------------------------------------------------------------------
 constexpr int SEL_EXACT = 0, SEL_FILTER = 1, SEL_RATIO = 2;
 
-template <int MODE = SEL_EXACT, class R>
-TGKS_HD unsigned teno_flag(const R* Q, const TenoCfg& c) {
+template <class R>
+TGKS_HD unsigned teno_exact(const R* Q, const TenoCfg& c) {
 #pragma clang fp contract(off)
   const R a = Q[0], b = Q[1], cc = Q[2], d = Q[3], e = Q[4];
   const double k13 = 13.0 / 12.0;
@@ -178,47 +224,6 @@ TGKS_HD unsigned teno_flag(const R* Q, const TenoCfg& c) {
   const R s2 = P2 + (123.0 / 455.0) * P4;
   beta[3] = (((s1 * s1) + (13.0 / 3.0) * (s2 * s2)) + (781.0 / 20.0) * (P3 * P3)) +
             (1421461.0 / 2275.0) * (P4 * P4);
-  if constexpr (MODE == SEL_RATIO && std::is_same_v<R, double>) {
-    if (c.fast & TENO_RATIO_OK) {
-      const R b0 = beta[0] + c.eps, b1 = beta[1] + c.eps, b2 = beta[2] + c.eps, b3 = beta[3] + c.eps;
-      if ((b0 + b1) + (b2 + b3) < 1e40) {
-        const R m = fmin(fmin(b0, b1), b2);
-        if (b3 <= 4.0 * m) return 1u;
-        if (b3 > 16.0 * m) {
-          const R lo = 4.0 * m, hi = 8.0 * m;
-          const bool sure = !(b0 > lo && b0 <= hi) && !(b1 > lo && b1 <= hi) && !(b2 > lo && b2 <= hi);
-          if (sure) return (b0 <= lo ? 2u : 0u) | (b1 <= lo ? 4u : 0u) | (b2 <= lo ? 8u : 0u);
-        }
-      }
-    }
-  }
-  if constexpr (MODE == SEL_FILTER && std::is_same_v<R, double>) {
-    if (c.fast & TENO_FILTER_OK) {
-      const R b0 = beta[0] + c.eps, b1 = beta[1] + c.eps, b2 = beta[2] + c.eps, b3 = beta[3] + c.eps;
-      const bool inr = (b0 + b1) + (b2 + b3) < 1e40;
-      // every comparison evaluated, one branch to the exact weights
-      R p[4], r[4], es = R(0.0);
-      const R bb[4] = {b0, b1, b2, b3};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const R x2 = bb[k] * bb[k];
-        const R x4 = x2 * x2;
-        p[k] = (x4 * x2) * bb[k];
-        r[k] = rcp_approx(p[k]);
-        es += fabs(fma(-p[k], r[k], 1.0));
-      }
-      const R s3 = (r[0] + r[1]) + r[2];
-      const R th1 = c.ct1 * (s3 + r[3]), th2 = c.ct2 * s3;
-      const double up = 1.0 + 0x1p-12, dn = 1.0 - 0x1p-12;
-      const R h2 = th2 * up, l2 = th2 * dn;
-      const bool keep = r[3] > th1 * up, rej = r[3] < th1 * dn;
-      const bool k0 = r[0] > h2, k1 = r[1] > h2, k2 = r[2] > h2;
-      // (bitwise operators: no short-circuit branches)
-      const bool sure = inr & (es <= 0x1p-18) &
-                        (keep | (rej & (k0 | (r[0] < l2)) & (k1 | (r[1] < l2)) & (k2 | (r[2] < l2))));
-      if (sure) return keep ? 1u : ((k0 ? 2u : 0u) | (k1 ? 4u : 0u) | (k2 ? 8u : 0u));
-    }
-  }
   R g[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -244,6 +249,115 @@ TGKS_HD unsigned teno_flag(const R* Q, const TenoCfg& c) {
   return f;
 }
 
+// 2^-e for a normal x in [2^e, 2^(e+1)), e > -1023: the exponent mirrored
+TGKS_HD double scale_of(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __hiloint2double(0x7fe00000 - (__double2hiint(x) & 0x7ff00000), 0);
+#else
+  uint64_t u;
+  __builtin_memcpy(&u, &x, sizeof u);
+  u = 0x7fe0000000000000ull - (u & 0x7ff0000000000000ull);
+  double r;
+  __builtin_memcpy(&r, &u, sizeof r);
+  return r;
+#endif
+}
+
+// the certain decisions; false where the exact weights have to decide
+template <int MODE>
+TGKS_HD bool teno_certain(const double* Q, const TenoParts<double>& p, const TenoCfg& c, TenoSel& s) {
+#pragma clang fp contract(off)
+  // Y2 = 56 P2 of the quartic indicator in the oracle's order; s1 = 12 (P1 +
+  // P3 / 10), s2 = 56 (P2 + 123/455 P4)
+  const double Y2 = (((40.0 * Q[1] - 3.0 * Q[0]) - 74.0 * Q[2]) + 40.0 * Q[3]) - 3.0 * Q[4];
+  const double s1 = fma(8.0, p.x, -p.y), s2 = fma(41.0 / 65.0, p.y4, Y2);
+  const double k = 13.0 / 3.0;
+  const double b0 = fma(k, p.t[0] * p.t[0], fma(p.l0, p.l0, c.eps4));
+  const double b1 = fma(k, p.t[1] * p.t[1], fma(p.x, p.x, c.eps4));
+  const double b2 = fma(k, p.t[2] * p.t[2], fma(p.l2, p.l2, c.eps4));
+  const double b3 = fma(13.0 / 2352.0, s2 * s2,
+                        fma(1.0 / 36.0, s1 * s1,
+                            fma(1421461.0 / 327600.0, p.y4 * p.y4, fma(781.0 / 720.0, p.y3 * p.y3, c.eps4))));
+  const double m = fmin(fmin(b0, b1), b2);
+  // a NaN or an infinite input makes b3 a NaN or infinite
+  const bool inr = (b3 < 1e40) & (m < 1e40);
+  if (MODE == SEL_RATIO) {
+    if (c.fast & TENO_RATIO_OK) {
+      if (inr) {
+        if (b3 <= 4.0 * m) {
+          s = TenoSel{true, false, false, false};
+          return true;
+        }
+        if (b3 > 16.0 * m) {
+          const double lo = 4.0 * m, hi = 8.0 * m;
+          const bool sure = !(b0 > lo && b0 <= hi) && !(b1 > lo && b1 <= hi) && !(b2 > lo && b2 <= hi);
+          if (sure) {
+            s = TenoSel{false, b0 <= lo, b1 <= lo, b2 <= lo};
+            return true;
+          }
+        }
+      }
+    }
+  }
+  if (!(c.fast & TENO_FILTER_OK)) return false;
+  const double sc = scale_of(m);
+  const double bb[4] = {b0, b1, b2, b3};
+  double q[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double t = fmin(bb[i] * sc, 2048.0);
+    const double t2 = t * t;
+    q[i] = (t2 * t2) * (t2 * t);
+  }
+  const double q01 = q[0] * q[1], q12 = q[1] * q[2], q02 = q[0] * q[2];
+  const double S = (q01 + q12) + q02, P = q01 * q[2];
+  const double X = fma(S, q[3], P);
+  const double hi = S * c.ct2_up, lo = S * c.ct2_dn;
+  const bool keep = P > X * c.ct1_up, rej = P < X * c.ct1_dn;
+  const bool k0 = q12 > hi, k1 = q02 > hi, k2 = q01 > hi;
+  const bool sure = inr & (keep | (rej & (k0 | (q12 < lo)) & (k1 | (q02 < lo)) & (k2 | (q01 < lo))));
+  s = TenoSel{keep, k0, k1, k2};
+  return sure;
+}
+
+// teno_exact as a function of its own: the rare path of the kernels, called
+// so that its code (four divisions, a power loop) stands once beside their
+// straight-line code
+__host__ __device__ __attribute__((noinline)) inline unsigned teno_exact_cold(double a, double b, double cc, double d,
+                                                                              double e, double ct1, double ct2,
+                                                                              double eps, int q) {
+  const double Q[5] = {a, b, cc, d, e};
+  TenoCfg c{};
+  c.ct1 = ct1;
+  c.ct2 = ct2;
+  c.eps = eps;
+  c.q = q;
+  return teno_exact(Q, c);
+}
+TGKS_HD unsigned teno_exact_cold(const double* Q, const TenoCfg& c) {
+  return teno_exact_cold(Q[0], Q[1], Q[2], Q[3], Q[4], c.ct1, c.ct2, c.eps, c.q);
+}
+
+template <int MODE, class R>
+TGKS_HD TenoSel teno_select(const R* Q, const TenoParts<R>& p, const TenoCfg& c) {
+  if constexpr (MODE != SEL_EXACT && std::is_same_v<R, double>) {
+    TenoSel s;
+    if (!teno_certain<MODE>(Q, p, c, s)) s = teno_sel(teno_exact_cold(Q, c));
+    return s;
+  } else {
+    return teno_sel(teno_exact(Q, c));
+  }
+}
+
+// the flag alone: bit0 = delta_{3,1}; if it is 0, bits 1..3 = delta_{0,2},
+// delta_{1,2}, delta_{2,2}
+template <int MODE = SEL_EXACT, class R>
+TGKS_HD unsigned teno_flag(const R* Q, const TenoCfg& c) {
+  TenoParts<R> p;
+  if constexpr (MODE != SEL_EXACT) teno_parts(Q, p);
+  return teno_select<MODE>(Q, p, c).flag();
+}
+
 // Values and slopes (cell units) at x_{i-1/2} and x_{i+1/2} of the selected
 // reconstruction: out = {v(-1/2), s(-1/2), v(+1/2), s(+1/2)}.
 template <class R>
@@ -252,9 +366,11 @@ TGKS_HD void teno_face(const R* Q, unsigned flag, R* out) {
   const R a = Q[0], b = Q[1], c = Q[2], d = Q[3], e = Q[4];
   if (flag & 1u) {
     // Eq. 4.8, Eq. 4.9 and their mirror images
-    out[2] = ((((2.0 * a - 13.0 * b) + 47.0 * c) + 27.0 * d) - 3.0 * e) * (1.0 / 60.0);
+    // (fma with a power of two: the product is exact, so the result is that
+    // of the separate multiplication and addition)
+    out[2] = (((fma_(R(2.0), a, -(13.0 * b)) + 47.0 * c) + 27.0 * d) - 3.0 * e) * (1.0 / 60.0);
     out[3] = (((b - 15.0 * c) + 15.0 * d) - e) * (1.0 / 12.0);
-    out[0] = ((((27.0 * b - 3.0 * a) + 47.0 * c) - 13.0 * d) + 2.0 * e) * (1.0 / 60.0);
+    out[0] = fma_(R(2.0), e, ((27.0 * b - 3.0 * a) + 47.0 * c) - 13.0 * d) * (1.0 / 60.0);
     out[1] = (((a - 15.0 * b) + 15.0 * c) - d) * (1.0 / 12.0);
     return;
   }
@@ -265,70 +381,73 @@ TGKS_HD void teno_face(const R* Q, unsigned flag, R* out) {
   const int cnt = (int)((flag >> 1) & 1u) + (int)((flag >> 2) & 1u) + (int)((flag >> 3) & 1u);
   const double om = cnt == 1 ? 1.0 : (cnt == 2 ? 0.5 : 1.0 / 3.0);
   const R o0 = R((flag & 2u) ? om : 0.0), o1 = R((flag & 4u) ? om : 0.0), o2 = R((flag & 8u) ? om : 0.0);
-  const R vp0 = ((2.0 * a - 7.0 * b) + 11.0 * c) * (1.0 / 6.0);
-  const R vp1 = ((5.0 * c - b) + 2.0 * d) * (1.0 / 6.0);
-  const R vp2 = ((2.0 * c + 5.0 * d) - e) * (1.0 / 6.0);
-  const R dp0 = (a - 3.0 * b) + 2.0 * c;
+  const R vp0 = (fma_(R(2.0), a, -(7.0 * b)) + 11.0 * c) * (1.0 / 6.0);
+  const R vp1 = fma_(R(2.0), d, 5.0 * c - b) * (1.0 / 6.0);
+  const R vp2 = (fma_(R(2.0), c, 5.0 * d) - e) * (1.0 / 6.0);
+  const R dp0 = fma_(R(2.0), c, a - 3.0 * b);
   const R dp12 = d - c;
-  const R vm0 = ((5.0 * b - a) + 2.0 * c) * (1.0 / 6.0);
-  const R vm1 = ((2.0 * b + 5.0 * c) - d) * (1.0 / 6.0);
-  const R vm2 = ((11.0 * c - 7.0 * d) + 2.0 * e) * (1.0 / 6.0);
+  const R vm0 = fma_(R(2.0), c, 5.0 * b - a) * (1.0 / 6.0);
+  const R vm1 = (fma_(R(2.0), b, 5.0 * c) - d) * (1.0 / 6.0);
+  const R vm2 = fma_(R(2.0), e, 11.0 * c - 7.0 * d) * (1.0 / 6.0);
   const R dm01 = c - b;
-  const R dm2 = (3.0 * d - 2.0 * c) - e;
-  const R z = R(0.0);
-  out[0] = ((z + o0 * vm0) + o1 * vm1) + o2 * vm2;
-  out[1] = ((z + o0 * dm01) + o1 * dm01) + o2 * dm2;
-  out[2] = ((z + o0 * vp0) + o1 * vp1) + o2 * vp2;
-  out[3] = ((z + o0 * dp0) + o1 * dp12) + o2 * dp12;
+  const R dm2 = fma_(R(-2.0), c, 3.0 * d) - e;
+  out[0] = (o0 * vm0 + o1 * vm1) + o2 * vm2;
+  out[1] = (o0 * dm01 + o1 * dm01) + o2 * dm2;
+  out[2] = (o0 * vp0 + o1 * vp1) + o2 * vp2;
+  out[3] = (o0 * dp0 + o1 * dp12) + o2 * dp12;
 }
 
-// Selected polynomial at the Gauss points s = -+1/(2 sqrt 3) (cell units):
-// val[m], der[m] for m = 0 (s-) and 1 (s+).  The values feed only the flux,
-// so contraction is allowed here.
+// The selected polynomial at the Gauss points +-s, s = 1/(2 sqrt 3) (cell
+// units): p(+-s) = base +- odd, p'(+-s) = ev +- od.
+//
+// s^2 = 1/12, so a quadratic with cell average c takes the values
+// c +- s p'(0) there, and the quartic of the five averages the values
+// c - y4 / 4320 +- s (x / 2 - 7/72 y3) with the derivatives
+// (x / 2 - y3 / 12) +- s (t1 - y4 / 9): the middle quadratic (slope x / 2,
+// second difference t1) plus terms in the third and fourth differences.  One
+// branch-free form therefore serves both: the surviving quadratics' mean
+// (large stencil: the middle one alone) plus those terms where the large
+// stencil is kept.  About 35 operations, most of them on differences that
+// the selection has formed; a branch per kind took 66 in wavefronts that mix
+// them.  The one-sided slopes and the fourth difference are formed from the
+// second differences here: constant data then has no rounding residue at
+// all (the selection's own have one, in the oracle's order), so a flow that
+// is uniform along the face stays so to the last bit.
+template <class R>
+struct TenoPoly {
+  R base, odd, ev, od;
+};
+
+template <class R>
+TGKS_HD void teno_poly(const TenoParts<R>& p, const TenoSel& s, TenoPoly<R>& o) {
+  const double h = 0.28867513459481288225;  // s = 1/(2 sqrt 3)
+  const R z = R(0.0), one = R(1.0);
+  const R o0 = !s.lg && s.k0 ? one : z, o1 = s.lg || s.k1 ? one : z, o2 = !s.lg && s.k2 ? one : z;
+  const R l0 = fma_(R(2.0), p.c - p.b, p.t[0]), l2 = fma_(R(2.0), p.d - p.c, -p.t[2]);
+  const R y3 = s.lg ? p.y3 : z, y4 = s.lg ? fma_(R(-2.0), p.t[1], p.t[0] + p.t[2]) : z;
+  const R n = (o0 + o1) + o2;
+  // 1/n for n = 1, 2, 3: (11 - 6 n + n^2) / 6
+  const R inv = fma_(n, fma_(n, R(1.0 / 6.0), R(-1.0)), R(11.0 / 6.0));
+  const R l = fma_(o2, l2, fma_(o1, p.x, o0 * l0)) * inv;             // twice the slope
+  const R t = fma_(o2, p.t[2], fma_(o1, p.t[1], o0 * p.t[0])) * inv;  // second difference
+  o.base = fma_(y4, R(-1.0 / 4320.0), p.c);
+  o.odd = (0.5 * h) * fma_(y3, R(-7.0 / 36.0), l);
+  o.ev = 0.5 * fma_(y3, R(-1.0 / 6.0), l);
+  o.od = h * fma_(y4, R(-1.0 / 9.0), t);
+}
+
+// Selected polynomial at the Gauss points: val[m], der[m] for m = 0 (s-) and
+// 1 (s+).  The values feed only the flux.
 template <class R>
 TGKS_HD void teno_gauss(const R* Q, unsigned flag, R* val, R* der) {
-  const R a = Q[0], b = Q[1], c = Q[2], d = Q[3], e = Q[4];
-  const double s = 0.28867513459481288225;  // 1/(2 sqrt 3)
-  R c0, c1, c2, c3 = R(0.0), c4 = R(0.0);
-  if (flag & 1u) {
-    c0 = ((2134.0 * c - 116.0 * (d + b)) + 9.0 * (e + a)) * (1.0 / 1920.0);
-    c1 = (34.0 * (d - b) - 5.0 * (e - a)) * (1.0 / 48.0);
-    c2 = ((12.0 * (d + b) - 22.0 * c) - (e + a)) * (1.0 / 16.0);
-    c3 = ((e - a) - 2.0 * (d - b)) * (1.0 / 12.0);
-    c4 = ((((a - 4.0 * b) + 6.0 * c) - 4.0 * d) + e) * (1.0 / 24.0);
-  } else {
-    const bool k0 = flag & 2u, k1 = flag & 4u, k2 = flag & 8u;
-    const int cnt = (int)k0 + (int)k1 + (int)k2;
-    const double inv = cnt == 1 ? 1.0 : (cnt == 2 ? 0.5 : 1.0 / 3.0);
-    R s0 = R(0.0), s1 = R(0.0), s2 = R(0.0);
-    if (k0) {
-      s0 += (23.0 * c + 2.0 * b - a) * (1.0 / 24.0);
-      s1 += (3.0 * c - 4.0 * b + a) * 0.5;
-      s2 += (c - 2.0 * b + a) * 0.5;
-    }
-    if (k1) {
-      s0 += (26.0 * c - d - b) * (1.0 / 24.0);
-      s1 += (d - b) * 0.5;
-      s2 += (d + b - 2.0 * c) * 0.5;
-    }
-    if (k2) {
-      s0 += (23.0 * c + 2.0 * d - e) * (1.0 / 24.0);
-      s1 += (4.0 * d - 3.0 * c - e) * 0.5;
-      s2 += (c - 2.0 * d + e) * 0.5;
-    }
-    c0 = s0 * inv;
-    c1 = s1 * inv;
-    c2 = s2 * inv;
-  }
-  const double ss = s * s;
-  const R even = c0 + ss * (c2 + ss * c4);  // even part of p at +-s
-  const R odd = s * (c1 + ss * c3);
-  val[0] = even - odd;
-  val[1] = even + odd;
-  const R deven = c1 + (3.0 * ss) * c3;  // even part of p' at +-s
-  const R dodd = s * (2.0 * c2 + (4.0 * ss) * c4);
-  der[0] = deven - dodd;
-  der[1] = deven + dodd;
+  TenoParts<R> p;
+  TenoPoly<R> o;
+  teno_parts(Q, p);
+  teno_poly(p, teno_sel(flag), o);
+  val[0] = o.base - o.odd;
+  val[1] = o.base + o.odd;
+  der[0] = o.ev - o.od;
+  der[1] = o.ev + o.od;
 }
 
 // teno_gauss in one fixed evaluation order without contraction: the 3-D
@@ -379,15 +498,6 @@ TGKS_HD void teno_gauss_exact(const R* Q, unsigned flag, R* val, R* der) {
   const R dodd = s * (2.0 * c2 + (4.0 * ss) * c4);
   der[0] = deven - dodd;
   der[1] = deven + dodd;
-}
-
-// The selected polynomial at one Gauss point m (0: s-, 1: s+), cell units.
-template <class R>
-TGKS_HD void teno_gauss_at(const R* Q, unsigned flag, int m, R& val, R& der) {
-  R v[2], d[2];
-  teno_gauss(Q, flag, v, d);
-  val = m ? v[1] : v[0];
-  der = m ? d[1] : d[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -1420,17 +1530,19 @@ TGKS_HD void side_sum(const SidePart<D, R>& l, const SidePart<D, R>& r, SidePart
 }
 
 // Time-integrated flux F(dt) and F(dt/2) at one Gauss point.
-// Wl, Wr: states; dWl[d], dWr[d]: derivatives along frame axis d.
+// Wl, Wr: states; dWl[d], dWr[d]: derivatives along frame axis d; sgn = 1:
+// Wl is the left side (u1 > 0), -1: the right one (and Wr the left; the two
+// sides' shares are added, so the order does not matter).
 // Returns false when a state is non-physical.
 template <int D, bool NS, class R>
 TGKS_HD bool gp_flux(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const FluxCfg& P,
-                     R dt, R* Fdt, R* Fh) {
+                     R dt, R* Fdt, R* Fh, double sgn = 1.0) {
   constexpr int NC = D + 2;
   Gas<D, R> gl, gr, g0;
   R hl0, hl1, hr0, hr1, wl[NC], wr[NC], W0[NC];
   // equilibrium state by kinetic weighting (Eq. 2.6): rho_l <psi>_{>0} + rho_r <psi>_{<0}
-  side_w0<D>(Wl, P, 1.0, gl, hl0, hl1, wl);
-  side_w0<D>(Wr, P, -1.0, gr, hr0, hr1, wr);
+  side_w0<D>(Wl, P, sgn, gl, hl0, hl1, wl);
+  side_w0<D>(Wr, P, -sgn, gr, hr0, hr1, wr);
 #pragma unroll
   for (int q = 0; q < NC; ++q) W0[q] = wl[q] + wr[q];
   make_gas<D>(W0, P.N, g0);
@@ -1451,12 +1563,12 @@ TGKS_HD bool gp_flux(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*
 // otherwise W0 is the kinetic weighting of the two sides (Eq. 2.6).
 template <int D, bool NS, class R>
 TGKS_HD bool gp_flux_eq(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const R* W0in,
-                        const R (*dW0)[D + 2], const FluxCfg& P, R dt, R* Fdt, R* Fh) {
+                        const R (*dW0)[D + 2], const FluxCfg& P, R dt, R* Fdt, R* Fh, double sgn = 1.0) {
   constexpr int NC = D + 2;
   Gas<D, R> gl, gr, g0;
   R hl0, hl1, hr0, hr1, wl[NC], wr[NC], W0[NC];
-  side_w0<D>(Wl, P, 1.0, gl, hl0, hl1, wl);
-  side_w0<D>(Wr, P, -1.0, gr, hr0, hr1, wr);
+  side_w0<D>(Wl, P, sgn, gl, hl0, hl1, wl);
+  side_w0<D>(Wr, P, -sgn, gr, hr0, hr1, wr);
 #pragma unroll
   for (int q = 0; q < NC; ++q) W0[q] = W0in ? W0in[q] : wl[q] + wr[q];
   make_gas<D>(W0, P.N, g0);

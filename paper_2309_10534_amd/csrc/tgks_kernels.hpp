@@ -186,6 +186,24 @@ __device__ __forceinline__ int fallback_side(double* w, double (*dw)[NC], const 
   return 1;
 }
 
+// The selection of five values and the selected polynomial at the Gauss
+// points; returns the flag (unused: not evaluated).  MODE SEL_FILTER or
+// SEL_RATIO: sure becomes false where the exact weights have to decide (the
+// caller then evaluates everything again with SEL_EXACT: one branch for all
+// its selections, which leaves them one straight line of code).
+template <int MODE>
+__device__ __forceinline__ unsigned select_poly(const double* Q, const TenoCfg& c, TenoPoly<double>& o, bool& sure) {
+  TenoParts<double> p;
+  teno_parts(Q, p);
+  TenoSel s;
+  if (MODE == SEL_EXACT)
+    s = teno_sel(teno_exact_cold(Q, c));
+  else
+    sure &= teno_certain<MODE>(Q, p, c, s);
+  teno_poly(p, s, o);
+  return s.flag();
+}
+
 template <int NC>
 __device__ __forceinline__ void write_combined(int STAGE, const double* Fdt, const double* Fh, double w,
                                                double* accA, double* accB) {
@@ -248,8 +266,7 @@ __device__ __forceinline__ void face1d_body(const StageArgs& a, int f) {
         Q[r] = EX ? cell_value(a.g, a.pb, a.W, c, f - 3 + r, 0, tb) : load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
       double o[4];
       if (SCHEME == SCHEME_TENO_D) {
-        const unsigned fl = teno_flag<SEL_FILTER>(Q, a.tn);
-        teno_face(Q, fl, o);
+        teno_face(Q, teno_flag<SEL_FILTER>(Q, a.tn), o);
         Wl[c] = o[2];
         dWl[0][c] = o[3] * idx;
         const unsigned fr = teno_flag<SEL_FILTER>(Q + 1, a.tn);
@@ -529,7 +546,10 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   // 3. lanes 2k and 2k+1 share face k.  Lane m reconstructs side m (left: 0,
   //    right: 1) along the face at both Gauss points, keeps Gauss point m and
   //    hands Gauss point 1-m to its partner; each lane then evaluates the
-  //    flux at its Gauss point m and the pair sums the two.
+  //    flux at its Gauss point m and the pair sums the two.  The flux takes
+  //    the lane's own side first, with its sign (+1 left, -1 right): the two
+  //    sides' shares are added in either order with the same result, so no
+  //    lane has to sort them.
   const int m = tid & 1;
   const int fi = tid >> 1;
   const int fn = fi % TN, ft = fi / TN;
@@ -538,17 +558,23 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   const long long nf = face_count(g, AX);
   const long long fidx = AX == 0 ? (long long)t * (g.n[0] + 1) + f : (long long)f * g.n[0] + t;
   const double idt = 1.0 / g.dx[TA];
-  double Wg[2][NC], Dg[2][2][NC];  // [side][q], [side][axis n/t][q]
+  double Wo[NC], Do[2][NC], Wp[NC], Dp[2][NC];  // own and partner's side; slopes [axis n/t][q]
+  const double sg = m ? 1.0 : -1.0;             // sign of the lane's Gauss point; -sg: of its side
   const int nr = m == 0 ? fn : fn + 1;
   const int vo = m == 0 ? 2 : 0;
-  if (CHAR) {
-    // fields of the basis along the face at this face's reference state
-    // (cells f-1 and f of row t); each field of W and of W_n is selected and
-    // evaluated at both Gauss points, then projected back
-    double aV[NC][2], aD[NC][2], aN[NC][2];
+  // value, derivative along the face and normal slope of the lane's side at
+  // its own Gauss point (index 0) and at its partner's (1); false where a
+  // selection needs the exact weights
+  double gV[NC][2], gD[NC][2], gN[NC][2];
+  auto tangential = [&](auto mode) {
+    constexpr int MODE = decltype(mode)::value;
+    bool sure = true;
+    if (CHAR) {
+      // fields of the basis along the face at this face's reference state
+      // (cells f-1 and f of row t); each field of W and of W_n is selected,
+      // evaluated and projected back
 #pragma unroll
-    for (int q = 0; q < NC; ++q) aV[q][0] = aV[q][1] = aD[q][0] = aD[q][1] = aN[q][0] = aN[q][1] = 0.0;
-    if (live) {
+      for (int q = 0; q < NC; ++q) gV[q][0] = gV[q][1] = gD[q][0] = gD[q][1] = gN[q][0] = gN[q][1] = 0.0;
       double Wb[NC], Lt[NC][NC], Rt[NC][NC];
       {
 #pragma clang fp contract(off)
@@ -570,15 +596,15 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
           Qw[r] = char_dot<NC>(Lt[k], xw);
           Qn[r] = char_dot<NC>(Lt[k], xn);
         }
-        const unsigned fw = teno_flag<SEL_FILTER>(Qw, a.tt);
-        const unsigned fq = teno_flag<SEL_FILTER>(Qn, a.tt);
+        TenoPoly<double> w, n;
+        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure), fq = select_poly<MODE>(Qn, a.tt, n, sure);
         if (FLAGS) {
           a.tflags[((long long)(0 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fw;
           a.tflags[((long long)(1 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fq;
         }
-        double v[2], dv[2], vn[2], dvn[2];
-        teno_gauss(Qw, fw, v, dv);
-        teno_gauss(Qn, fq, vn, dvn);
+        const double v[2] = {fma(sg, w.odd, w.base), fma(-sg, w.odd, w.base)};
+        const double dv[2] = {fma(sg, w.od, w.ev), fma(-sg, w.od, w.ev)};
+        const double vn[2] = {fma(sg, n.odd, n.base), fma(-sg, n.odd, n.base)};
         {
           // back-projection: dense sums in field order, no contraction
 #pragma clang fp contract(off)
@@ -586,33 +612,16 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
           for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int gp = 0; gp < 2; ++gp) {
-              aV[q][gp] = aV[q][gp] + Rt[q][k] * v[gp];
-              aD[q][gp] = aD[q][gp] + Rt[q][k] * dv[gp];
-              aN[q][gp] = aN[q][gp] + Rt[q][k] * vn[gp];
+              gV[q][gp] = gV[q][gp] + Rt[q][k] * v[gp];
+              gD[q][gp] = gD[q][gp] + Rt[q][k] * dv[gp];
+              gN[q][gp] = gN[q][gp] + Rt[q][k] * vn[gp];
             }
         }
       }
-    }
+    } else {
 #pragma unroll
-    for (int q = 0; q < NC; ++q) {
-      // selects, not an index by the lane's m (which would place the
-      // arrays in scratch memory)
-      const double sv = m ? aV[q][0] : aV[q][1], sd = m ? aD[q][0] : aD[q][1], sn = m ? aN[q][0] : aN[q][1];
-      const double rv = lane_xor<1>(sv), rd = lane_xor<1>(sd), rn = lane_xor<1>(sn);
-      const double ov = m ? aV[q][1] : aV[q][0], od = m ? aD[q][1] : aD[q][0], on = m ? aN[q][1] : aN[q][0];
-      Wg[0][q] = m == 0 ? ov : rv;
-      Wg[1][q] = m == 0 ? rv : ov;
-      Dg[0][1][q] = (m == 0 ? od : rd) * idt;
-      Dg[1][1][q] = (m == 0 ? rd : od) * idt;
-      Dg[0][0][q] = m == 0 ? on : rn;
-      Dg[1][0][q] = m == 0 ? rn : on;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < NC; ++q) {
-      const int c = perm[q];
-      double v[2] = {0, 0}, dv[2] = {0, 0}, vn[2] = {0, 0}, dvn[2];
-      if (live) {
+      for (int q = 0; q < NC; ++q) {
+        const int c = perm[q];
         double Qw[5], Qn[5];
 #pragma unroll
         for (int r = 0; r < 5; ++r) {
@@ -621,41 +630,65 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         }
         unsigned fw, fq;
         if (SCHEME == SCHEME_TENO_D) {
-          fw = teno_flag<SEL_FILTER>(Qw, a.tt);
-          fq = teno_flag<SEL_FILTER>(Qn, a.tt);
-          teno_gauss(Qw, fw, v, dv);
-          teno_gauss(Qn, fq, vn, dvn);
+          TenoPoly<double> w, n;
+          fw = select_poly<MODE>(Qw, a.tt, w, sure);
+          fq = select_poly<MODE>(Qn, a.tt, n, sure);
+#pragma unroll
+          for (int gp = 0; gp < 2; ++gp) {
+            const double x = gp == 0 ? sg : -sg;
+            gV[q][gp] = fma(x, w.odd, w.base);
+            gD[q][gp] = fma(x, w.od, w.ev);
+            gN[q][gp] = fma(x, n.odd, n.base);
+          }
         } else {
+          double v[2], dv[2], vn[2], dvn[2];
           fw = scheme_gauss<SCHEME>(Qw, a.sc, v, dv);
           fq = scheme_gauss<SCHEME>(Qn, a.sc, vn, dvn);
+#pragma unroll
+          for (int gp = 0; gp < 2; ++gp) {
+            gV[q][gp] = m ^ gp ? v[1] : v[0];
+            gD[q][gp] = m ^ gp ? dv[1] : dv[0];
+            gN[q][gp] = m ^ gp ? vn[1] : vn[0];
+          }
         }
         if (FLAGS) {
           a.tflags[((long long)(0 * 2 + m) * NC + c) * nf + fidx] = (uint8_t)fw;
           a.tflags[((long long)(1 * 2 + m) * NC + c) * nf + fidx] = (uint8_t)fq;
         }
       }
-      // own side at own Gauss point; the partner's side at this Gauss point
-      // arrives from the partner, which computed it
-      const double sv = m ? v[0] : v[1], sd = m ? dv[0] : dv[1], sn = m ? vn[0] : vn[1];
-      const double rv = lane_xor<1>(sv), rd = lane_xor<1>(sd), rn = lane_xor<1>(sn);
-      const double ov = m ? v[1] : v[0], od = m ? dv[1] : dv[0], on = m ? vn[1] : vn[0];
-      Wg[0][q] = m == 0 ? ov : rv;
-      Wg[1][q] = m == 0 ? rv : ov;
-      Dg[0][1][q] = (m == 0 ? od : rd) * idt;
-      Dg[1][1][q] = (m == 0 ? rd : od) * idt;
-      Dg[0][0][q] = m == 0 ? on : rn;
-      Dg[1][0][q] = m == 0 ? rn : on;
     }
+    return sure;
+  };
+  if (live) {
+    if (SCHEME != SCHEME_TENO_D) {
+      tangential(std::integral_constant<int, SEL_EXACT>());
+    } else {
+      bool sure = false;
+      if (a.tt.fast & TENO_FILTER_OK) sure = tangential(std::integral_constant<int, SEL_FILTER>());
+      if (!sure) tangential(std::integral_constant<int, SEL_EXACT>());
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) gV[q][0] = gV[q][1] = gD[q][0] = gD[q][1] = gN[q][0] = gN[q][1] = 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    Wo[q] = gV[q][0];
+    Do[0][q] = gN[q][0];
+    Do[1][q] = gD[q][0] * idt;
+    Wp[q] = lane_xor<1>(gV[q][1]);
+    Dp[0][q] = lane_xor<1>(gN[q][1]);
+    Dp[1][q] = lane_xor<1>(gD[q][1]) * idt;
   }
   double A[NC] = {0, 0, 0, 0}, B[NC] = {0, 0, 0, 0};
   if (EX && live && a.fallback) {
-    double Cl[NC], Cr[NC];
+    double Co[NC], Cp[NC];  // the cells of the lane's own and of its partner's side
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      Cl[q] = sW[perm[q]][ft + 2][fn + 2];
-      Cr[q] = sW[perm[q]][ft + 2][fn + 3];
+      Co[q] = sW[perm[q]][ft + 2][fn + 2 + m];
+      Cp[q] = sW[perm[q]][ft + 2][fn + 3 - m];
     }
-    const int nfb = fallback_side<NC, 2>(Wg[0], Dg[0], Cl, a.gamma) + fallback_side<NC, 2>(Wg[1], Dg[1], Cr, a.gamma);
+    const int nfb = fallback_side<NC, 2>(Wo, Do, Co, a.gamma) + fallback_side<NC, 2>(Wp, Dp, Cp, a.gamma);
     if (nfb && a.fbc) atomicAdd(a.fbc, (unsigned long long)nfb);
   }
   if (live) {
@@ -683,9 +716,9 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         scheme_gauss<SCHEME_TENO5>(Qx, se, v, d);
         dW0e[0][q] = m ? v[1] : v[0];
       }
-      ok = gp_flux_eq<2, NS>(Wg[0], Wg[1], Dg[0], Dg[1], W0e, dW0e, a.fc, dt, Fdt, Fh);
+      ok = gp_flux_eq<2, NS>(Wo, Wp, Do, Dp, W0e, dW0e, a.fc, dt, Fdt, Fh, -sg);
     } else {
-      ok = gp_flux<2, NS>(Wg[0], Wg[1], Dg[0], Dg[1], a.fc, dt, Fdt, Fh);
+      ok = gp_flux<2, NS>(Wo, Wp, Do, Dp, a.fc, dt, Fdt, Fh, -sg);
     }
     if (!ok) atomicAdd(a.fail, 1ull);
     write_combined<NC>(STAGE, Fdt, Fh, 0.5, A, B);
@@ -927,23 +960,50 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
   const bool live = fp[T1] < g.n[T1] && fp[T2] < g.n[T2];
   const long long fid = ((long long)fp[2] * nfa[1] + fp[1]) * nfa[0] + fp[0];
   const int perm[NC] = {0, 1 + AX, 1 + T1, 1 + T2, 4};
+  const double sg = m3 ? 1.0 : -1.0;  // sign of the lane's T2 point
+  // (cell units) at this lane's T2 point [r][0] and at its partner's [r][1];
+  // false where a selection needs the exact weights
+  double sv[8][2], sd[8][2];
+  auto sweep2 = [&](auto mode) {
+    constexpr int MODE = decltype(mode)::value;
+    bool sure = true;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int it = 2 * r + m3;
+      if (it < 15) {
+        const int q = it / 3, kind = it - 3 * q;
+        const int c = q == 0 ? perm[0] : q == 1 ? perm[1] : q == 2 ? perm[2] : q == 3 ? perm[3] : perm[4];
+        double Q[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) Q[k] = sS[m2][c][j2 + k][j1][2 * kind + m1];
+        TenoPoly<double> w;
+        const unsigned fl = select_poly<MODE>(Q, a.tt, w, sure);
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          const double x = gp == 0 ? sg : -sg;
+          sv[r][gp] = fma(x, w.odd, w.base);
+          sd[r][gp] = fma(x, w.od, w.ev);
+        }
+        if (FLAGS) a.tflags[((long long)4 * NC + ((m1 * 3 + kind) * 2 + m2) * NC + c) * nf + fid] = (uint8_t)fl;
+      } else {
+        sv[r][0] = sv[r][1] = sd[r][0] = sd[r][1] = 0.0;
+      }
+    }
+    return sure;
+  };
+  if (live) {
+    bool sure = false;
+    if (a.tt.fast & TENO_FILTER_OK) sure = sweep2(std::integral_constant<int, SEL_RATIO>());
+    if (!sure) sweep2(std::integral_constant<int, SEL_EXACT>());
+  } else {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) sv[r][0] = sv[r][1] = sd[r][0] = sd[r][1] = 0.0;
+  }
   double item[15], item_d[15];  // at this lane's T2 point: value, T2 derivative (cell units)
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    const int it = 2 * r + m3;
-    double v[2] = {0.0, 0.0}, d[2] = {0.0, 0.0};
-    if (live && it < 15) {
-      const int q = it / 3, kind = it - 3 * q;
-      const int c = q == 0 ? perm[0] : q == 1 ? perm[1] : q == 2 ? perm[2] : q == 3 ? perm[3] : perm[4];
-      double Q[5];
-#pragma unroll
-      for (int k = 0; k < 5; ++k) Q[k] = sS[m2][c][j2 + k][j1][2 * kind + m1];
-      const unsigned fl = teno_flag<SEL_RATIO>(Q, a.tt);
-      teno_gauss(Q, fl, v, d);
-      if (FLAGS) a.tflags[((long long)4 * NC + ((m1 * 3 + kind) * 2 + m2) * NC + c) * nf + fid] = (uint8_t)fl;
-    }
-    const double own = m3 ? v[1] : v[0], own_d = m3 ? d[1] : d[0];
-    const double rcv = lane_xor<2>(m3 ? v[0] : v[1]), rcv_d = lane_xor<2>(m3 ? d[0] : d[1]);
+    const double own = sv[r][0], own_d = sd[r][0];
+    const double rcv = lane_xor<2>(sv[r][1]), rcv_d = lane_xor<2>(sd[r][1]);
     // item 2 r is lane m3 = 0's, item 2 r + 1 lane m3 = 1's
     item[2 * r] = m3 ? rcv : own;
     item_d[2 * r] = m3 ? rcv_d : own_d;

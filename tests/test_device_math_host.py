@@ -221,6 +221,34 @@ def test_teno_flag_shortcut_at_worst_case_bounds(orc, case, ct1, ct2):
     assert len({f for _, f in decided}) == 2, (name, sorted(decided))
 
 
+@pytest.mark.parametrize("ct1,ct2", [(1e-7, 1e-5), (1e-20, 1e-20), (9.9e-21, 1e-5), (0.5, 0.5), (0.51, 1e-5)])
+def test_teno_flag_shortcut_with_spread_indicators(ct1, ct2):
+    """Indicators far apart (ratios around the 2048 at which the shortcuts
+    cut them, exact zeros beside jumps, magnitudes near the largest and the
+    smallest double, infinities and NaN), with cut-offs at and just outside
+    the range in which the shortcuts are on: all evaluations agree."""
+    from paper_2309_10534_amd import tgks
+    p = tgks.tgks_params_default(1, [10], [0.1])
+    p.ct1, p.ct2 = ct1, ct2
+    rng = np.random.default_rng(5)
+    base = [np.array([0.0, 0.0, 0.0, 0.0, 1.0]), np.array([1.0, 0.0, 0.0, 0.0, 0.0]),
+            np.array([0.0, 0.0, 1.0, 0.0, 0.0]), np.array([1.0, 2.0, 3.0, 4.0, 5.0]), np.ones(5)]
+    cases = [q * 10.0 ** x for q in base for x in (-150, -60, -20, -8, 0, 8, 20, 60, 150, 300)]
+    for r in (2.0 ** 10, 2.0 ** 11, 2.0 ** 11 * (1 + 1e-12), 2.0 ** 12, 1e8, 1e16, 1e30):
+        for _ in range(40):
+            q = rng.normal(size=5) * 1e-3
+            q[rng.integers(0, 2) * 4] += np.sqrt(r) * 1e-3 * rng.normal()
+            cases += [q, 1.0 + q, 1e12 * (1.0 + q)]
+    for bad in (np.inf, -np.inf, np.nan):
+        for k in range(5):
+            q = rng.normal(size=5)
+            q[k] = bad
+            cases.append(q)
+    for q in cases:
+        got = [tgks.tgks_teno_flag_host(p, q, fast=m) for m in (0, 1, 2)]
+        assert got[0] == got[1] == got[2], (q.tolist(), got)
+
+
 def test_erfc_series_accuracy():
     """The kernels' erfc (the Chebyshev series of (1 + 2t) exp(t^2) erfc(t)
     in y = (t - 3.75) / (t + 3.75), cut after 23 terms and summed in powers
