@@ -198,6 +198,7 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
     const int nr = m == 0 ? fn : fn + 1;
     const int vo = m == 0 ? 2 : 0;
     double gV[NC][2], gD[NC][2], gN[NC][2];  // at the lane's own Gauss point and at its partner's
+    unsigned given = 0;  // flags of W (bits 8 q) and W_n (8 q + 4) of frame component q
     auto tangential = [&](auto mode) {
       constexpr int MODE = decltype(mode)::value;
       bool sure = true;
@@ -211,7 +212,8 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
           Qn[r] = sR[c][ft + r][nr][vo + 1];
         }
         TenoPoly<double> w, n;
-        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure), fq = select_poly<MODE>(Qn, a.tt, n, sure);
+        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * q)) & 15u);
+        const unsigned fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * q + 4)) & 15u);
         a.TF[((long long)(m * 2 + 0) * NC + c) * nf + fidx] = (uint8_t)fw;
         a.TF[((long long)(m * 2 + 1) * NC + c) * nf + fidx] = (uint8_t)fq;
 #pragma unroll
@@ -226,7 +228,14 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
     };
     bool sure = false;
     if (a.tt.fast & TENO_FILTER_OK) sure = tangential(std::integral_constant<int, SEL_FILTER>());
-    if (!sure) tangential(std::integral_constant<int, SEL_EXACT>());
+    if (!sure) {
+      given = exact_flags(2 * NC, a.tt, [&](int i, double* Q) {
+        const int q = i >> 1, c = q == 1 ? perm[1] : q == 2 ? perm[2] : q;  // mass and energy in place
+#pragma unroll
+        for (int r = 0; r < 5; ++r) Q[r] = sR[c][ft + r][nr][vo + (i & 1)];
+      });
+      tangential(std::integral_constant<int, SEL_GIVEN>());
+    }
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       const double rv = lane_xor<1>(gV[q][1]), rd = lane_xor<1>(gD[q][1]), rn = lane_xor<1>(gN[q][1]);

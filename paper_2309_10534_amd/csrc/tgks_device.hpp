@@ -7,9 +7,9 @@
 //     candidate polynomials of Sec. 3.1-3.2, slopes Eqs. 3.22-3.24).
 //   * Tangential Gauss-point reconstruction (Sec. 3.2 Steps 1-3).
 //   * Gas-kinetic flux at one Gauss point (Sec. 2.1, Eqs. 2.2-2.9 with the
-//     kinetic weighting of Eqs. 3.25-3.26), in closed form: Maxwellian moment
-//     tables by the half-space erfc/exp recursion, closed-form solution of the
-//     micro-slope systems, moment sums over psi.
+//     kinetic weighting of Eqs. 3.25-3.26), in closed form: moments of the
+//     normal velocity by the half-space erfc/exp recursion, micro slopes from
+//     primitive derivatives in the frame of the tangential velocity.
 //
 // The selection arithmetic (smoothness indicators, gamma_k, cut-offs) and the
 // candidate values follow one fixed evaluation order (constant divisors as
@@ -338,11 +338,12 @@ TGKS_HD unsigned teno_exact_cold(const double* Q, const TenoCfg& c) {
   return teno_exact_cold(Q[0], Q[1], Q[2], Q[3], Q[4], c.ct1, c.ct2, c.eps, c.q);
 }
 
-template <int MODE, class R>
+// COLD: the exact weights called (for a kernel with several selections)
+template <int MODE, bool COLD, class R>
 TGKS_HD TenoSel teno_select(const R* Q, const TenoParts<R>& p, const TenoCfg& c) {
   if constexpr (MODE != SEL_EXACT && std::is_same_v<R, double>) {
     TenoSel s;
-    if (!teno_certain<MODE>(Q, p, c, s)) s = teno_sel(teno_exact_cold(Q, c));
+    if (!teno_certain<MODE>(Q, p, c, s)) s = teno_sel(COLD ? teno_exact_cold(Q, c) : teno_exact(Q, c));
     return s;
   } else {
     return teno_sel(teno_exact(Q, c));
@@ -351,11 +352,11 @@ TGKS_HD TenoSel teno_select(const R* Q, const TenoParts<R>& p, const TenoCfg& c)
 
 // the flag alone: bit0 = delta_{3,1}; if it is 0, bits 1..3 = delta_{0,2},
 // delta_{1,2}, delta_{2,2}
-template <int MODE = SEL_EXACT, class R>
+template <int MODE = SEL_EXACT, bool COLD = false, class R>
 TGKS_HD unsigned teno_flag(const R* Q, const TenoCfg& c) {
   TenoParts<R> p;
   if constexpr (MODE != SEL_EXACT) teno_parts(Q, p);
-  return teno_select<MODE>(Q, p, c).flag();
+  return teno_select<MODE, COLD>(Q, p, c).flag();
 }
 
 // Values and slopes (cell units) at x_{i-1/2} and x_{i+1/2} of the selected
@@ -916,8 +917,8 @@ TGKS_HD void char_recon_face(double gamma, const R (*C)[D + 2], const TenoCfg& t
     R V[6];
 #pragma unroll
     for (int r = 0; r < 6; ++r) V[r] = char_dot<NC>(L[k], C[r]);
-    const unsigned f0 = teno_flag<SEL_FILTER>(V, tn);
-    const unsigned f1 = teno_flag<SEL_FILTER>(V + 1, tn);
+    const unsigned f0 = teno_flag<SEL_FILTER, true>(V, tn);
+    const unsigned f1 = teno_flag<SEL_FILTER, true>(V + 1, tn);
     teno_face(V, f0, ol[k]);
     teno_face(V + 1, f1, orr[k]);
     fr[k] = f1;
@@ -954,7 +955,6 @@ struct FluxCfg {
 };
 
 constexpr int NM1 = 7;  // normal moment table <u1^n>, n = 0..6
-constexpr int NMT = 6;  // tangential tables <u_t^n>, n = 0..5
 
 template <int D, class R>
 struct Gas {
@@ -972,6 +972,14 @@ TGKS_HD double rsqrt_(double x) {
   return rsqrt(x);
 #else
   return 1.0 / sqrt(x);
+#endif
+}
+
+// The instruction scheduler moves nothing across this point.
+template <class R>
+TGKS_HD void phase_end() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_sched_barrier(0);
 #endif
 }
 
@@ -1007,22 +1015,6 @@ TGKS_HD void make_gas(const R* W, double N, Gas<D, R>& g) {
   g.h = ((2.0 / N) * re) * ir2;                      // p / rho = 1/(2 lambda)
   g.lam = (0.25 * N) * ((g.rho * g.rho) * (g.rho * inv));
   g.ok = (g.rho > 0.0) && (re > 0.0) && (g.rho < INFINITY) && (re < INFINITY);
-}
-
-template <class R>
-TGKS_HD void full_table(R U, R h, R* m, int n) {
-  m[0] = R(1.0);
-  m[1] = U;
-  for (int k = 1; k + 1 < n; ++k) m[k + 1] = U * m[k] + ((double)k * h) * m[k - 1];
-}
-
-// half-space table from its first two entries
-template <class R>
-TGKS_HD void half_table(R U, R h, R m0, R m1, R* m) {
-  m[0] = m0;
-  m[1] = m1;
-#pragma unroll
-  for (int k = 1; k + 1 < NM1; ++k) m[k + 1] = U * m[k] + ((double)k * h) * m[k - 1];
 }
 
 // erfc(x) given ex2 = exp(-x^2), which the half-space moments need anyway.
@@ -1084,122 +1076,114 @@ TGKS_HD void half_seed(R U, R lam, double sgn, R& m0, R& m1) {
   m1 = U * m0 + ((sgn * 0.28209479177387814347) * ex) * isl;  // 1/(2 sqrt(pi))
 }
 
+// ---------------------------------------------------------------------------
+// The Gauss-point flux.  Every moment it needs has the form <u1^j psi>,
+// <u1^j psi a> or <u1^j c_t psi a> with a microscopic slope a = the
+// logarithmic derivative of a Maxwellian along some direction.  They are
+// evaluated in the frame that moves with the state's tangential velocity
+// (c_t = u_t - U_t), where the odd moments of c_t vanish: with the derivatives
+// (dr = d rho / rho, dU, dh) along the direction, h = p / rho = 1/(2 lambda),
+//   a = al + be u1 + sum_t (dU_t / h) c_t + de (u1^2 + sum_t c_t^2 + xi^2),
+//   de = dh / (2 h^2), be = dU_1 / h - 2 U_1 de,
+// and with M_j = rho <u1^j> (over the half space for a side, the full space
+// for the equilibrium) and E_j = rho <u1^j (a, its even part in c, xi)> =
+// al' M_j + be M_{j+1} + de M_{j+2}, al' = al + (N-1) h de,
+//   rho <u1^j psi' a>     = (E_j, E_{j+1}, dU_t M_j, (E_{j+2} + (N-1) q_j) / 2),
+//   rho <u1^j c_t psi' a> = (dU_t M_j, dU_t M_{j+1}, q_j [t], dU_t (M_{j+2} + (N+1) h M_j) / 2),
+// q_j = h E_j + dh M_j, psi' the collision invariants of that frame.  The
+// convective sums split as u_t a_t = U_t a_t + c_t a_t, and the slope of the
+// time derivative as A = B - sum_t U_t a_t, with B from the Euler equations
+// of the moving frame in primitive variables; a result goes back to the face
+// frame at the end.  Tables of every monomial's moments in the face frame, a
+// linear solve per slope and sums of products took 209 more instructions per
+// lane of the 2-D face kernel (of 2,500) and 225 registers where this takes
+// 145, which is three wavefronts per SIMD instead of two: 20 steps of the
+// 2-D four-quadrant problem at 1024^2 15.5 ms (18.2 before), 2 steps of the
+// 3-D Taylor-Green vortex at 128^3 22.3 ms (24.4).
+// ---------------------------------------------------------------------------
 template <int D, class R>
-struct MomSet {
-  R m1[NM1];
-  R mt[D > 1 ? D - 1 : 1][NMT];
-  R xi1, xi2;  // <xi^2>, <xi^4>
+struct Slope {
+  R r, U[D], h;   // d rho / rho, dU, dh along the direction
+  R al, be, de;   // al', be, de above
 };
 
+// primitive derivatives of the conservative derivative dW
 template <int D, class R>
-TGKS_HD R mono(const MomSet<D, R>& S, int i, int j, int k) {
-  R v = S.m1[i];
-  if (D >= 2) v = v * S.mt[0][j];
-  if (D >= 3) v = v * S.mt[D >= 3 ? 1 : 0][k];
-  return v;
-}
-
-// g[alpha] = <psi_alpha u1^i u2^j u3^k xi^(2l)>, l in {0, 1}
-template <int D, class R>
-TGKS_HD void gpsi(const MomSet<D, R>& S, int i, int j, int k, int l, R* g) {
-  const R base = mono(S, i, j, k);
-  g[0] = l == 0 ? base : base * S.xi1;
-  g[1] = l == 0 ? mono(S, i + 1, j, k) : mono(S, i + 1, j, k) * S.xi1;
-  if (D >= 2) g[2] = l == 0 ? mono(S, i, j + 1, k) : mono(S, i, j + 1, k) * S.xi1;
-  if (D >= 3) g[D >= 3 ? 3 : 0] = l == 0 ? mono(S, i, j, k + 1) : mono(S, i, j, k + 1) * S.xi1;
-  R e = mono(S, i + 2, j, k);
-  if (D >= 2) e = e + mono(S, i, j + 2, k);
-  if (D >= 3) e = e + mono(S, i, j, k + 2);
-  g[D + 1] = l == 0 ? 0.5 * (e + base * S.xi1) : 0.5 * (e * S.xi1 + base * S.xi2);
-}
-
-// out[alpha] (+)= s * <psi_alpha a(psi) u1^i u2^j u3^k>
-template <int D, bool ACC, class R>
-TGKS_HD void mpsia(const MomSet<D, R>& S, const R* a, int i, int j, int k, R s, R* out) {
-  constexpr int NC = D + 2;
-  R g[NC], t[NC], r[NC];
-  gpsi<D>(S, i, j, k, 0, g);
-#pragma unroll
-  for (int q = 0; q < NC; ++q) r[q] = a[0] * g[q];
-  gpsi<D>(S, i + 1, j, k, 0, g);
-#pragma unroll
-  for (int q = 0; q < NC; ++q) r[q] += a[1] * g[q];
-  if (D >= 2) {
-    gpsi<D>(S, i, j + 1, k, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) r[q] += a[2] * g[q];
-  }
-  if (D >= 3) {
-    gpsi<D>(S, i, j, k + 1, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) r[q] += a[D >= 3 ? 3 : 0] * g[q];
-  }
-  gpsi<D>(S, i + 2, j, k, 0, t);
-  if (D >= 2) {
-    gpsi<D>(S, i, j + 2, k, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) t[q] += g[q];
-  }
-  if (D >= 3) {
-    gpsi<D>(S, i, j, k + 2, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) t[q] += g[q];
-  }
-  gpsi<D>(S, i, j, k, 1, g);
-  const R ae = 0.5 * a[NC - 1];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    const R v = r[q] + ae * (t[q] + g[q]);
-    if (ACC)
-      out[q] += s * v;
-    else
-      out[q] = s * v;
-  }
-}
-
-// closed-form solution a of <a psi> = b (per unit density) over the full
-// Maxwellian (U, lambda), N = K + D.
-template <int D, class R>
-TGKS_HD void micro_solve(const Gas<D, R>& g, double N, const R* b, R* a) {
-  R ub = R(0.0), u2 = R(0.0);
+TGKS_HD void slope_prim(const Gas<D, R>& g, double N, const R* dW, Slope<D, R>& s) {
+  s.r = dW[0] * g.irho;
+  R e = dW[D + 1] * g.irho, u2 = R(0.0);
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    ub += g.U[d] * b[d + 1];
+    const R m = dW[d + 1] * g.irho;
+    s.U[d] = m - g.U[d] * s.r;
+    e -= g.U[d] * m;
     u2 += g.U[d] * g.U[d];
   }
-  const R lam = g.lam;
-  const R aE = ((4.0 / N) * (lam * lam)) * ((2.0 * b[D + 1] - 2.0 * ub) + (u2 - N * g.h) * b[0]);
-  R ua = R(0.0);
+  s.h = (2.0 / N) * (e + (0.5 * u2) * s.r) - g.h * s.r;
+}
+
+// the polynomial's coefficients from the primitive derivatives
+template <int D, class R>
+TGKS_HD void slope_poly(const Gas<D, R>& g, Slope<D, R>& s) {
+  const R l2 = 2.0 * g.lam;
+  s.de = s.h * (l2 * g.lam);
+  const R b = s.U[0] * l2 - g.U[0] * s.de;
+  s.be = b - g.U[0] * s.de;
+  s.al = (s.r - g.h * s.de) - g.U[0] * b;
+}
+
+// the slope of the time derivative in the moving frame (Euler equations)
+// from the slopes along the frame axes
+template <int D, class R>
+TGKS_HD void slope_time(const Gas<D, R>& g, double N, const Slope<D, R>* a, Slope<D, R>& b) {
+  R div = a[0].U[0];
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    a[d + 1] = (2.0 * lam) * (b[d + 1] - g.U[d] * b[0]) - g.U[d] * aE;
-    ua += g.U[d] * a[d + 1];
+  for (int d = 1; d < D; ++d) div += a[d].U[d];
+  const R u = g.U[0];
+  b.r = -(u * a[0].r + div);
+#pragma unroll
+  for (int d = 0; d < D; ++d) b.U[d] = -(u * a[0].U[d] + (a[d].h + g.h * a[d].r));
+  b.h = -(u * a[0].h + (2.0 / N) * (g.h * div));
+  slope_poly<D>(g, b);
+}
+
+template <int D, class R>
+TGKS_HD R slope_e(const R* M, const Slope<D, R>& s, int j) {
+  return s.al * M[j] + (s.be * M[j + 1] + s.de * M[j + 2]);
+}
+
+// v = rho <u1^j psi' a>
+template <int D, class R>
+TGKS_HD void slope_vec(const R* M, const Gas<D, R>& g, double N, const Slope<D, R>& s, int j, R* v) {
+  const R e = slope_e<D>(M, s, j);
+  v[0] = e;
+  v[1] = slope_e<D>(M, s, j + 1);
+#pragma unroll
+  for (int d = 1; d < D; ++d) v[d + 1] = s.U[d] * M[j];
+  v[D + 1] = 0.5 * (slope_e<D>(M, s, j + 2) + (N - 1.0) * (g.h * e + s.h * M[j]));
+}
+
+// v += rho <u1^j c_t psi' a>
+template <int D, class R>
+TGKS_HD void slope_vec_c(const R* M, const Gas<D, R>& g, double N, const Slope<D, R>& s, int t, int j, R* v) {
+  v[0] += s.U[t] * M[j];
+  v[1] += s.U[t] * M[j + 1];
+  v[t + 1] += g.h * slope_e<D>(M, s, j) + s.h * M[j];
+  v[D + 1] += (0.5 * s.U[t]) * (M[j + 2] + ((N + 1.0) * g.h) * M[j]);
+}
+
+// moments of psi' to moments of psi (the face frame)
+template <int D, class R>
+TGKS_HD void to_face(const Gas<D, R>& g, R* v) {
+#pragma unroll
+  for (int t = 1; t < D; ++t) {
+    v[D + 1] += g.U[t] * (v[t + 1] + (0.5 * g.U[t]) * v[0]);
+    v[t + 1] += g.U[t] * v[0];
   }
-  a[D + 1] = aE;
-  a[0] = (b[0] - ua) - (0.5 * aE) * (u2 + N * g.h);
-}
-
-template <int D, class R>
-TGKS_HD void tangential_tables(const Gas<D, R>& g, MomSet<D, R>& S) {
-#pragma unroll
-  for (int d = 1; d < D; ++d) full_table(g.U[d], g.h, S.mt[d - 1], NMT);
-}
-
-template <int D, class R>
-TGKS_HD void xi_moments(const Gas<D, R>& g, double K, MomSet<D, R>& S) {
-  S.xi1 = K * g.h;
-  S.xi2 = (K * (K + 2.0)) * (g.h * g.h);
-}
-
-// (i, j, k) exponents of u_d
-TGKS_HD void unit(int d, int& i, int& j, int& k) {
-  i = d == 0;
-  j = d == 1;
-  k = d == 2;
 }
 
 // heat-flux moment <phi X> from <u1 psi X> (f1) and <psi X> (f0):
-// phi = (u1 - c1)(psi_E - c.u + |c|^2/2), c = U0 (face frame)
+// phi = (u1 - c1)(psi_E - c.u + |c|^2/2) about the velocity c
 template <int D, class R>
 TGKS_HD R heat_combine(const R* f1, const R* f0, const R* c) {
   R c2 = R(0.0), s1 = f1[D + 1], s0 = f0[D + 1];
@@ -1214,94 +1198,65 @@ TGKS_HD R heat_combine(const R* f1, const R* f0, const R* c) {
   return s1 - c[0] * s0;
 }
 
-// Directional derivatives of closed-form moments of a Maxwellian g(W).
-// The derivative of g along a change dW of its conservative variables is
-// g a(psi) with <a psi> = dW / rho, so every full-space moment of g a(psi)
-// is the directional derivative of the corresponding moment of g:
-//   rho <u_k psi a>      = J_k(W) dW     (Euler flux F_k = rho <u_k psi>)
-//   rho <u_1 u_d psi a>  = dG_1d(W) dW   (G_1d = rho <u_1 u_d psi>)
-// which replaces micro-slope solves and moment sums over the full space.
-template <int D, class R>
-struct Prim {
-  R dU[D], dp, dh;
-};
-
-template <int D, class R>
-TGKS_HD void prim_dir(const Gas<D, R>& g, double N, const R* dW, Prim<D, R>& o) {
-  R udm = R(0.0), u2 = R(0.0);
+// moments M[0..6] of one Maxwellian from the first two
+template <class R>
+TGKS_HD void moment_table(R U, R h, R m0, R m1, R* m) {
+  m[0] = m0;
+  m[1] = m1;
 #pragma unroll
-  for (int e = 0; e < D; ++e) {
-    o.dU[e] = (dW[e + 1] - g.U[e] * dW[0]) * g.irho;
-    udm += g.U[e] * dW[e + 1];
-    u2 += g.U[e] * g.U[e];
-  }
-  // p = (2/N)(E - rho |U|^2 / 2)
-  o.dp = (2.0 / N) * ((dW[D + 1] - udm) + (0.5 * u2) * dW[0]);
-  o.dh = (o.dp - g.h * dW[0]) * g.irho;
+  for (int k = 1; k + 1 < NM1; ++k) m[k + 1] = U * m[k] + ((double)k * h) * m[k - 1];
 }
 
-// out = J_k(W) dW, the Euler flux along frame axis k differentiated along dW
-template <int D, class R>
-TGKS_HD void euler_jvp(const Gas<D, R>& g, R E, int k, const R* dW, const Prim<D, R>& d, R* out) {
-  const R p = g.rho * g.h;
-  const R mk = g.rho * g.U[k];
-  out[0] = dW[k + 1];
+// v2 = rho sum_d <u1 u_d psi a_d>, v3 = rho <u1 psi A>, face frame; HEAT: y2,
+// y3 their heat-flux moments about the velocity c (moving frame)
+template <int D, bool HEAT, class R>
+TGKS_HD void slope_parts(const R* M, const Gas<D, R>& g, double N, const Slope<D, R>* a, const R* c, R* v2, R* v3,
+                         R& y2, R& y3) {
+  constexpr int NC = D + 2;
+  Slope<D, R> b;
+  slope_time<D>(g, N, a, b);
+  slope_vec<D>(M, g, N, a[0], 2, v2);
+  slope_vec<D>(M, g, N, b, 1, v3);
 #pragma unroll
-  for (int e = 0; e < D; ++e) {
-    R v = dW[k + 1] * g.U[e] + mk * d.dU[e];
-    if (e == k) v += d.dp;
-    out[e + 1] = v;
-  }
-  out[D + 1] = d.dU[k] * (E + p) + g.U[k] * (dW[D + 1] + d.dp);
-}
-
-// out = dG_1d(W) dW with G_1d = rho <u_1 u_d psi> (frame axis 0 normal):
-//   alpha 0: rho U1 Ud + p [d=0]
-//   alpha e: rho U1 Ud Ue + p (U1 [d=e] + Ud [e=0] + Ue [d=0])
-//   alpha E: rho U1 Ud (|U|^2 + (N+4) h)/2 + [d=0] p (|U|^2 + (N+2) h)/2
-template <int D, class R>
-TGKS_HD void g1d_jvp(const Gas<D, R>& g, double N, int d, const R* dW, const Prim<D, R>& q, R* out) {
-  const R p = g.rho * g.h;
-  const R dp = q.dp;
-  R u2 = R(0.0), udu = R(0.0);
+  for (int t = 1; t < D; ++t) {
+    R z[NC];
+    slope_vec<D>(M, g, N, a[t], 1, z);
+    slope_vec_c<D>(M, g, N, a[t], t, 1, v2);
 #pragma unroll
-  for (int e = 0; e < D; ++e) {
-    u2 += g.U[e] * g.U[e];
-    udu += g.U[e] * q.dU[e];
+    for (int q = 0; q < NC; ++q) {
+      v2[q] += g.U[t] * z[q];
+      v3[q] -= g.U[t] * z[q];
+    }
   }
-  const R A = g.U[0] * g.U[d];
-  const R dA = q.dU[0] * g.U[d] + g.U[0] * q.dU[d];
-  const R dr = dW[0];
-  const R rdA = dr * A + g.rho * dA;  // d(rho A)
-  out[0] = d == 0 ? rdA + dp : rdA;
-  const R rA = g.rho * A;
+  if (HEAT) {
+    R w2[NC], w3[NC];
+    slope_vec<D>(M, g, N, a[0], 1, w2);
+    slope_vec<D>(M, g, N, b, 0, w3);
 #pragma unroll
-  for (int e = 0; e < D; ++e) {
-    R v = rdA * g.U[e] + rA * q.dU[e];
-    if (d == e) v += dp * g.U[0] + p * q.dU[0];
-    if (e == 0) v += dp * g.U[d] + p * q.dU[d];
-    if (d == 0) v += dp * g.U[e] + p * q.dU[e];
-    out[e + 1] = v;
+    for (int t = 1; t < D; ++t) {
+      R z[NC];
+      slope_vec<D>(M, g, N, a[t], 0, z);
+      slope_vec_c<D>(M, g, N, a[t], t, 0, w2);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        w2[q] += g.U[t] * z[q];
+        w3[q] -= g.U[t] * z[q];
+      }
+    }
+    y2 = heat_combine<D>(v2, w2, c);
+    y3 = heat_combine<D>(v3, w3, c);
   }
-  const R Q = u2 + (N + 4.0) * g.h;
-  const R dQ = 2.0 * udu + (N + 4.0) * q.dh;
-  R vE = rdA * Q + rA * dQ;
-  if (d == 0) {
-    const R Rr = u2 + (N + 2.0) * g.h;
-    const R dRr = 2.0 * udu + (N + 2.0) * q.dh;
-    vE += dp * Rr + p * dRr;
-  }
-  out[D + 1] = 0.5 * vE;
+  to_face<D>(g, v2);
+  to_face<D>(g, v3);
 }
 
 // ---------------------------------------------------------------------------
-// The Gauss-point flux in three pieces, for kernels that give the two sides
-// of a Gauss point to two lanes: each lane evaluates its side's share of the
-// equilibrium state (side_w0) and, once W0 is known, its side's shares of
-// the slopes of W0 and of the non-equilibrium moments (side_part); the two
-// shares are summed left + right and flux_combine adds the equilibrium part
-// and the time integration.  gp_flux below evaluates the same arithmetic in
-// one lane.
+// The flux in three pieces, for kernels that give the two sides of a Gauss
+// point to two lanes: each lane evaluates its side's share of the equilibrium
+// state (side_w0) and, once W0 is known, its side's shares of the slopes of
+// W0 and of the non-equilibrium moments (side_part); the two shares are
+// summed and flux_combine adds the equilibrium part and the time integration.
+// gp_flux below evaluates the same arithmetic in one lane.
 // ---------------------------------------------------------------------------
 template <int D, class R>
 struct SidePart {
@@ -1310,159 +1265,79 @@ struct SidePart {
   R H1, H2, H3;             // their heat-flux moments (Navier-Stokes)
 };
 
-// gas state, half-space seeds and the side's share rho_s <psi>_s of W0;
-// sgn = +1 for the left side (u1 > 0), -1 for the right side
+// gas state, rho-weighted half-space seeds (M_0, M_1) and the side's share
+// rho_s <psi>_s of W0; sgn = +1 for the left side (u1 > 0), -1 for the right
 template <int D, class R>
 TGKS_HD void side_w0(const R* Ws, const FluxCfg& P, double sgn, Gas<D, R>& gs, R& h0, R& h1, R* w0) {
-  constexpr int NC = D + 2;
   make_gas<D>(Ws, P.N, gs);
   half_seed(gs.U[0], gs.lam, sgn, h0, h1);
-  MomSet<D, R> S;
-  half_table(gs.U[0], gs.h, h0, h1, S.m1);
-  tangential_tables<D>(gs, S);
-  xi_moments<D>(gs, P.K, S);
-  R g[NC];
-  gpsi<D>(S, 0, 0, 0, 0, g);
+  h0 = gs.rho * h0;
+  h1 = gs.rho * h1;
+  w0[0] = h0;
+  w0[1] = h1;
 #pragma unroll
-  for (int q = 0; q < NC; ++q) w0[q] = gs.rho * g[q];
+  for (int t = 1; t < D; ++t) w0[t + 1] = R(0.0);
+  w0[D + 1] = 0.5 * (gs.U[0] * h1 + (P.N * gs.h) * h0);  // M_2 + (N-1) h M_0, M_2 = U M_1 + h M_0
+  to_face<D>(gs, w0);
 }
 
 template <int D, bool NS, class R>
-TGKS_HD void side_part(const Gas<D, R>& gs, R h0, R h1, const R* Ws, const R (*dW)[D + 2], const FluxCfg& P,
-                       const Gas<D, R>& g0, SidePart<D, R>& o) {
-  constexpr int NC = D + 2;
+TGKS_HD void side_part(const Gas<D, R>& gs, R h0, R h1, const R (*dW)[D + 2], const FluxCfg& P, const Gas<D, R>& g0,
+                       SidePart<D, R>& o) {
   const double N = P.N;
-  MomSet<D, R> Sh;
-  half_table(gs.U[0], gs.h, h0, h1, Sh.m1);
-  tangential_tables<D>(gs, Sh);
-  xi_moments<D>(gs, P.K, Sh);
-  R a[D][NC];
-  R Wt[NC];  // rho <(sum_d u_d a_d) psi> = sum_d J_d dW_d; A^s solves <A psi> = -that / rho
+  R M[NM1];
+  moment_table(gs.U[0], gs.h, h0, h1, M);
+  Slope<D, R> a[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    R b[NC];
-#pragma unroll
-    for (int q = 0; q < NC; ++q) b[q] = dW[d][q] * gs.irho;
-    micro_solve<D>(gs, N, b, a[d]);
-    mpsia<D, false>(Sh, a[d], 0, 0, 0, gs.rho, o.dW0[d]);
-    Prim<D, R> pd;
-    prim_dir<D>(gs, N, dW[d], pd);
-    R jv[NC];
-    euler_jvp<D>(gs, Ws[D + 1], d, dW[d], pd, jv);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) {
-      if (d == 0)
-        Wt[q] = jv[q];
-      else
-        Wt[q] += jv[q];
-    }
+    slope_prim<D>(gs, N, dW[d], a[d]);
+    slope_poly<D>(gs, a[d]);
+    slope_vec<D>(M, gs, N, a[d], 0, o.dW0[d]);
+    to_face<D>(gs, o.dW0[d]);
   }
-  R A[NC];
-  {
-    R b[NC];
+  o.S1[0] = M[1];
+  o.S1[1] = M[2];
 #pragma unroll
-    for (int q = 0; q < NC; ++q) b[q] = -(Wt[q] * gs.irho);
-    micro_solve<D>(gs, N, b, A);
-  }
-  R g[NC];
-  gpsi<D>(Sh, 1, 0, 0, 0, g);
-  R v2[NC];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    int i, j, k;
-    unit(d, i, j, k);
-    if (d == 0)
-      mpsia<D, false>(Sh, a[d], 1 + i, j, k, R(1.0), v2);
-    else
-      mpsia<D, true>(Sh, a[d], 1 + i, j, k, R(1.0), v2);
-  }
-  R v3[NC];
-  mpsia<D, false>(Sh, A, 1, 0, 0, R(1.0), v3);
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    o.S1[q] = gs.rho * g[q];
-    o.S2[q] = gs.rho * v2[q];
-    o.S3[q] = gs.rho * v3[q];
-  }
+  for (int t = 1; t < D; ++t) o.S1[t + 1] = R(0.0);
+  o.S1[D + 1] = 0.5 * (M[3] + ((N - 1.0) * gs.h) * M[1]);
+  R c[D];  // velocity of the equilibrium in the side's moving frame
   o.H1 = o.H2 = o.H3 = R(0.0);
   if (NS) {
-    R f0[NC], w2[NC], w3[NC];
-    gpsi<D>(Sh, 0, 0, 0, 0, f0);
+    c[0] = g0.U[0];
+    R f0[D + 2];
+    f0[0] = M[0];
+    f0[1] = M[1];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      int i, j, k;
-      unit(d, i, j, k);
-      if (d == 0)
-        mpsia<D, false>(Sh, a[d], i, j, k, R(1.0), w2);
-      else
-        mpsia<D, true>(Sh, a[d], i, j, k, R(1.0), w2);
+    for (int t = 1; t < D; ++t) {
+      c[t] = g0.U[t] - gs.U[t];
+      f0[t + 1] = R(0.0);
     }
-    mpsia<D, false>(Sh, A, 0, 0, 0, R(1.0), w3);
-    o.H1 = gs.rho * heat_combine<D>(g, f0, g0.U);
-    o.H2 = gs.rho * heat_combine<D>(v2, w2, g0.U);
-    o.H3 = gs.rho * heat_combine<D>(v3, w3, g0.U);
+    f0[D + 1] = 0.5 * (M[2] + ((N - 1.0) * gs.h) * M[0]);
+    o.H1 = heat_combine<D>(o.S1, f0, c);
   }
+  slope_parts<D, NS>(M, gs, N, a, c, o.S2, o.S3, o.H2, o.H3);
+  to_face<D>(gs, o.S1);
 }
 
-// Equilibrium part of Eq. 2.5 and the time integration over dt and dt/2,
-// given W0, its gas state g0, the two sides' shares summed left + right
-// (dW0, S1..S3, H1..H3) and the side pressures pl, pr (collision time).
-template <int D, bool NS, class R>
-TGKS_HD void flux_combine(const R* W0, const Gas<D, R>& g0, const SidePart<D, R>& T, R pl, R pr,
-                          const FluxCfg& P, R dt, R* Fdt, R* Fh) {
-  constexpr int NC = D + 2;
-  const double N = P.N;
-  const R(*dW0)[NC] = T.dW0;
-  const R *S1 = T.S1, *S2 = T.S2, *S3 = T.S3;
-  const R H1 = T.H1, H2 = T.H2, H3 = T.H3;
-  // equilibrium part of Eq. 2.5, rho0-weighted moments in closed form:
-  //   T1 = rho0 <u1 psi>_0 = F_1(W0)
-  //   W0t = -sum_d J_d(W0) dW0_d = rho0 <Abar psi>_0 (compatibility, Eq. 2.7)
-  //   T2 = rho0 sum_d <u1 u_d psi abar_d>_0 = sum_d dG_1d(W0) dW0_d
-  //   T3 = rho0 <u1 psi Abar>_0 = J_1(W0) W0t
-  R T1[NC], T2[NC], T3[NC], W0t[NC];
-  {
-    const R p0 = g0.rho * g0.h;
-    const R E0 = W0[D + 1];
-    T1[0] = W0[1];
-#pragma unroll
-    for (int e = 0; e < D; ++e) T1[e + 1] = W0[1] * g0.U[e] + (e == 0 ? p0 : R(0.0));
-    T1[D + 1] = g0.U[0] * (E0 + p0);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      Prim<D, R> pd;
-      prim_dir<D>(g0, N, dW0[d], pd);
-      R jv[NC], gv[NC];
-      euler_jvp<D>(g0, E0, d, dW0[d], pd, jv);
-      g1d_jvp<D>(g0, N, d, dW0[d], pd, gv);
-#pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        if (d == 0) {
-          W0t[q] = -jv[q];
-          T2[q] = gv[q];
-        } else {
-          W0t[q] -= jv[q];
-          T2[q] += gv[q];
-        }
-      }
-    }
-    Prim<D, R> pt;
-    prim_dir<D>(g0, N, W0t, pt);
-    euler_jvp<D>(g0, E0, 0, W0t, pt, T3);
-  }
-  R G2 = R(0.0), G3 = R(0.0);  // heat-flux moments of the equilibrium part (the first vanishes)
-  if (NS) {
-    // <psi sum_d u_d abar_d>_0 = -<psi Abar>_0 by the compatibility condition
-    R w2[NC];
-#pragma unroll
-    for (int q = 0; q < NC; ++q) w2[q] = -W0t[q];
-    G2 = heat_combine<D>(T2, w2, g0.U);
-    G3 = heat_combine<D>(T3, W0t, g0.U);
-  }
+// What a kernel takes from a Gauss point, w its weight:
+//   FLUX_TIMES:  Fa = F(dt), Fb = F(dt/2) (w unused)
+//   FLUX_STAGE1: Fa = w F(dt/2), Fb = w (8/3 F(dt/2) - 1/3 F(dt))
+//   FLUX_STAGE2: Fa = w (4/3 F(dt) - 8/3 F(dt/2))
+// The combinations are made of the six time coefficients, not of the fluxes.
+constexpr int FLUX_TIMES = 0, FLUX_STAGE1 = 1, FLUX_STAGE2 = 2;
 
-  // collision time (Sec. 5 preamble); dt is the full step in both stages.
-  // xh = -dt / (2 tau): e^{-dt/tau} = (e^{xh})^2, one expm1 serves both
-  // intervals.
+// Collision time (Sec. 5 preamble; dt is the full step in both stages) and em
+// = expm1(-dt / (2 tau)): e^{-dt/tau} = (1 + em)^2, one exponential serves
+// both intervals; -1 for tau = 0.  Evaluated before the sides' moments: its
+// branches would otherwise end a basic block between them and their use, and
+// the compiler moves all of them past it, where they are live at once.
+template <class R>
+struct FluxTime {
+  R tau, em;
+};
+
+template <int D, class R>
+TGKS_HD FluxTime<R> flux_time(const Gas<D, R>& g0, R pl, R pr, const FluxCfg& P, R dt) {
   const R S = pl + pr, A = fabs(pl - pr);
   R tau = R(0.0), xh = R(0.0);
   if (P.tau_mode == 1) {
@@ -1477,42 +1352,86 @@ TGKS_HD void flux_combine(const R* W0, const Gas<D, R>& g0, const SidePart<D, R>
       xh = -0.5 * ((S * S) * inv);
     }
   }
-  R em = R(0.0);
+  R em = R(-1.0);
   if (tau != 0.0) em = expm1(xh);
+  return FluxTime<R>{tau, em};
+}
 
+// Equilibrium part of Eq. 2.5 and the time integration over dt and dt/2,
+// given W0, its gas state g0, the two sides' summed shares (dW0, S1..S3,
+// H1..H3) and the collision time.
+template <int D, bool NS, int OUT, class R>
+TGKS_HD void flux_combine(const R* W0, const Gas<D, R>& g0, const SidePart<D, R>& T, const FluxTime<R>& ft,
+                          const FluxCfg& P, R dt, double w, R* Fa, R* Fb) {
+  constexpr int NC = D + 2;
+  const double N = P.N;
+  // equilibrium part of Eq. 2.5: T1 = F_1(W0), T2 = rho0 sum_d <u1 u_d psi
+  // abar_d>_0, T3 = rho0 <u1 psi Abar>_0 (Abar by the compatibility
+  // condition, Eq. 2.7: the Euler equations)
+  R T1[NC], T2[NC], T3[NC];
+  R G2 = R(0.0), G3 = R(0.0);  // heat-flux moments of the equilibrium part (the first vanishes)
+  {
+    const R p0 = g0.rho * g0.h;
+    T1[0] = W0[1];
+#pragma unroll
+    for (int e = 0; e < D; ++e) T1[e + 1] = W0[1] * g0.U[e] + (e == 0 ? p0 : R(0.0));
+    T1[D + 1] = g0.U[0] * (W0[D + 1] + p0);
+    R M[NM1];
+    moment_table(g0.U[0], g0.h, g0.rho, W0[1], M);
+    Slope<D, R> a[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      slope_prim<D>(g0, N, T.dW0[d], a[d]);
+      slope_poly<D>(g0, a[d]);
+    }
+    R c[D];
+    c[0] = g0.U[0];
+#pragma unroll
+    for (int t = 1; t < D; ++t) c[t] = R(0.0);
+    slope_parts<D, NS>(M, g0, N, a, c, T2, T3, G2, G3);
+  }
+
+  R C[2][6];
 #pragma unroll
   for (int id = 0; id < 2; ++id) {
     const R dl = id == 0 ? dt : 0.5 * dt;
-    R e, ome;
-    if (tau == 0.0) {
-      e = R(0.0);
-      ome = R(1.0);
-    } else if (id == 1) {
-      e = em + 1.0;
-      ome = -em;
-    } else {
-      e = (em + 1.0) * (em + 1.0);
-      ome = -em * (em + 2.0);
-    }
+    const R tau = ft.tau, em = ft.em;
+    const R e = id == 1 ? em + 1.0 : (em + 1.0) * (em + 1.0);
+    const R ome = id == 1 ? -em : -em * (em + 2.0);
     const R tt = (tau * tau) * ome;
-    const R C1 = dl - tau * ome;
-    const R C2 = 2.0 * tt - (tau * dl) * (1.0 + e);
-    const R C3 = (0.5 * dl) * dl - tau * dl + tt;
-    const R C4 = tau * ome;
-    const R C5 = (tau * dl) * e - 2.0 * tt;
-    const R C6 = -tt;
-    R* F = id == 0 ? Fdt : Fh;
+    C[id][0] = dl - tau * ome;
+    C[id][1] = 2.0 * tt - (tau * dl) * (1.0 + e);
+    C[id][2] = (0.5 * dl) * dl - tau * dl + tt;
+    C[id][3] = tau * ome;
+    C[id][4] = (tau * dl) * e - 2.0 * tt;
+    C[id][5] = -tt;
+  }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const R cd = C[0][k], ch = C[1][k];
+    if (OUT == FLUX_STAGE1) {
+      C[0][k] = w * ch;
+      C[1][k] = (w * (8.0 / 3.0)) * ch - (w * (1.0 / 3.0)) * cd;
+    } else if (OUT == FLUX_STAGE2) {
+      C[0][k] = (w * (4.0 / 3.0)) * cd - (w * (8.0 / 3.0)) * ch;
+    }
+  }
+#pragma unroll
+  for (int id = 0; id < (OUT == FLUX_STAGE2 ? 1 : 2); ++id) {
+    R* F = id == 0 ? Fa : Fb;
+    const R* Ck = C[id];
 #pragma unroll
     for (int q = 0; q < NC; ++q)
-      F[q] = ((C1 * T1[q] + C2 * T2[q]) + C3 * T3[q]) + ((C4 * S1[q] + C5 * S2[q]) + C6 * S3[q]);
+      F[q] = ((Ck[0] * T1[q] + Ck[1] * T2[q]) + Ck[2] * T3[q]) +
+             ((Ck[3] * T.S1[q] + Ck[4] * T.S2[q]) + Ck[5] * T.S3[q]);
     if (NS) {
-      const R q = (C2 * G2 + C3 * G3) + ((C4 * H1 + C5 * H2) + C6 * H3);
+      const R q = (Ck[1] * G2 + Ck[2] * G3) + ((Ck[3] * T.H1 + Ck[4] * T.H2) + Ck[5] * T.H3);
       F[NC - 1] += P.pr_fix * q;
     }
   }
 }
 
-// left + right sum of the two sides' shares, in that order
+// sum of the two sides' shares (the same in either order)
 template <int D, class R>
 TGKS_HD void side_sum(const SidePart<D, R>& l, const SidePart<D, R>& r, SidePart<D, R>& o) {
   constexpr int NC = D + 2;
@@ -1529,14 +1448,18 @@ TGKS_HD void side_sum(const SidePart<D, R>& l, const SidePart<D, R>& r, SidePart
   o.H3 = l.H3 + r.H3;
 }
 
-// Time-integrated flux F(dt) and F(dt/2) at one Gauss point.
+// Time-integrated fluxes at one Gauss point (FLUX_TIMES, FLUX_STAGE1, 2).
 // Wl, Wr: states; dWl[d], dWr[d]: derivatives along frame axis d; sgn = 1:
 // Wl is the left side (u1 > 0), -1: the right one (and Wr the left; the two
-// sides' shares are added, so the order does not matter).
-// Returns false when a state is non-physical.
-template <int D, bool NS, class R>
-TGKS_HD bool gp_flux(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const FluxCfg& P,
-                     R dt, R* Fdt, R* Fh, double sgn = 1.0) {
+// sides' shares are added, so the order does not matter).  EQ: a separately
+// reconstructed equilibrium (WENO-Z and TENO5 GKS, Sec. 3.1): the slopes of
+// W0 along every frame axis are given (dW0), and so is W0 itself when W0in is
+// not null (2-D: the tangential reconstruction of the face segments'
+// equilibrium states); otherwise W0 is the kinetic weighting of the two sides
+// (Eq. 2.6).  Returns false when a state is non-physical.
+template <int D, bool NS, int OUT, bool EQ, class R>
+TGKS_HD bool gp_flux_any(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const R* W0in,
+                         const R (*dW0)[D + 2], const FluxCfg& P, R dt, double w, R* Fa, R* Fb, double sgn) {
   constexpr int NC = D + 2;
   Gas<D, R> gl, gr, g0;
   R hl0, hl1, hr0, hr1, wl[NC], wr[NC], W0[NC];
@@ -1544,44 +1467,42 @@ TGKS_HD bool gp_flux(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*
   side_w0<D>(Wl, P, sgn, gl, hl0, hl1, wl);
   side_w0<D>(Wr, P, -sgn, gr, hr0, hr1, wr);
 #pragma unroll
-  for (int q = 0; q < NC; ++q) W0[q] = wl[q] + wr[q];
+  for (int q = 0; q < NC; ++q) W0[q] = EQ && W0in ? W0in[q] : wl[q] + wr[q];
   make_gas<D>(W0, P.N, g0);
+  const FluxTime<R> ft = flux_time<D>(g0, gl.rho * gl.h, gr.rho * gr.h, P, dt);
   // side contributions: dW0 (Eq. 2.6), A^s (Eq. 2.7), and the moments of the
-  // non-equilibrium part of Eq. 2.5 over the half space
+  // non-equilibrium part of Eq. 2.5 over the half space.  One side is
+  // finished before the other is begun: interleaved by the scheduler they
+  // take more registers than three wavefronts per SIMD have.
   SidePart<D, R> L, Rt, T;
-  side_part<D, NS>(gl, hl0, hl1, Wl, dWl, P, g0, L);
-  side_part<D, NS>(gr, hr0, hr1, Wr, dWr, P, g0, Rt);
+  phase_end<R>();
+  side_part<D, NS>(gl, hl0, hl1, dWl, P, g0, L);
+  phase_end<R>();
+  side_part<D, NS>(gr, hr0, hr1, dWr, P, g0, Rt);
   side_sum<D>(L, Rt, T);
-  flux_combine<D, NS>(W0, g0, T, gl.rho * gl.h, gr.rho * gr.h, P, dt, Fdt, Fh);
+  phase_end<R>();
+  if (EQ) {
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) T.dW0[d][q] = dW0[d][q];
+  }
+  flux_combine<D, NS, OUT>(W0, g0, T, ft, P, dt, w, Fa, Fb);
   return gl.ok && gr.ok && g0.ok;
 }
 
-// The Gauss-point flux with a separately reconstructed equilibrium (WENO-Z
-// and TENO5 GKS, Sec. 3.1): the slopes of W0 along every frame axis are
-// given (dW0), and so is W0 itself when W0in is not null (2-D: the
-// tangential reconstruction of the face segments' equilibrium states);
-// otherwise W0 is the kinetic weighting of the two sides (Eq. 2.6).
-template <int D, bool NS, class R>
+template <int D, bool NS, int OUT = FLUX_TIMES, class R>
+TGKS_HD bool gp_flux(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const FluxCfg& P,
+                     R dt, R* Fa, R* Fb, double w = 1.0, double sgn = 1.0) {
+  return gp_flux_any<D, NS, OUT, false>(Wl, Wr, dWl, dWr, (const R*)nullptr, (const R(*)[D + 2]) nullptr, P, dt, w,
+                                        Fa, Fb, sgn);
+}
+
+template <int D, bool NS, int OUT = FLUX_TIMES, class R>
 TGKS_HD bool gp_flux_eq(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const R* W0in,
-                        const R (*dW0)[D + 2], const FluxCfg& P, R dt, R* Fdt, R* Fh, double sgn = 1.0) {
-  constexpr int NC = D + 2;
-  Gas<D, R> gl, gr, g0;
-  R hl0, hl1, hr0, hr1, wl[NC], wr[NC], W0[NC];
-  side_w0<D>(Wl, P, sgn, gl, hl0, hl1, wl);
-  side_w0<D>(Wr, P, -sgn, gr, hr0, hr1, wr);
-#pragma unroll
-  for (int q = 0; q < NC; ++q) W0[q] = W0in ? W0in[q] : wl[q] + wr[q];
-  make_gas<D>(W0, P.N, g0);
-  SidePart<D, R> L, Rt, T;
-  side_part<D, NS>(gl, hl0, hl1, Wl, dWl, P, g0, L);
-  side_part<D, NS>(gr, hr0, hr1, Wr, dWr, P, g0, Rt);
-  side_sum<D>(L, Rt, T);
-#pragma unroll
-  for (int d = 0; d < D; ++d)
-#pragma unroll
-    for (int q = 0; q < NC; ++q) T.dW0[d][q] = dW0[d][q];
-  flux_combine<D, NS>(W0, g0, T, gl.rho * gl.h, gr.rho * gr.h, P, dt, Fdt, Fh);
-  return gl.ok && gr.ok && g0.ok;
+                        const R (*dW0)[D + 2], const FluxCfg& P, R dt, R* Fa, R* Fb, double w = 1.0,
+                        double sgn = 1.0) {
+  return gp_flux_any<D, NS, OUT, true>(Wl, Wr, dWl, dWr, W0in, dW0, P, dt, w, Fa, Fb, sgn);
 }
 
 // ---------------------------------------------------------------------------

@@ -188,35 +188,43 @@ __device__ __forceinline__ int fallback_side(double* w, double (*dw)[NC], const 
 
 // The selection of five values and the selected polynomial at the Gauss
 // points; returns the flag (unused: not evaluated).  MODE SEL_FILTER or
-// SEL_RATIO: sure becomes false where the exact weights have to decide (the
-// caller then evaluates everything again with SEL_EXACT: one branch for all
-// its selections, which leaves them one straight line of code).
+// SEL_RATIO: sure becomes false where the exact weights have to decide.  The
+// caller then takes those selections in a loop of its own (exact_flags: one
+// copy of the exact code, four bits per selection) and evaluates everything
+// again with SEL_GIVEN; one branch for all its selections leaves them one
+// straight line of code.
+constexpr int SEL_GIVEN = 3;
+
 template <int MODE>
-__device__ __forceinline__ unsigned select_poly(const double* Q, const TenoCfg& c, TenoPoly<double>& o, bool& sure) {
+__device__ __forceinline__ unsigned select_poly(const double* Q, const TenoCfg& c, TenoPoly<double>& o, bool& sure,
+                                                unsigned given) {
   TenoParts<double> p;
   teno_parts(Q, p);
   TenoSel s;
-  if (MODE == SEL_EXACT)
-    s = teno_sel(teno_exact_cold(Q, c));
+  if constexpr (MODE == SEL_GIVEN)
+    s = teno_sel(given);
   else
     sure &= teno_certain<MODE>(Q, p, c, s);
   teno_poly(p, s, o);
   return s.flag();
 }
 
-template <int NC>
-__device__ __forceinline__ void write_combined(int STAGE, const double* Fdt, const double* Fh, double w,
-                                               double* accA, double* accB) {
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    if (STAGE == 1) {
-      accA[q] += w * Fh[q];
-      accB[q] += w * ((8.0 / 3.0) * Fh[q] - (1.0 / 3.0) * Fdt[q]);
-    } else {
-      accA[q] += w * ((4.0 / 3.0) * Fdt[q] - (8.0 / 3.0) * Fh[q]);
-    }
+// flags of n <= 8 selections from the exact weights, four bits each; load(i,
+// Q) fills the i-th one's values
+template <class F>
+__device__ __forceinline__ unsigned exact_flags(int n, const TenoCfg& c, F load) {
+  unsigned fl = 0;
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    double Q[5];
+    load(i, Q);
+    fl |= teno_exact(Q, c) << (4 * i);
   }
+  return fl;
 }
+
+// the combination of F(dt), F(dt/2) that stage STAGE's update needs
+__host__ __device__ constexpr int flux_out(int stage) { return stage == 1 ? FLUX_STAGE1 : FLUX_STAGE2; }
 
 // A no-slip adiabatic wall is impermeable and, at rest, does no work and
 // conducts no heat: the mass and energy fluxes of its faces are zero (frame
@@ -266,10 +274,10 @@ __device__ __forceinline__ void face1d_body(const StageArgs& a, int f) {
         Q[r] = EX ? cell_value(a.g, a.pb, a.W, c, f - 3 + r, 0, tb) : load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
       double o[4];
       if (SCHEME == SCHEME_TENO_D) {
-        teno_face(Q, teno_flag<SEL_FILTER>(Q, a.tn), o);
+        teno_face(Q, teno_flag<SEL_FILTER, true>(Q, a.tn), o);
         Wl[c] = o[2];
         dWl[0][c] = o[3] * idx;
-        const unsigned fr = teno_flag<SEL_FILTER>(Q + 1, a.tn);
+        const unsigned fr = teno_flag<SEL_FILTER, true>(Q + 1, a.tn);
         teno_face(Q + 1, fr, o);
         Wr[c] = o[0];
         dWr[0][c] = o[1] * idx;
@@ -297,12 +305,11 @@ __device__ __forceinline__ void face1d_body(const StageArgs& a, int f) {
     const int nfb = fallback_side<3, 1>(Wl, dWl, Cl, a.gamma) + fallback_side<3, 1>(Wr, dWr, Cr, a.gamma);
     if (nfb && a.fbc) atomicAdd(a.fbc, (unsigned long long)nfb);
   }
-  double Fdt[3], Fh[3], A[3] = {0, 0, 0}, B[3] = {0, 0, 0};
-  const bool ok = SCHEME >= SCHEME_TENO5
-                      ? gp_flux_eq<1, NS>(Wl, Wr, dWl, dWr, (const double*)nullptr, dW0, a.fc, dt, Fdt, Fh)
-                      : gp_flux<1, NS>(Wl, Wr, dWl, dWr, a.fc, dt, Fdt, Fh);
+  double A[3] = {0, 0, 0}, B[3] = {0, 0, 0};
+  const bool ok = SCHEME >= SCHEME_TENO5 ? gp_flux_eq<1, NS, flux_out(STAGE)>(
+                                               Wl, Wr, dWl, dWr, (const double*)nullptr, dW0, a.fc, dt, A, B)
+                                         : gp_flux<1, NS, flux_out(STAGE)>(Wl, Wr, dWl, dWr, a.fc, dt, A, B);
   if (!ok) atomicAdd(a.fail, 1ull);
-  write_combined<3>(STAGE, Fdt, Fh, 1.0, A, B);
   wall_fluxes<3>(a.g, 0, f, A, B);
   const long long nf = n + 1;
 #pragma unroll
@@ -445,7 +452,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         double V[5];
 #pragma unroll
         for (int r = 0; r < 5; ++r) V[r] = char_dot<NC>(Lm[k], sd == 0 ? C[r] : C[r + 1]);
-        const unsigned fl = teno_flag<SEL_FILTER>(V, a.tn);
+        const unsigned fl = teno_flag<SEL_FILTER, true>(V, a.tn);
         double o[4];
         teno_face(V, fl, o);
         if (sd == 0) {
@@ -566,6 +573,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   // its own Gauss point (index 0) and at its partner's (1); false where a
   // selection needs the exact weights
   double gV[NC][2], gD[NC][2], gN[NC][2];
+  unsigned given = 0;  // flags of W (bits 8 q) and W_n (8 q + 4) of frame component or field q
   auto tangential = [&](auto mode) {
     constexpr int MODE = decltype(mode)::value;
     bool sure = true;
@@ -597,7 +605,10 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
           Qn[r] = char_dot<NC>(Lt[k], xn);
         }
         TenoPoly<double> w, n;
-        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure), fq = select_poly<MODE>(Qn, a.tt, n, sure);
+        if (MODE == SEL_GIVEN)
+          given |= (teno_exact_cold(Qw, a.tt) << (8 * k)) | (teno_exact_cold(Qn, a.tt) << (8 * k + 4));
+        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * k)) & 15u);
+        const unsigned fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * k + 4)) & 15u);
         if (FLAGS) {
           a.tflags[((long long)(0 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fw;
           a.tflags[((long long)(1 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fq;
@@ -631,8 +642,8 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         unsigned fw, fq;
         if (SCHEME == SCHEME_TENO_D) {
           TenoPoly<double> w, n;
-          fw = select_poly<MODE>(Qw, a.tt, w, sure);
-          fq = select_poly<MODE>(Qn, a.tt, n, sure);
+          fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * q)) & 15u);
+          fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * q + 4)) & 15u);
 #pragma unroll
           for (int gp = 0; gp < 2; ++gp) {
             const double x = gp == 0 ? sg : -sg;
@@ -661,11 +672,20 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   };
   if (live) {
     if (SCHEME != SCHEME_TENO_D) {
-      tangential(std::integral_constant<int, SEL_EXACT>());
+      tangential(std::integral_constant<int, SEL_GIVEN>());
     } else {
       bool sure = false;
       if (a.tt.fast & TENO_FILTER_OK) sure = tangential(std::integral_constant<int, SEL_FILTER>());
-      if (!sure) tangential(std::integral_constant<int, SEL_EXACT>());
+      if (!sure) {
+        // characteristic fields take their flags as they are projected
+        if (!CHAR)
+          given = exact_flags(2 * NC, a.tt, [&](int i, double* Q) {
+            const int q = i >> 1, c = q == 1 ? perm[1] : q == 2 ? perm[2] : q;  // mass and energy in place
+#pragma unroll
+            for (int r = 0; r < 5; ++r) Q[r] = sR[c][ft + r][nr][vo + (i & 1)];
+          });
+        tangential(std::integral_constant<int, SEL_GIVEN>());
+      }
     }
   } else {
 #pragma unroll
@@ -692,7 +712,6 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
     if (nfb && a.fbc) atomicAdd(a.fbc, (unsigned long long)nfb);
   }
   if (live) {
-    double Fdt[NC], Fh[NC];
     bool ok;
     if (SCHEME >= SCHEME_TENO5) {
       // the equilibrium at this lane's Gauss point: the five face segments'
@@ -716,12 +735,11 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         scheme_gauss<SCHEME_TENO5>(Qx, se, v, d);
         dW0e[0][q] = m ? v[1] : v[0];
       }
-      ok = gp_flux_eq<2, NS>(Wo, Wp, Do, Dp, W0e, dW0e, a.fc, dt, Fdt, Fh, -sg);
+      ok = gp_flux_eq<2, NS, flux_out(STAGE)>(Wo, Wp, Do, Dp, W0e, dW0e, a.fc, dt, A, B, 0.5, -sg);
     } else {
-      ok = gp_flux<2, NS>(Wo, Wp, Do, Dp, a.fc, dt, Fdt, Fh, -sg);
+      ok = gp_flux<2, NS, flux_out(STAGE)>(Wo, Wp, Do, Dp, a.fc, dt, A, B, 0.5, -sg);
     }
     if (!ok) atomicAdd(a.fail, 1ull);
-    write_combined<NC>(STAGE, Fdt, Fh, 0.5, A, B);
   }
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
@@ -922,7 +940,7 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
       Qn[r] = sR[s][c][1][i2][j1 + r];
     }
     double v[2], dv[2], vn[2], dvn[2];
-    const unsigned fw = teno_flag<SEL_RATIO>(Qw, a.tt), fq = teno_flag<SEL_RATIO>(Qn, a.tt);
+    const unsigned fw = teno_flag<SEL_RATIO, true>(Qw, a.tt), fq = teno_flag<SEL_RATIO, true>(Qn, a.tt);
     // the inputs of the second sweep's selections: one fixed evaluation order
     teno_gauss_exact(Qw, fw, v, dv);
     teno_gauss_exact(Qn, fq, vn, dvn);
@@ -964,6 +982,14 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
   // (cell units) at this lane's T2 point [r][0] and at its partner's [r][1];
   // false where a selection needs the exact weights
   double sv[8][2], sd[8][2];
+  unsigned given = 0;  // flags of the lane's items, four bits each
+  auto item_values = [&](int it, int& kind, int& c, double* Q) {
+    const int q = it / 3;
+    kind = it - 3 * q;
+    c = q == 0 ? perm[0] : q == 1 ? perm[1] : q == 2 ? perm[2] : q == 3 ? perm[3] : perm[4];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) Q[k] = sS[m2][c][j2 + k][j1][2 * kind + m1];
+  };
   auto sweep2 = [&](auto mode) {
     constexpr int MODE = decltype(mode)::value;
     bool sure = true;
@@ -971,13 +997,11 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
     for (int r = 0; r < 8; ++r) {
       const int it = 2 * r + m3;
       if (it < 15) {
-        const int q = it / 3, kind = it - 3 * q;
-        const int c = q == 0 ? perm[0] : q == 1 ? perm[1] : q == 2 ? perm[2] : q == 3 ? perm[3] : perm[4];
+        int kind, c;
         double Q[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) Q[k] = sS[m2][c][j2 + k][j1][2 * kind + m1];
+        item_values(it, kind, c, Q);
         TenoPoly<double> w;
-        const unsigned fl = select_poly<MODE>(Q, a.tt, w, sure);
+        const unsigned fl = select_poly<MODE>(Q, a.tt, w, sure, (given >> (4 * r)) & 15u);
 #pragma unroll
         for (int gp = 0; gp < 2; ++gp) {
           const double x = gp == 0 ? sg : -sg;
@@ -994,7 +1018,13 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
   if (live) {
     bool sure = false;
     if (a.tt.fast & TENO_FILTER_OK) sure = sweep2(std::integral_constant<int, SEL_RATIO>());
-    if (!sure) sweep2(std::integral_constant<int, SEL_EXACT>());
+    if (!sure) {
+      given = exact_flags(8 - m3, a.tt, [&](int r, double* Q) {
+        int kind, c;
+        item_values(2 * r + m3, kind, c, Q);
+      });
+      sweep2(std::integral_constant<int, SEL_GIVEN>());
+    }
   } else {
 #pragma unroll
     for (int r = 0; r < 8; ++r) sv[r][0] = sv[r][1] = sd[r][0] = sd[r][1] = 0.0;
@@ -1046,12 +1076,13 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
   }
   P.H1 = P.H2 = P.H3 = 0.0;
   bool ok = true;
-  double ps = 0.0;
+  const double ps = live ? gs.rho * gs.h : 0.0, pp = lane_xor<1>(ps);
+  FluxTime<double> ftm{0.0, 0.0};
   if (live) {
     make_gas<3>(W0, a.fc.N, g0);
-    side_part<3, NS>(gs, h0, h1, Ws, dWs, a.fc, g0, P);
+    ftm = flux_time<3>(g0, ps, pp, a.fc, dt);
+    side_part<3, NS>(gs, h0, h1, dWs, a.fc, g0, P);
     ok = gs.ok && g0.ok;
-    ps = gs.rho * gs.h;
   }
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
@@ -1068,14 +1099,11 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
   } else {
     T.H1 = T.H2 = T.H3 = 0.0;
   }
-  const double pp = lane_xor<1>(ps);
   ok = ok && (lane_xor<1>((int)ok) != 0);
   double A[NC] = {0, 0, 0, 0, 0}, B[NC] = {0, 0, 0, 0, 0};
   if (live) {
-    double Fdt[NC], Fh[NC];
-    flux_combine<3, NS>(W0, g0, T, m2 ? pp : ps, m2 ? ps : pp, a.fc, dt, Fdt, Fh);
+    flux_combine<3, NS, flux_out(STAGE)>(W0, g0, T, ftm, a.fc, dt, 0.25, A, B);
     if (!ok && m2 == 0) atomicAdd(a.fail, 1ull);
-    write_combined<NC>(STAGE, Fdt, Fh, 0.25, A, B);
   }
   // sum over the four Gauss points (m3, m1); both lanes of a pair hold the
   // same flux

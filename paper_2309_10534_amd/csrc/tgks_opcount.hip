@@ -113,15 +113,14 @@ long long count_face(const tgks_ctx* c, int stage, tgks_opcount::Tally* detail) 
   for (int q = 0; q < NC; ++q) A[q] = B[q] = F(0.0);
   const double w = 1.0 / NG;
   for (int m = 0; m < NG; ++m) {
-    F Fdt[NC], Fh[NC];
-    gp_flux<D, NS>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fdt, Fh);
+    F Fa[NC], Fb[NC];
+    if (stage == 1)
+      gp_flux<D, NS, FLUX_STAGE1>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
+    else
+      gp_flux<D, NS, FLUX_STAGE2>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
     for (int q = 0; q < NC; ++q) {
-      if (stage == 1) {
-        A[q] += F(w) * Fh[q];
-        B[q] += F(w) * (F(8.0 / 3.0) * Fh[q] - F(1.0 / 3.0) * Fdt[q]);
-      } else {
-        A[q] += F(w) * (F(4.0 / 3.0) * Fdt[q] - F(8.0 / 3.0) * Fh[q]);
-      }
+      A[q] += Fa[q];
+      if (stage == 1) B[q] += Fb[q];
     }
   }
   if (detail) *detail = tgks_opcount::tally();
@@ -194,15 +193,14 @@ long long count_face_char(const tgks_ctx* c, int stage, tgks_opcount::Tally* det
   for (int q = 0; q < NC; ++q) A[q] = B[q] = F(0.0);
   const double w = 1.0 / NG;
   for (int m = 0; m < NG; ++m) {
-    F Fdt[NC], Fh[NC];
-    gp_flux<D, NS>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fdt, Fh);
+    F Fa[NC], Fb[NC];
+    if (stage == 1)
+      gp_flux<D, NS, FLUX_STAGE1>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
+    else
+      gp_flux<D, NS, FLUX_STAGE2>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
     for (int q = 0; q < NC; ++q) {
-      if (stage == 1) {
-        A[q] += F(w) * Fh[q];
-        B[q] += F(w) * (F(8.0 / 3.0) * Fh[q] - F(1.0 / 3.0) * Fdt[q]);
-      } else {
-        A[q] += F(w) * (F(4.0 / 3.0) * Fdt[q] - F(8.0 / 3.0) * Fh[q]);
-      }
+      A[q] += Fa[q];
+      if (stage == 1) B[q] += Fb[q];
     }
   }
   if (detail) *detail = tgks_opcount::tally();
@@ -288,19 +286,19 @@ long long count_face_scheme(const tgks_ctx* c, int stage, tgks_opcount::Tally* d
   for (int q = 0; q < NC; ++q) A[q] = B[q] = F(0.0);
   const double w = 1.0 / NG;
   for (int m = 0; m < NG; ++m) {
-    F Fdt[NC], Fh[NC];
-    if (SEP)
-      gp_flux_eq<D, NS>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], D == 1 ? (const F*)nullptr : W0[m], dW0[m], fc, dt,
-                        Fdt, Fh);
+    F Fa[NC], Fb[NC];
+    const F* W0m = D == 1 ? (const F*)nullptr : W0[m];
+    if (SEP && stage == 1)
+      gp_flux_eq<D, NS, FLUX_STAGE1>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], W0m, dW0[m], fc, dt, Fa, Fb, w);
+    else if (SEP)
+      gp_flux_eq<D, NS, FLUX_STAGE2>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], W0m, dW0[m], fc, dt, Fa, Fb, w);
+    else if (stage == 1)
+      gp_flux<D, NS, FLUX_STAGE1>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
     else
-      gp_flux<D, NS>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fdt, Fh);
+      gp_flux<D, NS, FLUX_STAGE2>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
     for (int q = 0; q < NC; ++q) {
-      if (stage == 1) {
-        A[q] += F(w) * Fh[q];
-        B[q] += F(w) * (F(8.0 / 3.0) * Fh[q] - F(1.0 / 3.0) * Fdt[q]);
-      } else {
-        A[q] += F(w) * (F(4.0 / 3.0) * Fdt[q] - F(8.0 / 3.0) * Fh[q]);
-      }
+      A[q] += Fa[q];
+      if (stage == 1) B[q] += Fb[q];
     }
   }
   if (detail) *detail = tgks_opcount::tally();
