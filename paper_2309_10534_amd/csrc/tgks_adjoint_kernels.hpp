@@ -91,7 +91,7 @@ __global__ __launch_bounds__(128) void adj_face1d_kernel(AdjArgs a) {
 #pragma unroll
     for (int r = 0; r < 6; ++r) Q[r] = load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
     double o[4];
-    teno_face(Q, teno_flag<SEL_FILTER>(Q, a.tn), o);
+    teno_face(Q, teno_flag<SEL_FILTER, true>(Q, a.tn), o);
     Wl[c] = o[2];
     dWl[0][c] = o[3] * idx;
     teno_face(Q + 1, teno_flag<SEL_FILTER>(Q + 1, a.tn), o);
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
     const int c = L / (RN * LT);
     const double* Q = &sW[c][tl][nr];
     double o[4];
-    teno_face(Q, teno_flag<SEL_FILTER>(Q, a.tn), o);
+    teno_face(Q, teno_flag<SEL_FILTER, true>(Q, a.tn), o);
     sR[c][tl][nr][0] = o[0];
     sR[c][tl][nr][1] = o[1] * idn;
     sR[c][tl][nr][2] = o[2];
@@ -212,8 +212,9 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
           Qn[r] = sR[c][ft + r][nr][vo + 1];
         }
         TenoPoly<double> w, n;
-        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * q)) & 15u);
-        const unsigned fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * q + 4)) & 15u);
+        const unsigned fw = select_poly<MODE, false>(Qw, a.tt, w, sure, (given >> (8 * q)) & 15u);
+        const unsigned fq = select_poly<MODE, false>(Qn, a.tt, n, sure, (given >> (8 * q + 4)) & 15u);
+        if (MODE == SEL_SMOOTH && !all_lanes(sure)) return false;
         a.TF[((long long)(m * 2 + 0) * NC + c) * nf + fidx] = (uint8_t)fw;
         a.TF[((long long)(m * 2 + 1) * NC + c) * nf + fidx] = (uint8_t)fq;
 #pragma unroll
@@ -227,7 +228,8 @@ __global__ __launch_bounds__(2 * ATN * ATT) void adj_face2d_kernel(AdjArgs a) {
       return sure;
     };
     bool sure = false;
-    if (a.tt.fast & TENO_FILTER_OK) sure = tangential(std::integral_constant<int, SEL_FILTER>());
+    if (a.tt.fast & TENO_RATIO_OK) sure = tangential(std::integral_constant<int, SEL_SMOOTH>());
+    if (!sure && (a.tt.fast & TENO_FILTER_OK)) sure = tangential(std::integral_constant<int, SEL_FILTER>());
     if (!sure) {
       given = exact_flags(2 * NC, a.tt, [&](int i, double* Q) {
         const int q = i >> 1, c = q == 1 ? perm[1] : q == 2 ? perm[2] : q;  // mass and energy in place

@@ -149,6 +149,34 @@ TGKS_HD void teno_parts(const R* Q, TenoParts<R>& p) {
   p.y4 = fma_(R(-4.0), d, f + 6.0 * c) + e;
 }
 
+// Whether the large stencil is kept for certain (true only where it is), from
+// the shared second differences alone; needs the fixed ratios of teno_cfg
+// (TENO_RATIO_OK).  EQ: also true for five equal values, where every
+// candidate polynomial is the constant and the selection does not matter.
+//
+// With e_a = t1 - t0, e_b = t2 - t1 the third differences and N^2 = x^2 +
+// 13/3 t1^2 = 4 beta_1, the other indicators are 4 beta_0 = (x - e_a)^2 +
+// 13/3 (t1 - e_a)^2, 4 beta_2 = (x - e_b)^2 + 13/3 (t1 + e_b)^2 and 4 beta_3 =
+// (x - y3/6)^2 + 13/3 (t1 - 0.0846 y4)^2 + 781/720 y3^2 + 4.339 y4^2, y3 =
+// e_a + e_b, y4 = e_b - e_a.  If |e_a|, |e_b| <= r N then sqrt(4 beta_0),
+// sqrt(4 beta_2) >= (1 - 2.31 r) N and sqrt(4 beta_3) <= (1 + 4.52 r) N, so at
+// r = 1/10 beta_3 <= 3.57 min(beta_0, beta_1, beta_2): the large stencil is
+// kept (ratio 4 of teno_cfg).  N >= 2^-29 |c| keeps the rounding of every
+// indicator (20 ulps of the values, here and in the oracle's order) below
+// 2^-18 N, far inside the margin; data with less variation than that is left
+// to the general evaluation.
+template <bool EQ>
+TGKS_HD bool teno_smooth(const TenoParts<double>& p) {
+#pragma clang fp contract(off)
+  const double ea = p.t[1] - p.t[0], eb = p.t[2] - p.t[1];
+  const double n = fma(13.0 / 3.0, p.t[1] * p.t[1], p.x * p.x);
+  const double e = fmax(fabs(ea), fabs(eb)), cs = p.c * 0x1p-29;
+  // (the sum, not the larger of the two, would be a NaN for a NaN: e - e)
+  const bool small = (e * e <= 0.01 * n) & (ea + eb == ea + eb);
+  const bool seen = cs * cs <= n;
+  return EQ ? small & (seen | (n == 0.0)) : small & seen;
+}
+
 // A selection: the large stencil, or the surviving small ones.
 struct TenoSel {
   bool lg, k0, k1, k2;
@@ -190,11 +218,12 @@ TGKS_HD TenoSel teno_sel(unsigned flag) {
 // problem at 1024^2 take 18.2 ms (21.9 before), 2 steps of the 3-D
 // Taylor-Green vortex at 128^3 24.4 ms (25.1).
 //
-// SEL_RATIO (the 3-D kernels): the fixed ratios of teno_cfg first (when
-// TENO_RATIO_OK; no powers at all).  Smooth data keeps the large stencil
-// there; constant data (the quadratics' indicators vanish exactly, the
-// quartic's keeps a rounding residue) rejects it there with all three
-// quadratics kept.  Then as SEL_FILTER.
+// SEL_RATIO (3-D normal reconstruction and first sweep): the fixed ratios of
+// teno_cfg first (when TENO_RATIO_OK; no powers at all), taken where they
+// decide for every lane of the wavefront: smooth data keeps the large
+// stencil; constant data (the quadratics' indicators vanish exactly, the
+// quartic's keeps a rounding residue) rejects it with the quadratics kept.
+// Then as SEL_FILTER.
 //
 // The operation-counting type always evaluates the exact weights.
 // ---------------------------------------------------------------------------
@@ -263,6 +292,15 @@ TGKS_HD double scale_of(double x) {
 #endif
 }
 
+// whether x holds in every active lane of the wavefront (the host: of one)
+TGKS_HD bool all_lanes(bool x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_ballot_w64(!x) == 0;
+#else
+  return x;
+#endif
+}
+
 // the certain decisions; false where the exact weights have to decide
 template <int MODE>
 TGKS_HD bool teno_certain(const double* Q, const TenoParts<double>& p, const TenoCfg& c, TenoSel& s) {
@@ -283,19 +321,12 @@ TGKS_HD bool teno_certain(const double* Q, const TenoParts<double>& p, const Ten
   const bool inr = (b3 < 1e40) & (m < 1e40);
   if (MODE == SEL_RATIO) {
     if (c.fast & TENO_RATIO_OK) {
-      if (inr) {
-        if (b3 <= 4.0 * m) {
-          s = TenoSel{true, false, false, false};
-          return true;
-        }
-        if (b3 > 16.0 * m) {
-          const double lo = 4.0 * m, hi = 8.0 * m;
-          const bool sure = !(b0 > lo && b0 <= hi) && !(b1 > lo && b1 <= hi) && !(b2 > lo && b2 <= hi);
-          if (sure) {
-            s = TenoSel{false, b0 <= lo, b1 <= lo, b2 <= lo};
-            return true;
-          }
-        }
+      const double lo = 4.0 * m, hi = 8.0 * m;
+      const bool k0 = b0 <= lo, k1 = b1 <= lo, k2 = b2 <= lo, keep = b3 <= lo;
+      const bool sure = inr & (keep | ((b3 > 16.0 * m) & (k0 | (b0 > hi)) & (k1 | (b1 > hi)) & (k2 | (b2 > hi))));
+      if (all_lanes(sure)) {
+        s = TenoSel{keep, k0, k1, k2};
+        return true;
       }
     }
   }
@@ -419,22 +450,38 @@ struct TenoPoly {
   R base, odd, ev, od;
 };
 
+// l: twice the slope, t: second difference of the quadratic; y3, y4: third and
+// fourth differences of the large stencil, or 0
 template <class R>
-TGKS_HD void teno_poly(const TenoParts<R>& p, const TenoSel& s, TenoPoly<R>& o) {
+TGKS_HD void teno_poly_at(R c, R l, R t, R y3, R y4, TenoPoly<R>& o) {
+#pragma clang fp contract(off)
   const double h = 0.28867513459481288225;  // s = 1/(2 sqrt 3)
-  const R z = R(0.0), one = R(1.0);
-  const R o0 = !s.lg && s.k0 ? one : z, o1 = s.lg || s.k1 ? one : z, o2 = !s.lg && s.k2 ? one : z;
-  const R l0 = fma_(R(2.0), p.c - p.b, p.t[0]), l2 = fma_(R(2.0), p.d - p.c, -p.t[2]);
-  const R y3 = s.lg ? p.y3 : z, y4 = s.lg ? fma_(R(-2.0), p.t[1], p.t[0] + p.t[2]) : z;
-  const R n = (o0 + o1) + o2;
-  // 1/n for n = 1, 2, 3: (11 - 6 n + n^2) / 6
-  const R inv = fma_(n, fma_(n, R(1.0 / 6.0), R(-1.0)), R(11.0 / 6.0));
-  const R l = fma_(o2, l2, fma_(o1, p.x, o0 * l0)) * inv;             // twice the slope
-  const R t = fma_(o2, p.t[2], fma_(o1, p.t[1], o0 * p.t[0])) * inv;  // second difference
-  o.base = fma_(y4, R(-1.0 / 4320.0), p.c);
+  o.base = fma_(y4, R(-1.0 / 4320.0), c);
   o.odd = (0.5 * h) * fma_(y3, R(-7.0 / 36.0), l);
   o.ev = 0.5 * fma_(y3, R(-1.0 / 6.0), l);
   o.od = h * fma_(y4, R(-1.0 / 9.0), t);
+}
+
+// the large stencil's, as teno_poly evaluates it (to the bit)
+template <class R>
+TGKS_HD void teno_poly_large(const TenoParts<R>& p, TenoPoly<R>& o) {
+#pragma clang fp contract(off)
+  teno_poly_at<R>(p.c, p.x, p.t[1], p.t[2] - p.t[0], fma_(R(-2.0), p.t[1], p.t[0] + p.t[2]), o);
+}
+
+template <class R>
+TGKS_HD void teno_poly(const TenoParts<R>& p, const TenoSel& s, TenoPoly<R>& o) {
+#pragma clang fp contract(off)
+  const R z = R(0.0), one = R(1.0);
+  const R o0 = !s.lg && s.k0 ? one : z, o1 = s.lg || s.k1 ? one : z, o2 = !s.lg && s.k2 ? one : z;
+  const R l0 = fma_(R(2.0), p.c - p.b, p.t[0]), l2 = fma_(R(2.0), p.d - p.c, -p.t[2]);
+  const R y3 = s.lg ? p.t[2] - p.t[0] : z, y4 = s.lg ? fma_(R(-2.0), p.t[1], p.t[0] + p.t[2]) : z;
+  // 1/(m + 1) for m = 0 (exactly), 1, 2 further stencils: 1 - 2/3 m + m^2/6
+  const R m = ((o0 + o1) + o2) - 1.0;
+  const R inv = fma_(m, fma_(m, R(1.0 / 6.0), R(-2.0 / 3.0)), one);
+  const R l = fma_(o2, l2, fma_(o1, p.x, o0 * l0)) * inv;
+  const R t = fma_(o2, p.t[2], fma_(o1, p.t[1], o0 * p.t[0])) * inv;
+  teno_poly_at<R>(p.c, l, t, y3, y4, o);
 }
 
 // Selected polynomial at the Gauss points: val[m], der[m] for m = 0 (s-) and

@@ -187,26 +187,44 @@ __device__ __forceinline__ int fallback_side(double* w, double (*dw)[NC], const 
 }
 
 // The selection of five values and the selected polynomial at the Gauss
-// points; returns the flag (unused: not evaluated).  MODE SEL_FILTER or
-// SEL_RATIO: sure becomes false where the exact weights have to decide.  The
-// caller then takes those selections in a loop of its own (exact_flags: one
-// copy of the exact code, four bits per selection) and evaluates everything
-// again with SEL_GIVEN; one branch for all its selections leaves them one
-// straight line of code.
-constexpr int SEL_GIVEN = 3;
+// points; returns the flag (unused: not evaluated).
+//   SEL_SMOOTH: the large stencil; sure becomes false where the data is not
+//     smooth for certain (teno_smooth).  About 30 instructions against 135: a
+//     wavefront whose lanes are all smooth, or hold equal values, takes its
+//     selections in this form, and the others give up at the first that is
+//     not.  Where both forms apply they agree to the bit, so a result does
+//     not depend on the lanes beside it.  2-D four-quadrant problem 1024^2,
+//     20 steps: 15.6 -> 12.3 ms; double Mach reflection, 8 steps: 1.76 ->
+//     1.51 ms; a 97 x 61 grid with waves everywhere: 366 -> 367 us.  The same
+//     test in the 2-D normal step gained nothing there and cost the small
+//     grid 13 % (three short passes, one branch more in each).
+//   SEL_FILTER: sure becomes false where the exact weights have to decide.
+//     The caller then takes those selections in a loop of its own
+//     (exact_flags: one copy of the exact code, four bits per selection) and
+//     evaluates everything again with
+//   SEL_GIVEN: the flag given.
+constexpr int SEL_GIVEN = 3, SEL_SMOOTH = 4;
 
-template <int MODE>
+// EQ: five equal values count as smooth (their flag is then not the
+// selection's).
+template <int MODE, bool EQ = true>
 __device__ __forceinline__ unsigned select_poly(const double* Q, const TenoCfg& c, TenoPoly<double>& o, bool& sure,
                                                 unsigned given) {
   TenoParts<double> p;
   teno_parts(Q, p);
-  TenoSel s;
-  if constexpr (MODE == SEL_GIVEN)
-    s = teno_sel(given);
-  else
-    sure &= teno_certain<MODE>(Q, p, c, s);
-  teno_poly(p, s, o);
-  return s.flag();
+  if constexpr (MODE == SEL_SMOOTH) {
+    sure &= teno_smooth<EQ>(p);
+    teno_poly_large(p, o);
+    return 1u;
+  } else {
+    TenoSel s;
+    if constexpr (MODE == SEL_GIVEN)
+      s = teno_sel(given);
+    else
+      sure &= teno_certain<MODE>(Q, p, c, s);
+    teno_poly(p, s, o);
+    return s.flag();
+  }
 }
 
 // flags of n <= 8 selections from the exact weights, four bits each; load(i,
@@ -503,7 +521,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
       double o[4];
       unsigned fl;
       if (SCHEME == SCHEME_TENO_D) {
-        fl = teno_flag<SEL_FILTER>(Q, a.tn);
+        fl = teno_flag<SEL_FILTER, true>(Q, a.tn);
         teno_face(Q, fl, o);
       } else {
         fl = scheme_face<SCHEME>(Q, a.sc, o);
@@ -609,6 +627,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
           given |= (teno_exact_cold(Qw, a.tt) << (8 * k)) | (teno_exact_cold(Qn, a.tt) << (8 * k + 4));
         const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * k)) & 15u);
         const unsigned fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * k + 4)) & 15u);
+        if (MODE == SEL_SMOOTH && !all_lanes(sure)) return false;
         if (FLAGS) {
           a.tflags[((long long)(0 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fw;
           a.tflags[((long long)(1 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fq;
@@ -644,12 +663,18 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
           TenoPoly<double> w, n;
           fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * q)) & 15u);
           fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * q + 4)) & 15u);
+          if (MODE == SEL_SMOOTH && !all_lanes(sure)) return false;
 #pragma unroll
           for (int gp = 0; gp < 2; ++gp) {
             const double x = gp == 0 ? sg : -sg;
             gV[q][gp] = fma(x, w.odd, w.base);
             gD[q][gp] = fma(x, w.od, w.ev);
             gN[q][gp] = fma(x, n.odd, n.base);
+            if (MODE == SEL_SMOOTH) {  // evaluated here, not after the last early exit
+              gV[q][gp] = opaque(gV[q][gp]);
+              gD[q][gp] = opaque(gD[q][gp]);
+              gN[q][gp] = opaque(gN[q][gp]);
+            }
           }
         } else {
           double v[2], dv[2], vn[2], dvn[2];
@@ -675,7 +700,8 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
       tangential(std::integral_constant<int, SEL_GIVEN>());
     } else {
       bool sure = false;
-      if (a.tt.fast & TENO_FILTER_OK) sure = tangential(std::integral_constant<int, SEL_FILTER>());
+      if (!FLAGS && (a.tt.fast & TENO_RATIO_OK)) sure = tangential(std::integral_constant<int, SEL_SMOOTH>());
+      if (!sure && (a.tt.fast & TENO_FILTER_OK)) sure = tangential(std::integral_constant<int, SEL_FILTER>());
       if (!sure) {
         // characteristic fields take their flags as they are projected
         if (!CHAR)
@@ -823,8 +849,8 @@ __global__ __launch_bounds__(256) void recon3d_kernel(StageArgs a) {
     const double v = Wc[m * sax];
     Q[s] = cell_flip(g, c, f[0], f[1], f[2]) ? -v : v;
   }
-  const unsigned fl = teno_flag<SEL_RATIO>(Q, a.tn);
   double o[4];
+  const unsigned fl = teno_flag<SEL_RATIO>(Q, a.tn);
   teno_face(Q, fl, o);
   const double idn = 1.0 / g.dx[AX];
   const long long base = (long long)c * 4 * nr + (id % nr);
@@ -851,8 +877,10 @@ __global__ __launch_bounds__(256) void recon3d_kernel(StageArgs a) {
 //   * Flux: each lane evaluates its side's share of the equilibrium state
 //     and of the non-equilibrium moments (side_w0, side_part); the pair
 //     (m2 = 0, 1) adds the shares (a + b is exact-order independent), and
-//     both lanes evaluate the equilibrium part (flux_combine).  One side per
-//     lane keeps the flux within the register budget of two waves per SIMD.
+//     both lanes evaluate the equilibrium part (flux_combine).
+// Three wavefronts per SIMD (168 registers, 4 to 30 of them spilled for a
+// short while) instead of two keep the vector units busier: 128^3
+// Taylor-Green vortex, 2 steps: 19.3 -> 18.6 ms.
 // Tiles are dealt to the 8 XCDs in contiguous ranges.
 // FLAGS: record the tangential selections (stage 1), per face of this
 // direction: sweep 1 of the face's own line as [(q*2 + side)*5 + c] (q = 0:
@@ -862,7 +890,7 @@ __global__ __launch_bounds__(256) void recon3d_kernel(StageArgs a) {
 constexpr int B3_1 = 2, B3_2 = 16, L3 = 8;
 
 template <int AX, int STAGE, bool NS, bool EX = false, bool FLAGS = false>
-__global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a) {
+__global__ __launch_bounds__(L3 * B3_1 * B3_2, 3) void face3d_kernel(StageArgs a) {
   constexpr int NC = 5, B1 = B3_1, B2 = B3_2, NT = L3 * B1 * B2;
   constexpr int L1 = B1 + 4, L2 = B2 + 4;
   constexpr int T1 = (AX + 1) % 3, T2 = (AX + 2) % 3;
@@ -940,7 +968,18 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
       Qn[r] = sR[s][c][1][i2][j1 + r];
     }
     double v[2], dv[2], vn[2], dvn[2];
-    const unsigned fw = teno_flag<SEL_RATIO, true>(Qw, a.tt), fq = teno_flag<SEL_RATIO, true>(Qn, a.tt);
+    unsigned fw = 1u, fq = 1u;
+    bool smooth = false;
+    if (a.tt.fast & TENO_RATIO_OK) {
+      TenoParts<double> pw, pn;
+      teno_parts(Qw, pw);
+      teno_parts(Qn, pn);
+      smooth = all_lanes(teno_smooth<false>(pw) & teno_smooth<false>(pn));
+    }
+    if (!smooth) {
+      fw = teno_flag<SEL_RATIO, true>(Qw, a.tt);
+      fq = teno_flag<SEL_RATIO, true>(Qn, a.tt);
+    }
     // the inputs of the second sweep's selections: one fixed evaluation order
     teno_gauss_exact(Qw, fw, v, dv);
     teno_gauss_exact(Qn, fq, vn, dvn);
@@ -1002,11 +1041,16 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
         item_values(it, kind, c, Q);
         TenoPoly<double> w;
         const unsigned fl = select_poly<MODE>(Q, a.tt, w, sure, (given >> (4 * r)) & 15u);
+        if (MODE == SEL_SMOOTH && !all_lanes(sure)) return false;
 #pragma unroll
         for (int gp = 0; gp < 2; ++gp) {
           const double x = gp == 0 ? sg : -sg;
           sv[r][gp] = fma(x, w.odd, w.base);
           sd[r][gp] = fma(x, w.od, w.ev);
+          if (MODE == SEL_SMOOTH) {
+            sv[r][gp] = opaque(sv[r][gp]);
+            if (r != 2 && r != 5) sd[r][gp] = opaque(sd[r][gp]);  // (their derivatives are not used)
+          }
         }
         if (FLAGS) a.tflags[((long long)4 * NC + ((m1 * 3 + kind) * 2 + m2) * NC + c) * nf + fid] = (uint8_t)fl;
       } else {
@@ -1017,7 +1061,8 @@ __global__ __launch_bounds__(L3 * B3_1 * B3_2, 2) void face3d_kernel(StageArgs a
   };
   if (live) {
     bool sure = false;
-    if (a.tt.fast & TENO_FILTER_OK) sure = sweep2(std::integral_constant<int, SEL_RATIO>());
+    if (!FLAGS && (a.tt.fast & TENO_RATIO_OK)) sure = sweep2(std::integral_constant<int, SEL_SMOOTH>());
+    if (!sure && (a.tt.fast & TENO_FILTER_OK)) sure = sweep2(std::integral_constant<int, SEL_FILTER>());
     if (!sure) {
       given = exact_flags(8 - m3, a.tt, [&](int r, double* Q) {
         int kind, c;
