@@ -180,8 +180,7 @@ int tgks_step_adjoint(tgks_ctx* c, const double* W_n, const double* W_star, cons
   // W* of the forward step, unless the caller kept it (P is recomputed
   // too, unused)
   if (!W_star) {
-    if ((r = launch_faces(c, W_n, dt_dev, 1, nullptr))) return r;
-    if ((r = launch_update(c, 1, W_n, c->Ws, c->P, dt_dev, false))) return r;
+    if ((r = do_stage1(c, W_n, dt_dev, nullptr))) return r;
   }
   const double* Ws = W_star ? W_star : c->Ws;
   // stage 2 at W*: G* = sum_d (dFA*_d / dW*)^T D_d^T G

@@ -26,8 +26,6 @@ struct tgks_batch {
   int2* wcell = nullptr;         // cell work list
   int2* wface[NTILE2][2] = {};   // 2-D face work lists per tile shape and direction
   int nwface[NTILE2][2] = {};
-  int2* wface1 = nullptr;        // 1-D face work list
-  int nwface1 = 0;
   double *Ws = nullptr, *P = nullptr, *W2 = nullptr;
   double* FA[2] = {nullptr, nullptr};
   double* FB[2] = {nullptr, nullptr};
@@ -58,7 +56,6 @@ static void free_batch(tgks_batch* b) {
   (void)hipFree(b->wcell);
   for (int t = 0; t < NTILE2; ++t)
     for (int d = 0; d < 2; ++d) (void)hipFree(b->wface[t][d]);
-  (void)hipFree(b->wface1);
   (void)hipFree(b->Ws);
   (void)hipFree(b->P);
   (void)hipFree(b->W2);
@@ -85,6 +82,7 @@ static BatchArgs batch_args(tgks_batch* b, const double* W, double* o1, double* 
   a.inst = b->inst;
   a.work = work;
   a.W = W;
+  a.base = W;
   a.out1 = o1;
   a.out2 = o2;
   for (int d = 0; d < 2; ++d) {
@@ -122,28 +120,34 @@ static void batch_face2d(tgks_batch* b, const double* W, int ax, int stage) {
 #undef BF2
 }
 
-static int batch_faces(tgks_batch* b, const double* W, int stage) {
-  if (b->D == 1) {
-    BatchArgs a = batch_args(b, W, nullptr, nullptr, b->wface1);
-#define BF1(CH, EX)                                                                     \
-  if (stage == 1) {                                                                     \
-    if (b->ns) BLAUNCH((batch_face1d_kernel<1, true, CH, EX>), b->nwface1, 256, a);     \
-    else BLAUNCH((batch_face1d_kernel<1, false, CH, EX>), b->nwface1, 256, a);          \
-  } else {                                                                              \
-    if (b->ns) BLAUNCH((batch_face1d_kernel<2, true, CH, EX>), b->nwface1, 256, a);     \
-    else BLAUNCH((batch_face1d_kernel<2, false, CH, EX>), b->nwface1, 256, a);          \
+// 1-D: one stage in one launch
+static int batch_line(tgks_batch* b, int stage, const double* W, const double* base, double* o1, double* o2) {
+  BatchArgs a = batch_args(b, W, o1, o2, b->wcell);
+  a.base = base;
+#define BF1(CH, EX)                                                                 \
+  if (stage == 1) {                                                                 \
+    if (b->ns) BLAUNCH((batch_line_kernel<1, true, CH, EX>), b->ncblk, 256, a);     \
+    else BLAUNCH((batch_line_kernel<1, false, CH, EX>), b->ncblk, 256, a);          \
+  } else {                                                                          \
+    if (b->ns) BLAUNCH((batch_line_kernel<2, true, CH, EX>), b->ncblk, 256, a);     \
+    else BLAUNCH((batch_line_kernel<2, false, CH, EX>), b->ncblk, 256, a);          \
   }
-    if (b->chr && b->fb) {
-      BF1(true, true)
-    } else if (b->chr) {
-      BF1(true, false)
-    } else if (b->fb) {
-      BF1(false, true)
-    } else {
-      BF1(false, false)
-    }
-#undef BF1
+  if (b->chr && b->fb) {
+    BF1(true, true)
+  } else if (b->chr) {
+    BF1(true, false)
+  } else if (b->fb) {
+    BF1(false, true)
   } else {
+    BF1(false, false)
+  }
+#undef BF1
+  HIPCHK(hipGetLastError());
+  return TGKS_OK;
+}
+
+static int batch_faces(tgks_batch* b, const double* W, int stage) {
+  {
     for (int ax = 0; ax < 2; ++ax) {
       if (b->chr || b->fb) {  // one tile shape on the characteristic / fallback path
         if (b->chr && b->fb) batch_face2d<CHAR_TILE2, true, true>(b, W, ax, stage);
@@ -169,13 +173,8 @@ static int batch_faces(tgks_batch* b, const double* W, int stage) {
 
 static int batch_update(tgks_batch* b, int stage, const double* W, double* o1, double* o2) {
   BatchArgs a = batch_args(b, W, o1, o2, b->wcell);
-  if (b->D == 1) {
-    if (stage == 1) BLAUNCH((batch_update_kernel<1, 1, false>), b->ncblk, 256, a);
-    else BLAUNCH((batch_update_kernel<1, 2, true>), b->ncblk, 256, a);
-  } else {
-    if (stage == 1) BLAUNCH((batch_update_kernel<2, 1, false>), b->ncblk, 256, a);
-    else BLAUNCH((batch_update_kernel<2, 2, true>), b->ncblk, 256, a);
-  }
+  if (stage == 1) BLAUNCH((batch_update_kernel<2, 1, false>), b->ncblk, 256, a);
+  else BLAUNCH((batch_update_kernel<2, 2, true>), b->ncblk, 256, a);
   HIPCHK(hipGetLastError());
   return TGKS_OK;
 }
@@ -199,6 +198,10 @@ static int batch_cfl_start(tgks_batch* b, const double* W, double cfl, double t_
 
 static int batch_step(tgks_batch* b, const double* W, double* out) {
   int r;
+  if (b->D == 1) {
+    if ((r = batch_line(b, 1, W, W, b->Ws, b->P))) return r;
+    return batch_line(b, 2, b->Ws, b->P, out, nullptr);
+  }
   if ((r = batch_faces(b, W, 1))) return r;
   if ((r = batch_update(b, 1, W, b->Ws, b->P))) return r;
   if ((r = batch_faces(b, b->Ws, 2))) return r;
@@ -247,7 +250,7 @@ int tgks_batch_create(const tgks_params* p, int32_t n_inst, void* stream, tgks_b
   b->chr = p[0].recon == TGKS_RECON_CHARACTERISTIC;
   b->fb = p[0].fallback != 0;
   b->stream = (hipStream_t)stream;
-  std::vector<int2> wcell, wface1, wface[NTILE2][2];
+  std::vector<int2> wcell, wface[NTILE2][2];
   long long woff = 0, foff[2] = {0, 0};
   int blk = 0;
   b->woff.push_back(0);
@@ -285,15 +288,13 @@ int tgks_batch_create(const tgks_params* p, int32_t n_inst, void* stream, tgks_b
       for (int e = 0; e < D; ++e) nf *= (long long)(g.n[e] + (e == d));
       foff[d] += (long long)b->nc * nf;
     }
-    const int nblk = (int)((g.ncell + 255) / 256);
+    const int per = D == 1 ? BATCH_LINE : 256;
+    const int nblk = (int)((g.ncell + per - 1) / per);
     I.blk0 = blk;
     I.nblk = nblk;
     blk += nblk;
     for (int k = 0; k < nblk; ++k) wcell.push_back(make_int2(i, k));
-    if (D == 1) {
-      const int nb = (g.n[0] + 1 + 255) / 256;
-      for (int k = 0; k < nb; ++k) wface1.push_back(make_int2(i, k));
-    } else {
+    if (D == 2) {
       for (int ax = 0; ax < 2; ++ax) {
         // one work list per tile shape; ntile is set with the shape
         for (int t = 0; t < NTILE2; ++t) {
@@ -309,13 +310,12 @@ int tgks_batch_create(const tgks_params* p, int32_t n_inst, void* stream, tgks_b
   b->nface[0] = foff[0];
   b->nface[1] = foff[1];
   b->ncblk = blk;
-  b->nwface1 = (int)wface1.size();
   for (int t = 0; t < NTILE2; ++t)
     for (int d = 0; d < 2; ++d) b->nwface[t][d] = (int)wface[t][d].size();
   const size_t state = (size_t)b->total * sizeof(double);
   bool ok = hipMalloc(&b->Ws, state) == hipSuccess && hipMalloc(&b->P, state) == hipSuccess &&
             hipMalloc(&b->W2, state) == hipSuccess;
-  for (int d = 0; d < D && ok; ++d)
+  for (int d = 0; d < D && D > 1 && ok; ++d)  // (1-D steps have no face arrays)
     ok = hipMalloc(&b->FA[d], (size_t)b->nface[d] * sizeof(double)) == hipSuccess &&
          hipMalloc(&b->FB[d], (size_t)b->nface[d] * sizeof(double)) == hipSuccess;
   if (ok)
@@ -323,7 +323,7 @@ int tgks_batch_create(const tgks_params* p, int32_t n_inst, void* stream, tgks_b
          hipMalloc(&b->clock, 2 * (size_t)n_inst * sizeof(double)) == hipSuccess &&
          hipMalloc(&b->steps, (size_t)n_inst * sizeof(long long)) == hipSuccess &&
          hipMalloc(&b->fail, (size_t)n_inst * sizeof(unsigned long long)) == hipSuccess;
-  if (ok) ok = upload(&b->wcell, wcell) && upload(&b->wface1, wface1);
+  if (ok) ok = upload(&b->wcell, wcell);
   for (int t = 0; t < NTILE2 && ok; ++t)
     for (int d = 0; d < 2 && ok; ++d) ok = upload(&b->wface[t][d], wface[t][d]);
   if (ok) ok = hipMalloc(&b->inst, (size_t)n_inst * sizeof(BatchInst)) == hipSuccess;

@@ -21,13 +21,14 @@ struct BatchInst {
   long long woff;     // first double of the instance's state in a packed state
   long long foff[2];  // first double of its face arrays, per direction
   int ntile[2];       // 2-D: face tiles along the normal axis, per direction
-  int blk0, nblk;     // its cell blocks (256 cells each) in the cell work list
+  int blk0, nblk;     // its cell blocks (256 cells each, 1-D: BATCH_LINE) in the cell work list
 };
 
 struct BatchArgs {
   const BatchInst* inst;
   const int2* work;  // (instance, local block)
   const double* W;
+  const double* base;  // 1-D: what the stage's flux differences are subtracted from
   double* out1;
   double* out2;
   double* FA[2];
@@ -64,11 +65,35 @@ __device__ __forceinline__ StageArgs batch_stage(const BatchArgs& b, const Batch
   return a;
 }
 
+// 1-D: one stage, blocks of four wavefronts (BATCH_LINE cells)
+constexpr int BATCH_LINE = 4 * LINE_CELLS;
+
 template <int STAGE, bool NS, bool CHAR = false, bool EX = false>
-__global__ __launch_bounds__(256) void batch_face1d_kernel(BatchArgs b) {
+__global__ __launch_bounds__(256) void batch_line_kernel(BatchArgs b) {
   const int2 w = b.work[blockIdx.x];
-  const StageArgs a = batch_stage(b, b.inst[w.x], w.x, 0);
-  face1d_body<STAGE, NS, false, CHAR, EX>(a, w.y * 256 + (int)threadIdx.x);
+  const BatchInst& I = b.inst[w.x];
+  LineArgs l;
+  l.s = batch_stage(b, I, w.x, 0);
+  l.base = b.base + I.woff;
+  l.out1 = b.out1 + I.woff;
+  l.out2 = STAGE == 1 ? b.out2 + I.woff : nullptr;
+  l.mu = I.mu;
+  l.idx = 1.0 / I.g.dx[0];
+  if (!(*l.s.dt > 0.0)) {
+    // the instance has stopped: its state stays, without the fluxes
+    const int c = w.y * BATCH_LINE + (int)threadIdx.x;
+    const bool live = (int)threadIdx.x < BATCH_LINE && c < I.g.n[0];
+    double v[3] = {1.0, 0.0, 1.0};
+    for (int q = 0; live && q < 3; ++q) {
+      v[q] = l.base[(long long)q * I.g.n[0] + c];
+      l.out1[(long long)q * I.g.n[0] + c] = v[q];
+      if (STAGE == 1) l.out2[(long long)q * I.g.n[0] + c] = v[q];
+    }
+    if (STAGE == 2) block_cfl<1>(live, v, I.gamma, I.mu, I.g.dx[0], b.partial + I.blk0 + w.y);
+    return;
+  }
+  line_body<STAGE, NS, false, STAGE == 2, CHAR, EX>(l, (w.y * 4 + (int)(threadIdx.x >> 6)) * LINE_CELLS,
+                                                     b.partial + I.blk0 + w.y);
 }
 
 template <int AX, int STAGE, bool NS, int TILE, bool CHAR = false, bool EX = false>
@@ -105,7 +130,8 @@ template <int D>
 __global__ __launch_bounds__(256) void batch_cfl_partial_kernel(BatchArgs b) {
   const int2 w = b.work[blockIdx.x];
   const BatchInst& I = b.inst[w.x];
-  cfl_partial_body<D>(I.g, b.W + I.woff, I.gamma, I.mu, (long long)w.y * 256 + threadIdx.x,
+  constexpr int per = D == 1 ? BATCH_LINE : 256;
+  cfl_partial_body<D>(I.g, b.W + I.woff, I.gamma, I.mu, (long long)w.y * per + threadIdx.x, (int)threadIdx.x < per,
                       b.partial + I.blk0 + w.y);
 }
 

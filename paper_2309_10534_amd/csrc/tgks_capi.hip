@@ -11,7 +11,62 @@ using namespace tgks;
 
 #define LAUNCH(kern, grid, block, args) hipLaunchKernelGGL(kern, grid, block, 0, c->stream, args)
 
-// face fluxes of one stage in every direction
+// one stage of a 1-D step
+int launch_line(tgks_ctx* c, int stage, const double* W, const double* base, double* o1, double* o2, const double* dt,
+                uint8_t* flags, bool cfl) {
+  const bool fl = flags != nullptr && stage == 1;
+  LineArgs l;
+  l.s = stage_args(c, W, 0, dt);
+  if (fl) l.s.nflags = flags;
+  l.base = base;
+  l.out1 = o1;
+  l.out2 = o2;
+  l.mu = c->p.mu;
+  l.idx = 1.0 / c->g.dx[0];
+  switch (c->p.scheme) {
+    case TGKS_SCHEME_WENO_AO:
+      return launch_scheme_line<SCHEME_WENO_AO>(c, l, stage, fl, cfl);
+    case TGKS_SCHEME_TENO5:
+      return launch_scheme_line<SCHEME_TENO5>(c, l, stage, fl, cfl);
+    case TGKS_SCHEME_WENO_Z:
+      return launch_scheme_line<SCHEME_WENO_Z>(c, l, stage, fl, cfl);
+    default:
+      break;
+  }
+  Timer tm(c, 0);
+  const dim3 grid((unsigned)c->nblk), blk(64 * c->line_waves);
+#define L1(...) hipLaunchKernelGGL((line_kernel<__VA_ARGS__>), grid, blk, 0, c->stream, l, c->partial)
+#define F1(CH, EX)                                     \
+  if (stage == 1 && fl) {                              \
+    if (c->ns) L1(1, true, true, false, CH, EX);       \
+    else L1(1, false, true, false, CH, EX);            \
+  } else if (stage == 1) {                             \
+    if (c->ns) L1(1, true, false, false, CH, EX);      \
+    else L1(1, false, false, false, CH, EX);           \
+  } else if (cfl) {                                    \
+    if (c->ns) L1(2, true, false, true, CH, EX);       \
+    else L1(2, false, false, true, CH, EX);            \
+  } else {                                             \
+    if (c->ns) L1(2, true, false, false, CH, EX);      \
+    else L1(2, false, false, false, CH, EX);           \
+  }
+  const bool ch = c->p.recon == TGKS_RECON_CHARACTERISTIC;
+  if (ch && c->ex) {
+    F1(true, true)
+  } else if (ch) {
+    F1(true, false)
+  } else if (c->ex) {
+    F1(false, true)
+  } else {
+    F1(false, false)
+  }
+#undef F1
+#undef L1
+  HIPCHK(hipGetLastError());
+  return TGKS_OK;
+}
+
+// face fluxes of one stage of a 2-D or 3-D step in every direction
 int launch_faces(tgks_ctx* c, const double* W, const double* dt, int stage, uint8_t* flags) {
   const int D = c->g.D;
   if (c->p.scheme != TGKS_SCHEME_TENO_D) {
@@ -23,7 +78,7 @@ int launch_faces(tgks_ctx* c, const double* W, const double* dt, int stage, uint
         a[ax].nflags = flags;
         long long off = (long long)D * c->nc * c->ncell;
         for (int d = 0; d < ax; ++d) off += 4LL * c->nc * c->nface[d];
-        a[ax].tflags = D == 2 ? flags + off : nullptr;
+        a[ax].tflags = flags + off;
       }
     }
     switch (c->p.scheme) {
@@ -65,34 +120,7 @@ int launch_faces(tgks_ctx* c, const double* W, const double* dt, int stage, uint
         a.tflags = flags + off;
       }
     }
-    if (D == 1) {
-      Timer tm(c, 0);
-      dim3 grid((unsigned)((c->g.n[0] + 1 + 255) / 256));
-#define F1(CH, EX)                                                                  \
-  if (stage == 1) {                                                                 \
-    if (fl) {                                                                       \
-      if (c->ns) LAUNCH((face1d_kernel<1, true, true, CH, EX>), grid, dim3(256), a);  \
-      else LAUNCH((face1d_kernel<1, false, true, CH, EX>), grid, dim3(256), a);       \
-    } else {                                                                        \
-      if (c->ns) LAUNCH((face1d_kernel<1, true, false, CH, EX>), grid, dim3(256), a); \
-      else LAUNCH((face1d_kernel<1, false, false, CH, EX>), grid, dim3(256), a);      \
-    }                                                                               \
-  } else {                                                                          \
-    if (c->ns) LAUNCH((face1d_kernel<2, true, false, CH, EX>), grid, dim3(256), a);   \
-    else LAUNCH((face1d_kernel<2, false, false, CH, EX>), grid, dim3(256), a);        \
-  }
-      const bool ch = c->p.recon == TGKS_RECON_CHARACTERISTIC;
-      if (ch && c->ex) {
-        F1(true, true)
-      } else if (ch) {
-        F1(true, false)
-      } else if (c->ex) {
-        F1(false, true)
-      } else {
-        F1(false, false)
-      }
-#undef F1
-    } else if (D == 2) {
+    if (D == 2) {
       Timer tm(c, ax);
       launch_face2d_any(c, a, ax, stage, fl);
     } else {
@@ -132,9 +160,7 @@ int launch_update(tgks_ctx* c, int stage, const double* W, double* o1, double* o
   if (stage == 1) LAUNCH((update_kernel<DV, 1, false>), grid, dim3(256), u);    \
   else if (cfl) LAUNCH((update_kernel<DV, 2, true>), grid, dim3(256), u);       \
   else LAUNCH((update_kernel<DV, 2, false>), grid, dim3(256), u);
-  if (c->g.D == 1) {
-    UPD(1)
-  } else if (c->g.D == 2) {
+  if (c->g.D == 2) {
     UPD(2)
   } else {
     UPD(3)
@@ -146,13 +172,17 @@ int launch_update(tgks_ctx* c, int stage, const double* W, double* o1, double* o
 
 static int launch_cfl_partial(tgks_ctx* c, const double* W) {
   Timer tm(c, 6);
-  dim3 grid((unsigned)c->nblk);
+  const dim3 grid((unsigned)c->nblk), blk(c->g.D == 1 ? 64 * c->line_waves : 256);
+#define CFLP(DV)                                                                                               \
+  hipLaunchKernelGGL((cfl_partial_kernel<DV>), grid, blk, 0, c->stream, c->g, W, c->p.gamma, c->p.mu, c->per, \
+                     c->partial)
   if (c->g.D == 1)
-    hipLaunchKernelGGL((cfl_partial_kernel<1>), grid, dim3(256), 0, c->stream, c->g, W, c->p.gamma, c->p.mu, c->partial);
+    CFLP(1);
   else if (c->g.D == 2)
-    hipLaunchKernelGGL((cfl_partial_kernel<2>), grid, dim3(256), 0, c->stream, c->g, W, c->p.gamma, c->p.mu, c->partial);
+    CFLP(2);
   else
-    hipLaunchKernelGGL((cfl_partial_kernel<3>), grid, dim3(256), 0, c->stream, c->g, W, c->p.gamma, c->p.mu, c->partial);
+    CFLP(3);
+#undef CFLP
   HIPCHK(hipGetLastError());
   return TGKS_OK;
 }
@@ -166,11 +196,18 @@ static int launch_finalize(tgks_ctx* c, double cfl, double t_in, double t_end, d
   return TGKS_OK;
 }
 
+int do_stage1(tgks_ctx* c, const double* W, const double* dt, uint8_t* flags) {
+  if (c->g.D == 1) return launch_line(c, 1, W, W, c->Ws, c->P, dt, flags, false);
+  int r;
+  if ((r = launch_faces(c, W, dt, 1, flags))) return r;
+  return launch_update(c, 1, W, c->Ws, c->P, dt, false);
+}
+
 // one S2O4 step W -> out, dt read from dt_dev
 int do_step(tgks_ctx* c, const double* W, double* out, const double* dt, uint8_t* flags, bool cfl) {
   int r;
-  if ((r = launch_faces(c, W, dt, 1, flags))) return r;
-  if ((r = launch_update(c, 1, W, c->Ws, c->P, dt, false))) return r;
+  if ((r = do_stage1(c, W, dt, flags))) return r;
+  if (c->g.D == 1) return launch_line(c, 2, c->Ws, c->P, out, nullptr, dt, nullptr, cfl);
   if ((r = launch_faces(c, c->Ws, dt, 2, nullptr))) return r;
   if ((r = launch_update(c, 2, c->P, out, nullptr, dt, cfl))) return r;
   return TGKS_OK;
@@ -272,7 +309,13 @@ void init_ctx_host(tgks_ctx* c, const tgks_params* p, void* stream) {
     for (int e = 0; e < 3; ++e) nf *= (long long)(g.n[e] + (e == d));
     c->nface[d] = d < D ? nf : 0;
   }
-  c->nblk = (int)((g.ncell + 255) / 256);
+  if (D == 1) {
+    // one wavefront per block spreads a small grid over the chip (400 cells:
+    // 7 compute units); four keep the partial minima of a large one few
+    c->line_waves = g.ncell <= 1024LL * LINE_CELLS ? 1 : 4;
+    c->per = LINE_CELLS * c->line_waves;
+  }
+  c->nblk = (int)((g.ncell + c->per - 1) / c->per);
 }
 
 extern "C" {
@@ -288,7 +331,7 @@ int tgks_create(const tgks_params* p, void* stream, tgks_ctx** out) {
   const size_t state = (size_t)c->nc * g.ncell * sizeof(double);
   bool ok = hipMalloc(&c->Ws, state) == hipSuccess && hipMalloc(&c->P, state) == hipSuccess &&
             hipMalloc(&c->W2, state) == hipSuccess;
-  for (int d = 0; d < D && ok; ++d)
+  for (int d = 0; d < D && D > 1 && ok; ++d)  // (the 1-D step has no face arrays)
     ok = hipMalloc(&c->FA[d], (size_t)c->nc * c->nface[d] * sizeof(double)) == hipSuccess &&
          hipMalloc(&c->FB[d], (size_t)c->nc * c->nface[d] * sizeof(double)) == hipSuccess;
   if (ok && D == 3) {

@@ -1561,18 +1561,16 @@ TGKS_HD bool gp_flux_eq(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R
 constexpr int BC_NOSLIP = 3;  // boundary kind of the no-slip adiabatic wall
 constexpr int BC_PRESCRIBED = 4;  // boundary kind of given states (resolved before the map)
 
+// Selects, no division or branch: an index used by a face is at most three
+// cells outside (n >= 3), so one wrap serves; what lies farther outside feeds
+// no face and is clamped into the domain so that every load stays in bounds.
 TGKS_HD int map_index(int i, int n, int bclo, int bchi, int& flip) {
-  if (i >= 0 && i < n) return i;
-  const int bc = i < 0 ? bclo : bchi;
-  if (bc == 0) {
-    int r = i % n;
-    return r < 0 ? r + n : r;
-  }
-  if (bc == 1) return i < 0 ? 0 : n - 1;
-  flip ^= bc == BC_NOSLIP ? 2 : 1;
-  // mirror image; cells farther than n outside are never used by a face and
-  // are clamped into the domain so that every load stays in bounds
-  const int r = i < 0 ? -1 - i : 2 * n - 1 - i;
+  const bool low = i < 0, out = low || i >= n;
+  const int bc = low ? bclo : bchi;
+  const int wrap = low ? i + n : i - n, edge = low ? 0 : n - 1, mirror = low ? -1 - i : (n - 1) - (i - n);
+  int r = bc == 0 ? wrap : (bc == 1 ? edge : mirror);
+  r = out ? r : i;
+  flip ^= out && bc >= 2 ? (bc == BC_NOSLIP ? 2 : 1) : 0;
   return r < 0 ? 0 : (r >= n ? n - 1 : r);
 }
 

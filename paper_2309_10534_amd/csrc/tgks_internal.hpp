@@ -40,7 +40,9 @@ struct tgks_ctx {
   double* FB[3] = {nullptr, nullptr, nullptr};
   double* R = nullptr;
   double* partial = nullptr;
-  int nblk = 0;
+  int nblk = 0;          // CFL partial minima (blocks of the updates)
+  int per = 256;         // cells per block
+  int line_waves = 1;    // 1-D: wavefronts per block of the line kernel
   double* clock = nullptr;
   unsigned long long* fail = nullptr;
   // prescribed sides: states, lines, and the time of the state being stepped
@@ -205,10 +207,18 @@ inline StageArgs stage_args(tgks_ctx* c, const double* W, int ax, const double* 
 int launch_face2d_any(tgks_ctx* c, const StageArgs& a, int ax, int stage, bool fl);
 int launch_face2d_xy_any(tgks_ctx* c, const StageArgs& ax, const StageArgs& ay, int stage, bool fl);
 
-// face kernels of a comparison scheme, all directions of one stage
+// 2-D face kernels of a comparison scheme, both directions of one stage
 // (tgks_scheme_*.hip)
 template <int SCHEME>
 int launch_scheme_faces(tgks_ctx* c, const StageArgs* a, int stage, bool fl);
+
+// 1-D: one stage in one kernel (faces and update): out1 = W* or W^{n+1}, out2
+// = P (stage 1); W: the state the fluxes are computed from, base: what they
+// are subtracted from
+int launch_line(tgks_ctx* c, int stage, const double* W, const double* base, double* o1, double* o2, const double* dt,
+                uint8_t* flags, bool cfl);
+template <int SCHEME>
+int launch_scheme_line(tgks_ctx* c, const LineArgs& l, int stage, bool fl, bool cfl);
 
 // 3-D normal reconstruction and face kernels of direction AX (tgks_face3d_*.hip)
 template <int AX>
@@ -217,7 +227,9 @@ int launch_face3d_ax(tgks_ctx* c, const StageArgs& a, int stage, bool fl);
 // host-side description of a grid without device memory (tgks_capi.hip)
 void init_ctx_host(tgks_ctx* c, const tgks_params* p, void* stream);
 
-// forward pieces of one step (tgks_capi.hip)
+// forward pieces of one step (tgks_capi.hip); stage 1: W -> Ws, P of the
+// context; cfl: also the CFL partial minima of the new state
+int do_stage1(tgks_ctx* c, const double* W, const double* dt, uint8_t* flags);
 int do_step(tgks_ctx* c, const double* W, double* out, const double* dt, uint8_t* flags, bool cfl);
 int launch_faces(tgks_ctx* c, const double* W, const double* dt, int stage, uint8_t* flags);
 int launch_update(tgks_ctx* c, int stage, const double* W, double* o1, double* o2, const double* dt, bool cfl);

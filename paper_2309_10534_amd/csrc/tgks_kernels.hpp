@@ -256,90 +256,174 @@ __device__ __forceinline__ void wall_fluxes(const Geom& g, int ax, int f, double
 }
 
 // ---------------------------------------------------------------------------
-// 1-D: one thread per face.
+// CFL time step (Sec. 5 preamble).
 // ---------------------------------------------------------------------------
+// minimum over the block (blockDim.x a multiple of 64, at most 1024);
+// valid in thread 0
+__device__ __forceinline__ double block_min(double v, double* red) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  if (l == 0) red[w] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) v = fmin(v, red[i]);
+  }
+  return v;
+}
+
+// local CFL limit of one cell (Sec. 5 preamble); NaN for a non-physical state
+template <int D>
+__device__ __forceinline__ double cell_dt(const double* w, double gamma, double mu, double dxm) {
+  const double rho = w[0];
+  double ke = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const double u = w[d + 1] / rho;
+    ke += u * u;
+  }
+  const double p = (gamma - 1.0) * (w[D + 1] - 0.5 * rho * ke);
+  if (!(rho > 0.0) || !(p > 0.0)) return NAN;
+  double v = dxm / (sqrt(ke) + sqrt(gamma * p / rho));
+  if (mu > 0.0) v = fmin(v, dxm * dxm * rho / (4.0 * mu));
+  return v;
+}
+
+// the block's CFL minimum over its live cells' states w, to *partial
+template <int D>
+__device__ __forceinline__ void block_cfl(bool live, const double* w, double gamma, double mu, double dxm,
+                                          double* partial) {
+  __shared__ double red[16];  // one entry per wave, up to 1024 threads
+  double v = live ? cell_dt<D>(w, gamma, mu, dxm) : INFINITY;
+  // NaN (non-physical cell) wins the reduction
+  const bool nan = live && !(v == v);
+  v = block_min(nan ? -INFINITY : v, red);
+  if (threadIdx.x == 0) *partial = v == -INFINITY ? NAN : v;
+}
+
+// ---------------------------------------------------------------------------
+// 1-D: one stage of a step in one kernel, faces and update together.  A
+// wavefront owns LINE_CELLS = 62 consecutive cells: lane i reconstructs cell
+// c = first - 1 + i and evaluates the flux of the face below it, the left
+// state and then the upper face's flux coming from the neighbouring lanes, so
+// that lanes 1..62 update their cells without a face array between two
+// launches.  What bounds a single small grid is latency: the chain of
+// dependent loads at the start of each kernel and of one lane's arithmetic
+// (half of a face launch's 10 us were waits for memory).  Three selections
+// per lane instead of six, two launches per step fewer, every load issued
+// before the first wait: 50 steps of 400 cells 0.82 ms (1.42 with a face and
+// an update kernel per stage), 10 steps of 128 uneven tubes 98 us (168).
+// ---------------------------------------------------------------------------
+constexpr int LINE_CELLS = 62;
+
+struct LineArgs {
+  StageArgs s;
+  const double* base;  // what the stage's flux differences are subtracted from: stage 1: s.W; stage 2: P
+  double* out1;        // stage 1: W*; stage 2: W^{n+1}
+  double* out2;        // stage 1: P
+  double mu, idx;      // viscosity; 1 / dx
+};
+
+// value of the lane below (UP = false) or above (UP = true)
+template <bool UP>
+__device__ __forceinline__ double lane_shift(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), UP ? 0x130 : 0x138, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), UP ? 0x130 : 0x138, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+
 // EX: prescribed sides or the first-order fallback may be on (a separate
 // instantiation, so that grids without them run the plain code)
 // SCHEME: the reconstruction (SCHEME_TENO_D, the paper's scheme, or one of
 // its comparison schemes)
-template <int STAGE, bool NS, bool FLAGS, bool CHAR = false, bool EX = false, int SCHEME = SCHEME_TENO_D>
-__device__ __forceinline__ void face1d_body(const StageArgs& a, int f) {
+// first: the wavefront's first cell; partial (CFL): where the block's minimum
+// over its cells goes.  A step of dt <= 0 or NaN leaves the state as it is:
+// decided at the end, so that no load waits for dt.
+template <int STAGE, bool NS, bool FLAGS, bool CFL, bool CHAR = false, bool EX = false, int SCHEME = SCHEME_TENO_D>
+__device__ __forceinline__ void line_body(const LineArgs& l, int first, double* partial) {
+  const StageArgs& a = l.s;
+  const int n = a.g.n[0], i = threadIdx.x & 63;
+  const int f = first - 1 + i;  // the lane's cell and the face below it
+  const bool own = i >= 1 && i <= LINE_CELLS && f < n;  // the lane updates its cell
+  const bool face = i >= 1 && f <= n;
+  // the constants, loaded together before the first wait (one latency of the
+  // scalar cache instead of one where each group is used)
+  asm volatile("" ::"s"(l.idx), "s"(a.g.bclo[0]), "s"(a.g.bchi[0]), "s"(a.fc.N), "s"(a.fc.mu), "s"(a.fc.c1),
+               "s"(a.fc.c2), "s"(a.fc.tau_mode), "s"(a.tn.fast), "s"(a.tn.eps4), "s"(a.tn.ct1_up), "s"(a.tn.ct1_dn),
+               "s"(a.tn.ct2_up), "s"(a.tn.ct2_dn), "s"(a.W), "s"(a.dt), "s"(l.base), "s"(l.out1));
   const double dt = *a.dt;
-  if (!(dt > 0.0)) return;
-  const int n = a.g.n[0];
-  if (f > n) return;
-  double Wl[3], Wr[3], dWl[1][3], dWr[1][3], dW0[1][3];
-  const double idx = 1.0 / a.g.dx[0];  // normal slopes per unit length
   const double tb = EX ? boundary_time(a, STAGE, dt) : 0.0;
+  // the cells f-3 .. f+2 around the face (the lane's own: C[3])
+  double C[6][3], w[3];
+#pragma unroll
+  for (int r = 0; r < 6; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      C[r][c] = EX ? cell_value(a.g, a.pb, a.W, c, f - 3 + r, 0, tb) : load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
+  const int fc = f < 0 ? 0 : (f >= n ? n - 1 : f);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) w[c] = l.base[(long long)c * n + fc];
+  double A[3] = {0, 0, 0}, B[3] = {0, 0, 0};
+  const bool adv = dt > 0.0;
+  double Wl[3], Wr[3], dWl[1][3], dWr[1][3], dW0[1][3];
+  const double idx = l.idx;  // normal slopes per unit length
   if (CHAR) {
-    double C[6][3];
-#pragma unroll
-    for (int r = 0; r < 6; ++r)
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        C[r][c] = EX ? cell_value(a.g, a.pb, a.W, c, f - 3 + r, 0, tb) : load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
     unsigned fr[3];
     char_recon_face<1>(a.gamma, C, a.tn, idx, Wl, dWl[0], Wr, dWr[0], fr);
-    if (FLAGS && f < n)
+    if (FLAGS && own && adv)
 #pragma unroll
       for (int k = 0; k < 3; ++k) a.nflags[(long long)k * n + f] = (uint8_t)fr[k];
   } else {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      double Q[6];
-#pragma unroll
-      for (int r = 0; r < 6; ++r)
-        Q[r] = EX ? cell_value(a.g, a.pb, a.W, c, f - 3 + r, 0, tb) : load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
+      const double Q[5] = {C[1][c], C[2][c], C[3][c], C[4][c], C[5][c]};
       double o[4];
+      unsigned fl;
       if (SCHEME == SCHEME_TENO_D) {
-        teno_face(Q, teno_flag<SEL_FILTER, true>(Q, a.tn), o);
-        Wl[c] = o[2];
-        dWl[0][c] = o[3] * idx;
-        const unsigned fr = teno_flag<SEL_FILTER, true>(Q + 1, a.tn);
-        teno_face(Q + 1, fr, o);
-        Wr[c] = o[0];
-        dWr[0][c] = o[1] * idx;
-        if (FLAGS && f < n) a.nflags[(long long)c * n + f] = (uint8_t)fr;
+        fl = teno_flag<SEL_FILTER, true>(Q, a.tn);
+        teno_face(Q, fl, o);
       } else {
-        scheme_face<SCHEME>(Q, a.sc, o);
-        Wl[c] = o[2];
-        dWl[0][c] = o[3] * idx;
-        const unsigned fr = scheme_face<SCHEME>(Q + 1, a.sc, o);
-        Wr[c] = o[0];
-        dWr[0][c] = o[1] * idx;
-        if (FLAGS && f < n) a.nflags[(long long)c * n + f] = (uint8_t)fr;
+        fl = scheme_face<SCHEME>(Q, a.sc, o);
         // separately reconstructed equilibrium slope (Eq. 3.12)
-        if (SCHEME >= SCHEME_TENO5) dW0[0][c] = eq_slope(Q[1], Q[2], Q[3], Q[4]) * idx;
+        if (SCHEME >= SCHEME_TENO5) dW0[0][c] = eq_slope(C[1][c], C[2][c], C[3][c], C[4][c]) * idx;
       }
+      Wr[c] = o[0];
+      dWr[0][c] = o[1] * idx;
+      Wl[c] = lane_shift<false>(o[2]);
+      dWl[0][c] = lane_shift<false>(o[3] * idx);
+      if (FLAGS && own && adv) a.nflags[(long long)c * n + f] = (uint8_t)fl;
     }
   }
-  if (EX && a.fallback) {
-    double Cl[3], Cr[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      Cl[c] = cell_value(a.g, a.pb, a.W, c, f - 1, 0, tb);
-      Cr[c] = cell_value(a.g, a.pb, a.W, c, f, 0, tb);
+  if (face) {
+    if (EX && a.fallback) {
+      const int nfb =
+          fallback_side<3, 1>(Wl, dWl, C[2], a.gamma) + fallback_side<3, 1>(Wr, dWr, C[3], a.gamma);
+      // (the wavefront's last face is the next one's first: counted there)
+      if (nfb && adv && a.fbc && (own || (f == n && first < n))) atomicAdd(a.fbc, (unsigned long long)nfb);
     }
-    const int nfb = fallback_side<3, 1>(Wl, dWl, Cl, a.gamma) + fallback_side<3, 1>(Wr, dWr, Cr, a.gamma);
-    if (nfb && a.fbc) atomicAdd(a.fbc, (unsigned long long)nfb);
+    const bool ok = SCHEME >= SCHEME_TENO5 ? gp_flux_eq<1, NS, flux_out(STAGE)>(
+                                                 Wl, Wr, dWl, dWr, (const double*)nullptr, dW0, a.fc, dt, A, B)
+                                           : gp_flux<1, NS, flux_out(STAGE)>(Wl, Wr, dWl, dWr, a.fc, dt, A, B);
+    if (!ok && adv && (own || (f == n && first < n))) atomicAdd(a.fail, 1ull);
+    wall_fluxes<3>(a.g, 0, f, A, B);
   }
-  double A[3] = {0, 0, 0}, B[3] = {0, 0, 0};
-  const bool ok = SCHEME >= SCHEME_TENO5 ? gp_flux_eq<1, NS, flux_out(STAGE)>(
-                                               Wl, Wr, dWl, dWr, (const double*)nullptr, dW0, a.fc, dt, A, B)
-                                         : gp_flux<1, NS, flux_out(STAGE)>(Wl, Wr, dWl, dWr, a.fc, dt, A, B);
-  if (!ok) atomicAdd(a.fail, 1ull);
-  wall_fluxes<3>(a.g, 0, f, A, B);
-  const long long nf = n + 1;
+  double w1[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    a.FA[c * nf + f] = A[c];
-    if (STAGE == 1) a.FB[c * nf + f] = B[c];
+    const double Ah = lane_shift<true>(A[c]), Bh = lane_shift<true>(B[c]);
+    w1[c] = adv ? w[c] - (Ah - A[c]) * idx : w[c];
+    if (own) {
+      l.out1[(long long)c * n + f] = w1[c];
+      if (STAGE == 1) l.out2[(long long)c * n + f] = adv ? w[c] - (Bh - B[c]) * idx : w[c];
+    }
   }
+  if (CFL) block_cfl<1>(own, w1, a.gamma, l.mu, a.g.dx[0], partial);
 }
 
-template <int STAGE, bool NS, bool FLAGS, bool CHAR = false, bool EX = false, int SCHEME = SCHEME_TENO_D>
-__global__ __launch_bounds__(256) void face1d_kernel(StageArgs a) {
-  face1d_body<STAGE, NS, FLAGS, CHAR, EX, SCHEME>(a, blockIdx.x * blockDim.x + threadIdx.x);
+template <int STAGE, bool NS, bool FLAGS, bool CFL, bool CHAR = false, bool EX = false, int SCHEME = SCHEME_TENO_D>
+__global__ __launch_bounds__(256) void line_kernel(LineArgs l, double* partial) {
+  const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  line_body<STAGE, NS, FLAGS, CFL, CHAR, EX, SCHEME>(l, wave * LINE_CELLS, partial + blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1188,42 +1272,10 @@ struct UpdateArgs {
   double* partial;    // stage 2 with CFL: one minimum per block, or null
 };
 
-// minimum over the block (blockDim.x a multiple of 64, at most 1024);
-// valid in thread 0
-__device__ __forceinline__ double block_min(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  if (l == 0) red[w] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) v = fmin(v, red[i]);
-  }
-  return v;
-}
-
-// local CFL limit of one cell (Sec. 5 preamble); NaN for a non-physical state
-template <int D>
-__device__ __forceinline__ double cell_dt(const double* w, double gamma, double mu, double dxm) {
-  const double rho = w[0];
-  double ke = 0.0;
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    const double u = w[d + 1] / rho;
-    ke += u * u;
-  }
-  const double p = (gamma - 1.0) * (w[D + 1] - 0.5 * rho * ke);
-  if (!(rho > 0.0) || !(p > 0.0)) return NAN;
-  double v = dxm / (sqrt(ke) + sqrt(gamma * p / rho));
-  if (mu > 0.0) v = fmin(v, dxm * dxm * rho / (4.0 * mu));
-  return v;
-}
-
 // cell id of this thread; the block's CFL minimum goes to *partial
 template <int D, int STAGE, bool CFL>
 __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, double* partial) {
   constexpr int NC = D + 2;
-  __shared__ double red[16];  // one entry per wave, up to 1024 threads
   const Geom& g = u.g;
   const bool live = id < g.ncell;
   const double dt = *u.dt;
@@ -1264,11 +1316,7 @@ __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, d
   if (CFL) {
     double dxm = g.dx[0];
     for (int d = 1; d < D; ++d) dxm = fmin(dxm, g.dx[d]);
-    double v = live ? cell_dt<D>(w1, u.gamma, u.mu, dxm) : INFINITY;
-    // NaN (non-physical cell) wins the reduction
-    const bool nan = live && !(v == v);
-    v = block_min(nan ? -INFINITY : v, red);
-    if (threadIdx.x == 0) *partial = v == -INFINITY ? NAN : v;
+    block_cfl<D>(live, w1, u.gamma, u.mu, dxm, partial);
   }
 }
 
@@ -1278,31 +1326,26 @@ __global__ __launch_bounds__(256) void update_kernel(UpdateArgs u) {
                             CFL ? u.partial + blockIdx.x : nullptr);
 }
 
-// CFL partial minima of a state (no update)
+// CFL partial minima of a state (no update); id: the thread's cell, if live
 template <int D>
 __device__ __forceinline__ void cfl_partial_body(const Geom& g, const double* W, double gamma, double mu,
-                                                 long long id, double* partial) {
+                                                 long long id, bool live, double* partial) {
   constexpr int NC = D + 2;
-  __shared__ double red[16];  // one entry per wave, up to 1024 threads
   double dxm = g.dx[0];
   for (int d = 1; d < D; ++d) dxm = fmin(dxm, g.dx[d]);
-  double v = INFINITY;
-  bool nan = false;
-  if (id < g.ncell) {
-    double w[NC];
+  live = live && id < g.ncell;
+  double w[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) w[c] = W[(long long)c * g.ncell + id];
-    v = cell_dt<D>(w, gamma, mu, dxm);
-    nan = !(v == v);
-  }
-  v = block_min(nan ? -INFINITY : v, red);
-  if (threadIdx.x == 0) *partial = v == -INFINITY ? NAN : v;
+  for (int c = 0; c < NC; ++c) w[c] = live ? W[(long long)c * g.ncell + id] : 1.0;
+  block_cfl<D>(live, w, gamma, mu, dxm, partial);
 }
 
+// per: cells per block (one partial minimum each), at most the block's threads
 template <int D>
-__global__ __launch_bounds__(256) void cfl_partial_kernel(Geom g, const double* W, double gamma, double mu,
+__global__ __launch_bounds__(256) void cfl_partial_kernel(Geom g, const double* W, double gamma, double mu, int per,
                                                           double* partial) {
-  cfl_partial_body<D>(g, W, gamma, mu, (long long)blockIdx.x * blockDim.x + threadIdx.x, partial + blockIdx.x);
+  cfl_partial_body<D>(g, W, gamma, mu, (long long)blockIdx.x * per + threadIdx.x, (int)threadIdx.x < per,
+                      partial + blockIdx.x);
 }
 
 // Final reduction.  clock = {t, dt}.  mode 0: dt_out = cfl * min (clipped to

@@ -64,7 +64,9 @@ int64_t tgks_noalloc_need(const tgks_params* p) {
     }
     need += pad(mx * 4 * 5);
   }
-  need += pad(c.nblk) + pad(4) + pad(2);
+  // (1-D: the partial minima lie in the face arrays' region, which its step
+  // does not use)
+  need += pad((c.ncell + 255) / 256) + pad(4) + pad(2);
   return need;
 }
 
@@ -104,7 +106,7 @@ int tgks_step_noalloc(const tgks_params* p, void* hip_stream, const double* W_in
     }
     c.R = take(mx * 4 * 5);
   }
-  c.partial = take(c.nblk);
+  c.partial = c.g.D == 1 ? c.FA[0] : take(c.nblk);
   c.clock = take(4);
   c.fail = reinterpret_cast<unsigned long long*>(take(2));
   // the counters keep the last call's values: clear them (a kernel, so that

@@ -1,0 +1,116 @@
+"""The routes a step can take through the kernels, at the sizes and on the
+data where each begins and ends: 1-D grids around the cells that one wavefront
+(62) and one block (248 above 63,488 cells) own, and the smooth / general
+forms of the tangential selections, which must agree to the bit."""
+import numpy as np
+import pytest
+
+from gpu_common import GpuProblem, assert_close, orc_params, problem
+from paper_2309_10534_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    return torch
+
+
+BC1 = [("periodic", "periodic"), ("transmissive", "reflective"), ("noslip", "transmissive")]
+
+
+def field_1d(n, seed):
+    rng = np.random.default_rng(seed)
+    x = (np.arange(n) + 0.5) / n
+    rho = 1.0 + 0.2 * np.sin(2 * np.pi * x) + 0.5 * (x > 0.6) + 1e-3 * rng.normal(size=n)
+    return I.conservative(rho, [0.3 * np.cos(2 * np.pi * x)], 1.0 + 0.4 * (x < 0.3) + 0.0 * x)
+
+
+@pytest.mark.parametrize("n", [3, 4, 60, 61, 62, 63, 64, 123, 124, 125, 186, 187, 63488, 63489])
+def test_line_kernel_sizes(orc, torch_dev, n):
+    """One step with flags and three CFL steps of tgks_run against the
+    oracle, every boundary pair, and the failure counter of a state that is
+    non-physical at the last face a wavefront owns."""
+    for k, bc in enumerate(BC1 if n < 1000 else BC1[1:2]):
+        pr = problem([n], [1.0 / n], bc=[bc])
+        W = field_1d(n, 7 * n + k)
+        P = orc_params(orc, pr)
+        dt = orc.cfl_dt(P, W, 0.5)
+        Wo, fo, Wso, bado = orc.step(P, W, dt, want_flags=True, want_wstar=True)
+        print(f"[paths] 1-D n={n} bc={bc}", flush=True)
+        gp = GpuProblem(pr)
+        try:
+            Wg, Wsg, fg, badg = gp.step(W, dt)
+            Wr, td, badr = gp.run(W, 3, cfl=0.5)
+            Wc = W
+            for _ in range(3):
+                Wc = gp.step(Wc, gp.cfl_dt(Wc, 0.5), flags=False)[0]
+        finally:
+            gp.close()
+        assert badg == bado and badr == 0
+        assert np.array_equal(fg, fo), (n, bc)
+        assert_close(Wsg, Wso, 1e-10, f"W* n={n} {bc}")
+        assert_close(Wg, Wo, 1e-10, f"n={n} {bc}")
+        assert np.array_equal(Wr, Wc) and td[0] > 0
+
+
+@pytest.mark.parametrize("n,at", [(125, 61), (125, 62), (125, 124), (62, 61), (63, 62)])
+def test_line_kernel_counts_each_failure_once(orc, torch_dev, n, at):
+    """A cell of negative pressure beside a wavefront's first and last faces:
+    the faces on both sides of a boundary between wavefronts are evaluated
+    by both and counted by one."""
+    W = field_1d(n, n)
+    W[2, at] = 0.01
+    W[1, at] = 1.0
+    pr = problem([n], [1.0 / n])
+    P = orc_params(orc, pr)
+    Wo, fo, _, bado = orc.step(P, W, 1e-6, want_flags=True)
+    print(f"[paths] 1-D n={n} negative pressure at {at}", flush=True)
+    gp = GpuProblem(pr)
+    try:
+        _, _, fg, badg = gp.step(W, 1e-6)
+    finally:
+        gp.close()
+    assert badg == bado > 0
+    assert np.array_equal(fg, fo)
+
+
+def mixed(shape, level, seed):
+    """A field whose third differences reach `level` of its first ones: 0
+    constant, small values smooth, 0.1 the edge of what counts as smooth."""
+    rng = np.random.default_rng(seed)
+    D = len(shape)
+    x = np.meshgrid(*[(np.arange(n) + 0.5) / n for n in shape[::-1]], indexing="ij")
+    s = sum(np.sin(2 * np.pi * (c + 0.1 * k)) for k, c in enumerate(x)) / D
+    f = lambda a: a * (s + level * rng.normal(size=s.shape) / 30.0) if level is not None else 0.0 * s
+    rho = 1.0 + f(0.2)
+    if level is not None:
+        rho = rho + (0.7 if level > 0.5 else 0.0) * (x[-1] > 0.5)
+    return I.conservative(rho, [0.2 + f(0.1) for _ in range(D)], 1.0 + f(0.3))
+
+
+@pytest.mark.parametrize("level", [None, 0.0, 1e-6, 0.03, 0.1, 0.3, 1.0])
+@pytest.mark.parametrize("shape", [(41, 37), (64, 16), (11, 9, 13)])
+def test_smooth_and_general_selections_agree(torch_dev, shape, level):
+    """The step that records its flags takes the general form of every
+    tangential selection, the plain step the smooth one where a wavefront
+    allows it: the same bits on constant, smooth, rough and mixed data."""
+    D = len(shape)
+    W = mixed(shape, level, 5)
+    kw = dict(tau="viscous", mu=1e-3, prandtl=0.72) if level == 0.03 else {}
+    bc = [("periodic", "periodic"), ("reflective", "transmissive"), ("noslip", "periodic")][:D]
+    bc = [b if "periodic" not in b or b == ("periodic", "periodic") else ("noslip", "noslip") for b in bc]
+    pr = problem(list(shape), [1.0 / max(shape)] * D, bc=bc, **kw)
+    print(f"[paths] selections {shape} level={level}", flush=True)
+    gp = GpuProblem(pr)
+    try:
+        dt = gp.cfl_dt(W, 0.4)
+        a, sa, _, ba = gp.step(W, dt, flags=True)
+        b, sb, _, bb = gp.step(W, dt, flags=False)
+    finally:
+        gp.close()
+    assert ba == bb == 0
+    assert np.array_equal(sa, sb) and np.array_equal(a, b)
