@@ -22,6 +22,7 @@ struct tgks_batch {
   long long total = 0;           // doubles of one packed state
   long long nface[2] = {0, 0};   // doubles of the face arrays per direction
   int ncblk = 0;                 // cell blocks
+  int max_nblk = 0;              // most of one instance
   BatchInst* inst = nullptr;
   int2* wcell = nullptr;         // cell work list
   int2* wface[NTILE2][2] = {};   // 2-D face work lists per tile shape and direction
@@ -90,6 +91,9 @@ static BatchArgs batch_args(tgks_batch* b, const double* W, double* o1, double* 
     a.FB[d] = b->FB[d];
   }
   a.clock = b->clock;
+  a.prev = nullptr;
+  a.steps = b->steps;
+  a.cfl = a.t_end = 0.0;
   a.partial = b->partial;
   a.fail = b->fail;
   a.fallback = b->fb ? 1 : 0;
@@ -121,9 +125,21 @@ static void batch_face2d(tgks_batch* b, const double* W, int ax, int stage) {
 }
 
 // 1-D: one stage in one launch
-static int batch_line(tgks_batch* b, int stage, const double* W, const double* base, double* o1, double* o2) {
+// (ck: its clocks, and for stage 1 the step before's)
+struct BatchClock {
+  double* clock;
+  const double* prev;
+  double cfl, t_end;
+};
+
+static int batch_line(tgks_batch* b, int stage, const double* W, const double* base, double* o1, double* o2,
+                      const BatchClock& ck) {
   BatchArgs a = batch_args(b, W, o1, o2, b->wcell);
   a.base = base;
+  a.clock = ck.clock;
+  a.prev = stage == 1 ? ck.prev : nullptr;
+  a.cfl = ck.cfl;
+  a.t_end = ck.t_end;
 #define BF1(CH, EX)                                                                 \
   if (stage == 1) {                                                                 \
     if (b->ns) BLAUNCH((batch_line_kernel<1, true, CH, EX>), b->ncblk, 256, a);     \
@@ -179,9 +195,9 @@ static int batch_update(tgks_batch* b, int stage, const double* W, double* o1, d
   return TGKS_OK;
 }
 
-static int batch_finalize(tgks_batch* b, double cfl, double t_end, int mode) {
+static int batch_finalize(tgks_batch* b, double cfl, double t_end, int mode, double* clock) {
   hipLaunchKernelGGL(batch_finalize_kernel, dim3((unsigned)b->ninst), dim3(256), 0, b->stream, b->inst, b->partial,
-                     cfl, t_end, b->clock, b->steps, mode);
+                     cfl, t_end, clock, b->steps, mode);
   HIPCHK(hipGetLastError());
   return TGKS_OK;
 }
@@ -193,14 +209,15 @@ static int batch_cfl_start(tgks_batch* b, const double* W, double cfl, double t_
   else
     BLAUNCH((batch_cfl_partial_kernel<2>), b->ncblk, 256, a);
   HIPCHK(hipGetLastError());
-  return batch_finalize(b, cfl, t_end, 0);
+  return batch_finalize(b, cfl, t_end, 0, b->clock);
 }
 
 static int batch_step(tgks_batch* b, const double* W, double* out) {
   int r;
   if (b->D == 1) {
-    if ((r = batch_line(b, 1, W, W, b->Ws, b->P))) return r;
-    return batch_line(b, 2, b->Ws, b->P, out, nullptr);
+    const BatchClock ck{b->clock, nullptr, 0.0, 0.0};
+    if ((r = batch_line(b, 1, W, W, b->Ws, b->P, ck))) return r;
+    return batch_line(b, 2, b->Ws, b->P, out, nullptr, ck);
   }
   if ((r = batch_faces(b, W, 1))) return r;
   if ((r = batch_update(b, 1, W, b->Ws, b->P))) return r;
@@ -213,16 +230,31 @@ static int enqueue_batch_run(tgks_batch* b, double* W, int n_steps, double cfl, 
   if ((r = batch_cfl_start(b, W, cfl, t_end))) return r;
   double* src = W;
   double* dst = b->W2;
+  double* clk = b->clock;  // the clocks of the last step
+  // 1-D: a step's stage 1 takes the clocks from the step before (two sets in
+  // turn), as single grids do
+  const bool own_clock = b->D == 1 && b->max_nblk <= CLOCK_NBLK;
   for (int s = 0; s < n_steps; ++s) {
-    if ((r = batch_step(b, src, dst))) return r;
-    if ((r = batch_finalize(b, cfl, t_end, 1))) return r;
+    if (own_clock) {
+      BatchClock ck{clk, nullptr, cfl, t_end};
+      if (s > 0) {
+        ck.prev = clk;
+        clk = ck.clock = b->clock + 2 * (size_t)b->ninst * (s & 1);
+      }
+      if ((r = batch_line(b, 1, src, src, b->Ws, b->P, ck))) return r;
+      if ((r = batch_line(b, 2, b->Ws, b->P, dst, nullptr, ck))) return r;
+    } else if ((r = batch_step(b, src, dst))) {
+      return r;
+    }
+    if (!own_clock || s == n_steps - 1)
+      if ((r = batch_finalize(b, cfl, t_end, 1, clk))) return r;
     double* t = src;
     src = dst;
     dst = t;
   }
   if (src != W) HIPCHK(hipMemcpyAsync(W, src, (size_t)b->total * sizeof(double), hipMemcpyDeviceToDevice, b->stream));
   if (time_dev)
-    HIPCHK(hipMemcpyAsync(time_dev, b->clock, 2 * (size_t)b->ninst * sizeof(double), hipMemcpyDeviceToDevice,
+    HIPCHK(hipMemcpyAsync(time_dev, clk, 2 * (size_t)b->ninst * sizeof(double), hipMemcpyDeviceToDevice,
                           b->stream));
   return TGKS_OK;
 }
@@ -292,6 +324,7 @@ int tgks_batch_create(const tgks_params* p, int32_t n_inst, void* stream, tgks_b
     const int nblk = (int)((g.ncell + per - 1) / per);
     I.blk0 = blk;
     I.nblk = nblk;
+    b->max_nblk = nblk > b->max_nblk ? nblk : b->max_nblk;
     blk += nblk;
     for (int k = 0; k < nblk; ++k) wcell.push_back(make_int2(i, k));
     if (D == 2) {
@@ -320,7 +353,7 @@ int tgks_batch_create(const tgks_params* p, int32_t n_inst, void* stream, tgks_b
          hipMalloc(&b->FB[d], (size_t)b->nface[d] * sizeof(double)) == hipSuccess;
   if (ok)
     ok = hipMalloc(&b->partial, (size_t)b->ncblk * sizeof(double)) == hipSuccess &&
-         hipMalloc(&b->clock, 2 * (size_t)n_inst * sizeof(double)) == hipSuccess &&
+         hipMalloc(&b->clock, 4 * (size_t)n_inst * sizeof(double)) == hipSuccess &&
          hipMalloc(&b->steps, (size_t)n_inst * sizeof(long long)) == hipSuccess &&
          hipMalloc(&b->fail, (size_t)n_inst * sizeof(unsigned long long)) == hipSuccess;
   if (ok) ok = upload(&b->wcell, wcell);

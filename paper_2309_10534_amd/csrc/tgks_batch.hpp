@@ -34,6 +34,9 @@ struct BatchArgs {
   double* FA[2];
   double* FB[2];
   double* clock;     // [instance][t, dt]
+  const double* prev;  // 1-D stage 1: the clocks of the step before (null: clock holds this step's already)
+  long long* steps;  // steps taken per instance
+  double cfl, t_end;
   double* partial;   // per cell block
   unsigned long long* fail;  // per instance
   // first-order fallback, the same for every instance; a run-time value so
@@ -79,19 +82,9 @@ __global__ __launch_bounds__(256) void batch_line_kernel(BatchArgs b) {
   l.out2 = STAGE == 1 ? b.out2 + I.woff : nullptr;
   l.mu = I.mu;
   l.idx = 1.0 / I.g.dx[0];
-  if (!(*l.s.dt > 0.0)) {
-    // the instance has stopped: its state stays, without the fluxes
-    const int c = w.y * BATCH_LINE + (int)threadIdx.x;
-    const bool live = (int)threadIdx.x < BATCH_LINE && c < I.g.n[0];
-    double v[3] = {1.0, 0.0, 1.0};
-    for (int q = 0; live && q < 3; ++q) {
-      v[q] = l.base[(long long)q * I.g.n[0] + c];
-      l.out1[(long long)q * I.g.n[0] + c] = v[q];
-      if (STAGE == 1) l.out2[(long long)q * I.g.n[0] + c] = v[q];
-    }
-    if (STAGE == 2) block_cfl<1>(live, v, I.gamma, I.mu, I.g.dx[0], b.partial + I.blk0 + w.y);
-    return;
-  }
+  // (an instance's clock, partial minima and step count)
+  l.ck = StepClock{b.prev ? b.prev + 2 * w.x : nullptr, b.clock + 2 * w.x, b.partial + I.blk0, b.steps + w.x, I.nblk,
+                   b.cfl, b.t_end};
   line_body<STAGE, NS, false, STAGE == 2, CHAR, EX>(l, (w.y * 4 + (int)(threadIdx.x >> 6)) * LINE_CELLS,
                                                      b.partial + I.blk0 + w.y);
 }

@@ -13,9 +13,10 @@ using namespace tgks;
 
 // one stage of a 1-D step
 int launch_line(tgks_ctx* c, int stage, const double* W, const double* base, double* o1, double* o2, const double* dt,
-                uint8_t* flags, bool cfl) {
+                uint8_t* flags, bool cfl, const StepClock* ck) {
   const bool fl = flags != nullptr && stage == 1;
-  LineArgs l;
+  LineArgs l{};
+  if (ck) l.ck = *ck;
   l.s = stage_args(c, W, 0, dt);
   if (fl) l.s.nflags = flags;
   l.base = base;
@@ -192,6 +193,29 @@ static int launch_finalize(tgks_ctx* c, double cfl, double t_in, double t_end, d
   Timer tm(c, 6);
   hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(256), 0, c->stream, c->partial, c->nblk, cfl, t_in, t_end,
                      clock, dt_out, mode);
+  HIPCHK(hipGetLastError());
+  return TGKS_OK;
+}
+
+// the CFL step of a state: to clock = {t_in, dt} and dt_out (either may be null)
+static int launch_cfl(tgks_ctx* c, const double* W, double cfl, double t_in, double t_end, double* clock,
+                      double* dt_out) {
+  if (c->ncell > CFL_ONE) {
+    const int r = launch_cfl_partial(c, W);
+    return r ? r : launch_finalize(c, cfl, t_in, t_end, clock, dt_out, 0);
+  }
+  Timer tm(c, 6);
+  const dim3 blk((unsigned)(c->ncell > 512 ? 1024 : c->ncell > 256 ? 512 : 256));
+#define CFL1(DV)                                                                                              \
+  hipLaunchKernelGGL((cfl_one_kernel<DV>), dim3(1), blk, 0, c->stream, c->g, W, c->p.gamma, c->p.mu, cfl, t_in, \
+                     t_end, clock, dt_out)
+  if (c->g.D == 1)
+    CFL1(1);
+  else if (c->g.D == 2)
+    CFL1(2);
+  else
+    CFL1(3);
+#undef CFL1
   HIPCHK(hipGetLastError());
   return TGKS_OK;
 }
@@ -392,9 +416,7 @@ int64_t tgks_flag_bytes(const tgks_ctx* c) {
 
 int tgks_cfl_dt(tgks_ctx* c, const double* W, double cfl, double t, double t_end, double* dt_dev) {
   if (!c || !W || !dt_dev || !(cfl > 0.0)) return TGKS_EINVAL;
-  int r;
-  if ((r = launch_cfl_partial(c, W))) return r;
-  return launch_finalize(c, cfl, t, t_end, nullptr, dt_dev, 0);
+  return launch_cfl(c, W, cfl, t, t_end, nullptr, dt_dev);
 }
 
 int tgks_step(tgks_ctx* c, const double* W_in, double* W_out, const double* dt_dev, uint8_t* flags,
@@ -413,18 +435,33 @@ static int enqueue_run(tgks_ctx* c, double* W, int n_steps, double cfl, double t
   int r = 0;
   const bool use_cfl = cfl > 0.0;
   if (use_cfl) {
-    if ((r = launch_cfl_partial(c, W))) return r;
-    if ((r = launch_finalize(c, cfl, 0.0, t_end, c->clock, nullptr, 0))) return r;
+    if ((r = launch_cfl(c, W, cfl, 0.0, t_end, c->clock, nullptr))) return r;
   } else {
     hipLaunchKernelGGL(set_clock_kernel, dim3(1), dim3(1), 0, c->stream, c->clock, 0.0, fixed_dt);
     HIPCHK(hipGetLastError());
   }
   double* src = W;
   double* dst = c->W2;
-  c->tclk = c->clock;  // the state of each step is that of time t0 + clock[0]
+  double* clk = c->clock;  // the clock of the last step
+  // 1-D: a step's stage 1 takes the clock from the step before (two clocks in
+  // turn), as long as its wavefronts read the partial minima in a few loads
+  const bool own_clock = c->g.D == 1 && c->nblk <= CLOCK_NBLK;
   for (int s = 0; s < n_steps; ++s) {
-    if ((r = do_step(c, src, dst, c->clock + 1, nullptr, use_cfl))) break;
-    if ((r = launch_finalize(c, cfl, 0.0, t_end, c->clock, nullptr, use_cfl ? 1 : 2))) break;
+    if (own_clock) {
+      StepClock ck{nullptr, nullptr, c->partial, nullptr, c->nblk, use_cfl ? cfl : 0.0, t_end};
+      if (s > 0) {
+        ck.prev = clk;
+        clk = ck.next = c->clock + 2 * (s & 1);
+      }
+      c->tclk = clk;  // the state of each step is that of time t0 + clk[0]
+      if ((r = launch_line(c, 1, src, src, c->Ws, c->P, clk + 1, nullptr, false, &ck))) break;
+      if ((r = launch_line(c, 2, c->Ws, c->P, dst, nullptr, clk + 1, nullptr, use_cfl))) break;
+    } else {
+      c->tclk = clk;
+      if ((r = do_step(c, src, dst, clk + 1, nullptr, use_cfl))) break;
+    }
+    if (!own_clock || s == n_steps - 1)
+      if ((r = launch_finalize(c, cfl, 0.0, t_end, clk, nullptr, use_cfl ? 1 : 2))) break;
     double* t = src;
     src = dst;
     dst = t;
@@ -434,7 +471,7 @@ static int enqueue_run(tgks_ctx* c, double* W, int n_steps, double cfl, double t
   if (src != W)
     HIPCHK(hipMemcpyAsync(W, src, (size_t)c->nc * c->ncell * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   if (time_dev)
-    HIPCHK(hipMemcpyAsync(time_dev, c->clock, 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(time_dev, clk, 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   return TGKS_OK;
 }
 
@@ -614,8 +651,7 @@ int tgks_tune(tgks_ctx* c, const double* W, int32_t steps, int32_t* chosen, floa
   const int nvar = c->g.D == 2 ? NTILE2 : 1;
   int r;
   // dt of W into the clock (no clipping)
-  if ((r = launch_cfl_partial(c, W))) return r;
-  if ((r = launch_finalize(c, 0.5, 0.0, 0.0, c->clock, nullptr, 0))) return r;
+  if ((r = launch_cfl(c, W, 0.5, 0.0, 0.0, c->clock, nullptr))) return r;
   const bool timing = c->timing;
   c->timing = false;
   hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -429,6 +429,18 @@ TGKS_HD void teno_face(const R* Q, unsigned flag, R* out) {
   out[3] = (o0 * dp0 + o1 * dp12) + o2 * dp12;
 }
 
+// teno_face with both kinds evaluated and one selected, to the same bits: one
+// straight line for a kernel whose few wavefronts wait for their own results
+// (several cells' values can then be evaluated in turn).
+template <class R>
+TGKS_HD void teno_face_both(const R* Q, const TenoSel& s, R* out) {
+  R lg[4], sm[4];
+  teno_face(Q, 1u, lg);
+  teno_face(Q, (s.k0 ? 2u : 0u) | (s.k1 ? 4u : 0u) | (s.k2 ? 8u : 0u), sm);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) out[k] = s.lg ? lg[k] : sm[k];
+}
+
 // The selected polynomial at the Gauss points +-s, s = 1/(2 sqrt 3) (cell
 // units): p(+-s) = base +- odd, p'(+-s) = ev +- od.
 //
@@ -1041,6 +1053,15 @@ TGKS_HD R opaque(R x) {
 TGKS_HD double opaque(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" : "+v"(x));
+#endif
+  return x;
+}
+
+// ... which may be moved or dropped like any other value: code after it is
+// compiled from the value alone, not from how it was made
+TGKS_HD double sealed(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(x));
 #endif
   return x;
 }

@@ -216,7 +216,7 @@ int launch_scheme_faces(tgks_ctx* c, const StageArgs* a, int stage, bool fl);
 // = P (stage 1); W: the state the fluxes are computed from, base: what they
 // are subtracted from
 int launch_line(tgks_ctx* c, int stage, const double* W, const double* base, double* o1, double* o2, const double* dt,
-                uint8_t* flags, bool cfl);
+                uint8_t* flags, bool cfl, const StepClock* ck = nullptr);
 template <int SCHEME>
 int launch_scheme_line(tgks_ctx* c, const LineArgs& l, int stage, bool fl, bool cfl);
 

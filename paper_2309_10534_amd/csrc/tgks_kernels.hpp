@@ -112,13 +112,18 @@ __device__ __forceinline__ double load_cell(const Geom& g, const double* W, int 
   return cell_flip(g, c, f0, f1, f2) ? -v : v;
 }
 
+// stage 2 works on W*, the state at the half step
+__device__ __forceinline__ double stage2_time(double t, double dt) {
+#pragma clang fp contract(off)
+  return t + 0.5 * dt;
+}
+
 // time of the prescribed states in stage STAGE of a step of length dt
-// (stage 2 works on W*, the state at the half step)
 __device__ __forceinline__ double boundary_time(const StageArgs& a, int stage, double dt) {
 #pragma clang fp contract(off)
   if (!a.pb.on) return 0.0;
   const double t = a.t0 + (a.tclk ? *a.tclk : 0.0);
-  return stage == 2 ? t + 0.5 * dt : t;
+  return stage == 2 ? stage2_time(t, dt) : t;
 }
 
 // load_cell with prescribed sides resolved first (x side, then y side): the
@@ -258,11 +263,34 @@ __device__ __forceinline__ void wall_fluxes(const Geom& g, int ax, int f, double
 // ---------------------------------------------------------------------------
 // CFL time step (Sec. 5 preamble).
 // ---------------------------------------------------------------------------
+// value of another lane of the row by a DPP control, and of lane k
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int k) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                          __builtin_amdgcn_readlane(__double2loint(v), k));
+}
+
+// minimum over the wavefront (all lanes active, no NaN), in every lane: the
+// rows of sixteen lanes by DPP moves, then the four rows (six steps through
+// the LDS lane shuffle took 800 cycles of a small grid's kernel)
+__device__ __forceinline__ double wave_min(double v) {
+  v = fmin(v, dpp_move<0xB1>(v));   // quad: lane ^ 1
+  v = fmin(v, dpp_move<0x4E>(v));   // quad: lane ^ 2
+  v = fmin(v, dpp_move<0x141>(v));  // half row mirrored
+  v = fmin(v, dpp_move<0x140>(v));  // row mirrored
+  return fmin(fmin(lane_value(v, 0), lane_value(v, 16)), fmin(lane_value(v, 32), lane_value(v, 48)));
+}
+
 // minimum over the block (blockDim.x a multiple of 64, at most 1024);
 // valid in thread 0
 __device__ __forceinline__ double block_min(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
+  v = wave_min(v);
+  if (blockDim.x == 64) return v;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   if (l == 0) red[w] = v;
   __syncthreads();
@@ -301,20 +329,73 @@ __device__ __forceinline__ void block_cfl(bool live, const double* w, double gam
   if (threadIdx.x == 0) *partial = v == -INFINITY ? NAN : v;
 }
 
+// the time step after the minimum v of the cells' limits (-inf: a
+// non-physical cell), clipped to t_end - t
+__device__ __forceinline__ double next_dt(double v, double cfl, double t, double t_end) {
+#pragma clang fp contract(off)
+  double dt = v == -INFINITY ? NAN : cfl * v;
+  if (t_end > 0.0) {
+    if (t >= t_end * (1.0 - 1e-14))
+      dt = 0.0;
+    else if (t + dt > t_end)
+      dt = t_end - t;
+  }
+  return dt;
+}
+
+// The clock {t, dt} of a step taken from the step before: t += dt, the new dt
+// from the partial minima that its stage 2 left (cfl > 0; else the same dt).
+// Every wavefront of the new step's stage 1 evaluates it for itself (few
+// partial minima) and the grid's first writes it down, in another place than
+// the old one: no kernel of its own between the steps.
+constexpr int CLOCK_NBLK = 256;  // partial minima: at most four loads per lane
+
+struct StepClock {
+  const double* prev;     // the clock of the step before; null: none, dt is given
+  double* next;
+  const double* partial;
+  long long* steps;       // counts the steps taken (null: not counted)
+  int nblk;
+  double cfl, t_end;
+};
+
+__device__ __forceinline__ void step_clock(const StepClock& k, bool write, double& t, double& dt) {
+  double v = INFINITY;
+  bool nan = false;
+  if (k.cfl > 0.0)
+    for (int i = threadIdx.x & 63; i < k.nblk; i += 64) {
+      const double p = k.partial[i];
+      nan = nan || !(p == p);
+      v = fmin(v, p);
+    }
+  t = k.prev[0];
+  const double used = k.prev[1];
+  if (used > 0.0) t += used;
+  dt = k.cfl > 0.0 ? next_dt(wave_min(nan ? -INFINITY : v), k.cfl, t, k.t_end) : used;
+  t = lane_value(t, 0);  // in scalar registers, as a clock that is loaded
+  dt = lane_value(dt, 0);
+  if (write && (threadIdx.x & 63) == 0) {
+    k.next[0] = t;
+    k.next[1] = dt;
+    if (k.steps && used > 0.0) *k.steps += 1;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // 1-D: one stage of a step in one kernel, faces and update together.  A
-// wavefront owns LINE_CELLS = 62 consecutive cells: lane i reconstructs cell
-// c = first - 1 + i and evaluates the flux of the face below it, the left
-// state and then the upper face's flux coming from the neighbouring lanes, so
-// that lanes 1..62 update their cells without a face array between two
-// launches.  What bounds a single small grid is latency: the chain of
-// dependent loads at the start of each kernel and of one lane's arithmetic
-// (half of a face launch's 10 us were waits for memory).  Three selections
-// per lane instead of six, two launches per step fewer, every load issued
-// before the first wait: 50 steps of 400 cells 0.82 ms (1.42 with a face and
-// an update kernel per stage), 10 steps of 128 uneven tubes 98 us (168).
+// wavefront owns LINE_CELLS = 58 consecutive cells: lane i loads cell c =
+// first - 3 + i (ghost cells by the index map), takes its neighbours' values
+// from the lanes beside it, reconstructs its cell and evaluates the flux of
+// the face below it, with the left state from the lane below; lanes 3..60 then
+// update their cells with the upper face's flux from the lane above.  What
+// bounds a single small grid is latency: dependent loads and one lane's chain
+// of arithmetic.  Hence one cell's loads and index map per lane, the three
+// selections and both kinds of face values as one straight line of code, and
+// every load issued before the first wait.  50 steps of 400 cells: 0.74 ms
+// (0.82 with all six cells loaded by each lane, the selections in turn and a
+// clock kernel between the steps; 1.42 with separate face and update kernels).
 // ---------------------------------------------------------------------------
-constexpr int LINE_CELLS = 62;
+constexpr int LINE_CELLS = 58;
 
 struct LineArgs {
   StageArgs s;
@@ -322,6 +403,7 @@ struct LineArgs {
   double* out1;        // stage 1: W*; stage 2: W^{n+1}
   double* out2;        // stage 1: P
   double mu, idx;      // viscosity; 1 / dx
+  StepClock ck;        // stage 1: the step's clock from the step before (or dt given by s.dt)
 };
 
 // value of the lane below (UP = false) or above (UP = true)
@@ -343,78 +425,124 @@ template <int STAGE, bool NS, bool FLAGS, bool CFL, bool CHAR = false, bool EX =
 __device__ __forceinline__ void line_body(const LineArgs& l, int first, double* partial) {
   const StageArgs& a = l.s;
   const int n = a.g.n[0], i = threadIdx.x & 63;
-  const int f = first - 1 + i;  // the lane's cell and the face below it
-  const bool own = i >= 1 && i <= LINE_CELLS && f < n;  // the lane updates its cell
-  const bool face = i >= 1 && f <= n;
+  const int f = first - 3 + i;  // the lane's cell and the face below it
+  const bool own = i >= 3 && i < 3 + LINE_CELLS && f < n;  // the lane updates its cell
+  const bool face = i >= 3 && i <= 3 + LINE_CELLS && f <= n;
+  const bool counts = own || (face && f == n && first < n);  // (a face between two wavefronts: the upper one)
   // the constants, loaded together before the first wait (one latency of the
   // scalar cache instead of one where each group is used)
   asm volatile("" ::"s"(l.idx), "s"(a.g.bclo[0]), "s"(a.g.bchi[0]), "s"(a.fc.N), "s"(a.fc.mu), "s"(a.fc.c1),
                "s"(a.fc.c2), "s"(a.fc.tau_mode), "s"(a.tn.fast), "s"(a.tn.eps4), "s"(a.tn.ct1_up), "s"(a.tn.ct1_dn),
                "s"(a.tn.ct2_up), "s"(a.tn.ct2_dn), "s"(a.W), "s"(a.dt), "s"(l.base), "s"(l.out1));
-  const double dt = *a.dt;
-  const double tb = EX ? boundary_time(a, STAGE, dt) : 0.0;
-  // the cells f-3 .. f+2 around the face (the lane's own: C[3])
-  double C[6][3], w[3];
-#pragma unroll
-  for (int r = 0; r < 6; ++r)
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      C[r][c] = EX ? cell_value(a.g, a.pb, a.W, c, f - 3 + r, 0, tb) : load_cell(a.g, a.W, c, f - 3 + r, 0, 0);
+  double C[6][3], w[3];  // cells f-3 .. f+2 (the lane's own: C[3])
   const int fc = f < 0 ? 0 : (f >= n ? n - 1 : f);
+  if (!EX)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) C[3][c] = load_cell(a.g, a.W, c, f, 0, 0);
 #pragma unroll
   for (int c = 0; c < 3; ++c) w[c] = l.base[(long long)c * n + fc];
+  double dt, t = 0.0;
+  if (STAGE == 1 && l.ck.prev) {
+    step_clock(l.ck, first == 0, t, dt);
+    t += a.t0;
+  } else {
+    dt = *a.dt;
+    if (EX && a.pb.on) t = a.t0 + (a.tclk ? *a.tclk : 0.0);
+  }
+  if (EX) {
+    const double tb = STAGE == 2 ? stage2_time(t, dt) : t;  // of the prescribed states
+#pragma unroll
+    for (int c = 0; c < 3; ++c) C[3][c] = cell_value(a.g, a.pb, a.W, c, f, 0, tb);
+  }
+  if (!(dt > 0.0)) {
+    // at the end time: the state stays, without the fluxes
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (own) {
+        l.out1[(long long)c * n + f] = w[c];
+        if (STAGE == 1) l.out2[(long long)c * n + f] = w[c];
+      }
+    if (CFL) block_cfl<1>(own, w, a.gamma, l.mu, a.g.dx[0], partial);
+    return;
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    C[4][c] = lane_shift<true>(C[3][c]);
+    C[5][c] = lane_shift<true>(C[4][c]);
+    C[2][c] = lane_shift<false>(C[3][c]);
+    C[1][c] = lane_shift<false>(C[2][c]);
+    C[0][c] = lane_shift<false>(C[1][c]);
+  }
   double A[3] = {0, 0, 0}, B[3] = {0, 0, 0};
-  const bool adv = dt > 0.0;
   double Wl[3], Wr[3], dWl[1][3], dWr[1][3], dW0[1][3];
   const double idx = l.idx;  // normal slopes per unit length
   if (CHAR) {
     unsigned fr[3];
     char_recon_face<1>(a.gamma, C, a.tn, idx, Wl, dWl[0], Wr, dWr[0], fr);
-    if (FLAGS && own && adv)
+    if (FLAGS && own)
 #pragma unroll
       for (int k = 0; k < 3; ++k) a.nflags[(long long)k * n + f] = (uint8_t)fr[k];
   } else {
+    double Q[3][5];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int r = 0; r < 5; ++r) Q[c][r] = C[1 + r][c];
+    TenoSel sel[3];
+    if (SCHEME == SCHEME_TENO_D) {
+      bool sure = (a.tn.fast & TENO_FILTER_OK) != 0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        TenoParts<double> p;
+        teno_parts(Q[c], p);
+        sure &= teno_certain<SEL_FILTER>(Q[c], p, a.tn, sel[c]);
+      }
+      if (!sure) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) sel[c] = teno_sel(teno_exact_cold(Q[c], a.tn));
+      }
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const double Q[5] = {C[1][c], C[2][c], C[3][c], C[4][c], C[5][c]};
       double o[4];
       unsigned fl;
       if (SCHEME == SCHEME_TENO_D) {
-        fl = teno_flag<SEL_FILTER, true>(Q, a.tn);
-        teno_face(Q, fl, o);
+        teno_face_both(Q[c], sel[c], o);
+        fl = sel[c].flag();
       } else {
-        fl = scheme_face<SCHEME>(Q, a.sc, o);
+        fl = scheme_face<SCHEME>(Q[c], a.sc, o);
         // separately reconstructed equilibrium slope (Eq. 3.12)
-        if (SCHEME >= SCHEME_TENO5) dW0[0][c] = eq_slope(C[1][c], C[2][c], C[3][c], C[4][c]) * idx;
+        if (SCHEME >= SCHEME_TENO5) dW0[0][c] = sealed(eq_slope(C[1][c], C[2][c], C[3][c], C[4][c]) * idx);
       }
-      Wr[c] = o[0];
-      dWr[0][c] = o[1] * idx;
-      Wl[c] = lane_shift<false>(o[2]);
-      dWl[0][c] = lane_shift<false>(o[3] * idx);
-      if (FLAGS && own && adv) a.nflags[(long long)c * n + f] = (uint8_t)fl;
+      // (sealed: the flux of every variant of the kernel is compiled from the
+      // same inputs, hence with the same contractions and to the same bits)
+      Wr[c] = sealed(o[0]);
+      dWr[0][c] = sealed(o[1] * idx);
+      Wl[c] = sealed(lane_shift<false>(o[2]));
+      dWl[0][c] = sealed(lane_shift<false>(o[3] * idx));
+      if (FLAGS && own) a.nflags[(long long)c * n + f] = (uint8_t)fl;
     }
   }
   if (face) {
     if (EX && a.fallback) {
       const int nfb =
           fallback_side<3, 1>(Wl, dWl, C[2], a.gamma) + fallback_side<3, 1>(Wr, dWr, C[3], a.gamma);
-      // (the wavefront's last face is the next one's first: counted there)
-      if (nfb && adv && a.fbc && (own || (f == n && first < n))) atomicAdd(a.fbc, (unsigned long long)nfb);
+      if (nfb && a.fbc && counts) atomicAdd(a.fbc, (unsigned long long)nfb);
     }
     const bool ok = SCHEME >= SCHEME_TENO5 ? gp_flux_eq<1, NS, flux_out(STAGE)>(
                                                  Wl, Wr, dWl, dWr, (const double*)nullptr, dW0, a.fc, dt, A, B)
                                            : gp_flux<1, NS, flux_out(STAGE)>(Wl, Wr, dWl, dWr, a.fc, dt, A, B);
-    if (!ok && adv && (own || (f == n && first < n))) atomicAdd(a.fail, 1ull);
+    if (!ok && counts) atomicAdd(a.fail, 1ull);
     wall_fluxes<3>(a.g, 0, f, A, B);
   }
   double w1[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const double Ah = lane_shift<true>(A[c]), Bh = lane_shift<true>(B[c]);
-    w1[c] = adv ? w[c] - (Ah - A[c]) * idx : w[c];
+    w1[c] = w[c] - (Ah - A[c]) * idx;
     if (own) {
       l.out1[(long long)c * n + f] = w1[c];
-      if (STAGE == 1) l.out2[(long long)c * n + f] = adv ? w[c] - (Bh - B[c]) * idx : w[c];
+      if (STAGE == 1) l.out2[(long long)c * n + f] = w[c] - (Bh - B[c]) * idx;
     }
   }
   if (CFL) block_cfl<1>(own, w1, a.gamma, l.mu, a.g.dx[0], partial);
@@ -1372,16 +1500,43 @@ __device__ __forceinline__ void finalize_body(const double* partial, int nblk, d
     }
     if (clock) clock[0] = t;
     if (mode != 2) {
-      double dt = v == -INFINITY ? NAN : cfl * v;
-      if (t_end > 0.0) {
-        if (t >= t_end * (1.0 - 1e-14))
-          dt = 0.0;
-        else if (t + dt > t_end)
-          dt = t_end - t;
-      }
+      const double dt = next_dt(v, cfl, t, t_end);
       if (clock) clock[1] = dt;
       if (dt_out) *dt_out = dt;
     }
+  }
+}
+
+// the whole CFL step of a small state in one block, at most sixteen cells per
+// thread: one launch instead of two (time step and step of 100 cells: 15 us,
+// 18 with two)
+constexpr int CFL_ONE = 16384;
+
+template <int D>
+__global__ __launch_bounds__(1024) void cfl_one_kernel(Geom g, const double* W, double gamma, double mu, double cfl,
+                                                       double t_in, double t_end, double* clock, double* dt_out) {
+  constexpr int NC = D + 2;
+  __shared__ double red[16];  // one entry per wave
+  double dxm = g.dx[0];
+  for (int d = 1; d < D; ++d) dxm = fmin(dxm, g.dx[d]);
+  double v = INFINITY;
+  bool nan = false;
+  for (int id = threadIdx.x; id < (int)g.ncell; id += blockDim.x) {
+    double w[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) w[c] = W[(long long)c * g.ncell + id];
+    const double x = cell_dt<D>(w, gamma, mu, dxm);
+    nan = nan || !(x == x);
+    v = fmin(v, x);
+  }
+  v = block_min(nan ? -INFINITY : v, red);
+  if (threadIdx.x == 0) {
+    const double dt = next_dt(v, cfl, t_in, t_end);
+    if (clock) {
+      clock[0] = t_in;
+      clock[1] = dt;
+    }
+    if (dt_out) *dt_out = dt;
   }
 }
 

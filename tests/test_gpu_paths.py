@@ -1,7 +1,9 @@
 """The routes a step can take through the kernels, at the sizes and on the
 data where each begins and ends: 1-D grids around the cells that one wavefront
-(62) and one block (248 above 63,488 cells) own, and the smooth / general
-forms of the tangential selections, which must agree to the bit."""
+(58) and one block (232 above 59,392 cells) own, the steps that take their
+clock from the step before (up to 256 partial minima), the time step of small
+grids in one block (up to 16,384 cells), and the smooth / general forms of the
+tangential selections, which must agree to the bit."""
 import numpy as np
 import pytest
 
@@ -29,7 +31,8 @@ def field_1d(n, seed):
     return I.conservative(rho, [0.3 * np.cos(2 * np.pi * x)], 1.0 + 0.4 * (x < 0.3) + 0.0 * x)
 
 
-@pytest.mark.parametrize("n", [3, 4, 60, 61, 62, 63, 64, 123, 124, 125, 186, 187, 63488, 63489])
+@pytest.mark.parametrize("n", [3, 4, 57, 58, 59, 60, 61, 62, 63, 64, 115, 116, 117, 123, 124, 125, 174, 175, 186, 187,
+                               14848, 14849, 16384, 16385, 59392, 59393, 63488, 63489])
 def test_line_kernel_sizes(orc, torch_dev, n):
     """One step with flags and three CFL steps of tgks_run against the
     oracle, every boundary pair, and the failure counter of a state that is
@@ -57,7 +60,47 @@ def test_line_kernel_sizes(orc, torch_dev, n):
         assert np.array_equal(Wr, Wc) and td[0] > 0
 
 
-@pytest.mark.parametrize("n,at", [(125, 61), (125, 62), (125, 124), (62, 61), (63, 62)])
+@pytest.mark.parametrize("t_end", [0.0, 0.02])
+@pytest.mark.parametrize("sizes", [[57, 231, 232, 233, 465], [40, 59392], [40, 59393]])
+def test_batch_clocks_between_steps(torch_dev, sizes, t_end):
+    """Batches of grids around a block's 232 cells and the 256 partial minima
+    up to which a step takes its clock from the step before: states, times,
+    time steps and step counts of single runs, to the bit, eager and captured,
+    with instances that stop at t_end after different numbers of steps."""
+    from paper_2309_10534_amd import tgks
+    from gpu_common import gpu_params
+    torch, steps = torch_dev, 7
+    probs = [(field_1d(n, n), problem([n], [1.0 / min(n, 500)], bc=[BC1[k % 3]])) for k, n in enumerate(sizes)]
+    ref = []
+    for W, pr in probs:
+        gp = GpuProblem(pr)
+        try:
+            ref.append(gp.run(W, steps, cfl=0.5, t_end=t_end))
+        finally:
+            gp.close()
+    b = tgks.tgks_batch_create([gpu_params(pr) for _, pr in probs])
+    try:
+        off = tgks.tgks_batch_offsets(b)
+        W0 = torch.from_numpy(tgks.pack([W for W, _ in probs])).cuda()
+        td = torch.zeros(2 * len(sizes), dtype=torch.float64, device="cuda")
+        for graph in (False, True, True):
+            W = W0.clone()
+            tgks.tgks_batch_run(b, W, steps, 0.5, t_end, td, graph)
+            torch.cuda.synchronize()
+            out = tgks.unpack(W.cpu().numpy(), off, [w.shape for w, _ in probs])
+            clock = td.cpu().numpy().reshape(-1, 2)
+            count = tgks.tgks_batch_steps(b)
+            for k, (Wr, tr, bad) in enumerate(ref):
+                assert bad == 0 and np.array_equal(out[k], Wr), (sizes[k], graph)
+                assert np.array_equal(clock[k], tr), (sizes[k], graph)
+                assert count[k] == (steps if tr[1] > 0.0 else count[k]) <= steps
+                assert t_end == 0.0 or tr[1] > 0.0 or abs(clock[k][0] - t_end) < 1e-13
+    finally:
+        tgks.tgks_batch_destroy(b)
+
+
+@pytest.mark.parametrize("n,at", [(125, 57), (125, 58), (125, 61), (125, 62), (125, 124), (58, 57), (59, 58),
+                                  (62, 61), (63, 62)])
 def test_line_kernel_counts_each_failure_once(orc, torch_dev, n, at):
     """A cell of negative pressure beside a wavefront's first and last faces:
     the faces on both sides of a boundary between wavefronts are evaluated
