@@ -327,7 +327,7 @@ void init_ctx_host(tgks_ctx* c, const tgks_params* p, void* stream) {
   c->fc.tau_mode = p->tau_mode;
   c->tn = teno_cfg(p->ct1, p->ct2, p->eps, p->q);
   c->tt = teno_cfg(p->ct1_tan, p->ct2_tan, p->eps, p->q);
-  c->sc = {p->ct1, p->eps, p->q, p->d_hi, p->d_lo, p->eps_w};
+  c->sc = scheme_cfg(p->ct1, p->eps, p->q, p->d_hi, p->d_lo, p->eps_w);
   for (int d = 0; d < 3; ++d) {
     long long nf = 1;
     for (int e = 0; e < 3; ++e) nf *= (long long)(g.n[e] + (e == d));

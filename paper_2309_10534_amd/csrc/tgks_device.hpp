@@ -587,9 +587,15 @@ constexpr int SCHEME_TENO_D = 0, SCHEME_WENO_AO = 1, SCHEME_TENO5 = 2, SCHEME_WE
 struct SchemeCfg {
   double ct, eps;      // TENO5 cut-off C_T and epsilon
   int q;               // TENO5 power
-  double d_hi, d_lo;   // WENO-AO linear weights
+  double d[3];         // WENO-AO linear weights of p0 (and p2), p1 and p3
+  double r[3];         // their ratios to that of p3; of p3: 1 / d3
   double eps_w;        // WENO-AO / WENO-Z epsilon
 };
+
+inline SchemeCfg scheme_cfg(double ct, double eps, int q, double dh, double dl, double eps_w) {
+  const double d0 = (1.0 - dh) * (1.0 - dl) / 2.0, d1 = (1.0 - dh) * dl;
+  return SchemeCfg{ct, eps, q, {d0, d1, dh}, {d0 / dh, d1 / dh, 1.0 / dh}, eps_w};
+}
 
 // Jiang-Shu indicators of p0..p2 and Balsara's form for p3 (the same
 // arithmetic as teno_flag's)
@@ -616,6 +622,16 @@ TGKS_HD void indicators(const R* Q, R* beta) {
   const R s2 = P2 + (123.0 / 455.0) * P4;
   beta[3] = (((s1 * s1) + (13.0 / 3.0) * (s2 * s2)) + (781.0 / 20.0) * (P3 * P3)) +
             (1421461.0 / 2275.0) * (P4 * P4);
+}
+
+// the same of p0..p2 alone, from the shared differences
+template <class R>
+TGKS_HD void small_indicators(const TenoParts<R>& p, R* beta) {
+#pragma clang fp contract(off)
+  const double k13 = 13.0 / 12.0;
+  const R l[3] = {p.l0, p.x, p.l2};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) beta[k] = fma_(R(0.25), l[k] * l[k], k13 * (p.t[k] * p.t[k]));
 }
 
 // TENO5 cut-offs: bit k = delta_k (Eqs. 4.1-4.3)
@@ -646,65 +662,118 @@ TGKS_HD unsigned teno5_flags(const R* beta, const SchemeCfg& c) {
   return f;
 }
 
-// linear weights of p0..p2 at x_{i-1/2} (where 0), x_{i+1/2} (1), the Gauss
-// points -1/(2 sqrt 3) (2) and +1/(2 sqrt 3) (3)
-TGKS_HD void lin_weights(int where, double* d) {
-  const double gw = 1.7320508075688772 / 1080.0;
-  if (where == 0) {
-    d[0] = 0.3; d[1] = 0.6; d[2] = 0.1;
-  } else if (where == 1) {
-    d[0] = 0.1; d[1] = 0.6; d[2] = 0.3;
-  } else if (where == 2) {
-    d[0] = 7.0 / 36.0 + gw; d[1] = 11.0 / 18.0; d[2] = 7.0 / 36.0 - gw;
+// ... as a function of its own, the rare path of teno5_select
+__host__ __device__ __attribute__((noinline)) inline unsigned teno5_flags_cold(double b0, double b1, double b2,
+                                                                               double ct, double eps, int q) {
+  const double beta[3] = {b0, b1, b2};
+  SchemeCfg c{};
+  c.ct = ct;
+  c.eps = eps;
+  c.q = q;
+  return teno5_flags(beta, c);
+}
+
+// The cut-offs by estimated reciprocals: each ratio is right to 2^-45, its
+// q-th power (q <= 1024) to 2^-34, so a power outside the cut-off by 2^-30 on
+// either side is decided; what is not (also where a power overflows, an
+// indicator is huge or anything is NaN) takes the exact quotients.  Three
+// estimates for three divisions: half of the selection's operations.
+template <class R>
+TGKS_HD unsigned teno5_select(const R* beta, const SchemeCfg& c) {
+  if constexpr (std::is_same_v<R, double>) {
+#pragma clang fp contract(off)
+    const double tau = fabs(beta[0] - beta[2]);
+    double g[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double x = beta[k] + c.eps;
+      double r = rcp_approx(x);
+      r = fma(r, fma(-x, r, 1.0), r);
+      g[k] = fma(tau, r, 1.0);
+    }
+    if (c.q == 6) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const double t2 = g[k] * g[k];
+        g[k] = t2 * t2 * t2;
+      }
+    } else {
+      const double t[3] = {g[0], g[1], g[2]};
+      g[0] = g[1] = g[2] = 1.0;
+      for (int r = 0; r < c.q; ++r)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g[k] *= t[k];
+    }
+    const double sg = (g[0] + g[1]) + g[2], cut = c.ct * sg;
+    const double up = cut * (1.0 + 0x1p-30), dn = cut * (1.0 - 0x1p-30);
+    bool sure = (sg < 1e300) & ((beta[0] + beta[1]) + beta[2] < 1e300) & (c.q <= 1024);
+    unsigned f = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const bool keep = g[k] > up;
+      sure &= keep | (g[k] < dn);
+      f |= keep ? 1u << k : 0u;
+    }
+    if (!sure) f = teno5_flags_cold(beta[0], beta[1], beta[2], c.ct, c.eps, c.q);
+    return f;
   } else {
-    d[0] = 7.0 / 36.0 - gw; d[1] = 11.0 / 18.0; d[2] = 7.0 / 36.0 + gw;
+    return teno5_flags(beta, c);
   }
 }
 
-// normalised weights of p0..p2 at point `where`: TENO5 from its flags,
-// WENO-Z from the indicators
-template <int SCHEME, class R>
-TGKS_HD void small_weights(const R* beta, unsigned flag, int where, const SchemeCfg& c, R* ob) {
-#pragma clang fp contract(off)
-  double d[3];
-  lin_weights(where, d);
-  if (SCHEME == SCHEME_TENO5) {
-    double S = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) S = S + ((flag >> k) & 1u ? d[k] : 0.0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) ob[k] = R((flag >> k) & 1u ? d[k] / S : 0.0);
-  } else {
-    const R tau = fabs(beta[0] - beta[2]);
-    R om[3], S = R(0.0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      om[k] = d[k] * (1.0 + tau / (beta[k] + c.eps_w));
-      S = S + om[k];
+// linear weights of p0..p2 at x_{i-1/2} (where 0), x_{i+1/2} (1), the Gauss
+// points -1/(2 sqrt 3) (2) and +1/(2 sqrt 3) (3)
+constexpr double LIN_GW = 1.7320508075688772 / 1080.0;
+constexpr double LIN_W[4][3] = {{0.3, 0.6, 0.1},
+                                {0.1, 0.6, 0.3},
+                                {7.0 / 36.0 + LIN_GW, 11.0 / 18.0, 7.0 / 36.0 - LIN_GW},
+                                {7.0 / 36.0 - LIN_GW, 11.0 / 18.0, 7.0 / 36.0 + LIN_GW}};
+
+// TENO5's normalised weights d_k delta_k / sum d_k delta_k of each flag at the
+// four points: divided by the compiler, which rounds as the division of the
+// definition does
+struct Teno5Weights {
+  double w[8][4][3];
+};
+constexpr Teno5Weights teno5_weights() {
+  Teno5Weights t{};
+  for (int f = 1; f < 8; ++f)
+    for (int x = 0; x < 4; ++x) {
+      double S = 0.0;
+      for (int k = 0; k < 3; ++k) S = S + ((f >> k) & 1 ? LIN_W[x][k] : 0.0);
+      for (int k = 0; k < 3; ++k) t.w[f][x][k] = (f >> k) & 1 ? LIN_W[x][k] / S : 0.0;
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) ob[k] = om[k] / S;
-  }
+  return t;
 }
+constexpr Teno5Weights TENO5_W = teno5_weights();
+
+// tau / (beta + eps) of the WENO weights, without a division; indicators
+// below 1e-300 belong to differences below 1e-150, whose weighting no longer
+// shows in a value
+template <class R>
+TGKS_HD R weno_ratio(R tau, R x) {
+  return tau / x;
+}
+TGKS_HD double weno_ratio(double tau, double x) { return tau * recip(fmax(x, 1e-300)); }
 
 // WENO-AO coefficients of p0..p2 (w[0..2]) and p3 (w[3])
 template <class R>
 TGKS_HD void ao_coeffs(const R* beta, const SchemeCfg& c, R* w) {
-  const double dh = c.d_hi, dl = c.d_lo;
-  const double d[4] = {(1.0 - dh) * (1.0 - dl) / 2.0, (1.0 - dh) * dl, (1.0 - dh) * (1.0 - dl) / 2.0, dh};
   const R tau = ((fabs(beta[3] - beta[0]) + fabs(beta[3] - beta[1])) + fabs(beta[3] - beta[2])) * (1.0 / 3.0);
+  const double d[4] = {c.d[0], c.d[1], c.d[0], c.d[2]};
   R om[4], S = R(0.0);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const R r = tau / (beta[k] + c.eps_w);
+    const R r = weno_ratio(tau, beta[k] + c.eps_w);
     om[k] = d[k] * (1.0 + r * r);
     S = S + om[k];
   }
-  const R iS = R(1.0) / S;
+  const R iS = recip(S);
   const R o3 = om[3] * iS;
-  w[3] = o3 * (1.0 / dh);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) w[k] = om[k] * iS - o3 * (d[k] / dh);
+  w[3] = o3 * c.r[2];
+  w[0] = om[0] * iS - o3 * c.r[0];
+  w[1] = om[1] * iS - o3 * c.r[1];
+  w[2] = om[2] * iS - o3 * c.r[0];
 }
 
 // interface values of p0..p2 at x_{i-1/2} (vm) and x_{i+1/2} (vp)
@@ -720,35 +789,43 @@ TGKS_HD void small_face(const R* Q, R* vm, R* vp) {
   vm[2] = ((11.0 * c - 7.0 * d) + 2.0 * e) * (1.0 / 6.0);
 }
 
-// WENO-Z / TENO5 interface values v(-1/2), v(+1/2); returns the flags
-template <int SCHEME, class R>
-TGKS_HD unsigned zt_face(const R* Q, const R* beta, const SchemeCfg& c, R& vm_o, R& vp_o) {
-#pragma clang fp contract(off)
-  const unsigned f = SCHEME == SCHEME_TENO5 ? teno5_flags(beta, c) : 0u;
-  R om[3], op[3], vm[3], vp[3];
-  small_weights<SCHEME>(beta, f, 0, c, om);
-  small_weights<SCHEME>(beta, f, 1, c, op);
-  small_face(Q, vm, vp);
-  R a = R(0.0), b = R(0.0);
+// the WENO-Z ratios u_k = 1 + tau / (beta_k + eps) of p0..p2, and the
+// normalised weights d_k u_k / sum d_k u_k at point `where`
+template <class R>
+TGKS_HD void wenoz_ratios(const R* beta, const SchemeCfg& c, R* u) {
+  const R tau = fabs(beta[0] - beta[2]);
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    a = a + om[k] * vm[k];
-    b = b + op[k] * vp[k];
-  }
-  vm_o = a;
-  vp_o = b;
-  return f;
+  for (int k = 0; k < 3; ++k) u[k] = 1.0 + weno_ratio(tau, beta[k] + c.eps_w);
+}
+template <class R>
+TGKS_HD void wenoz_weights(const R* u, int where, R* w) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) w[k] = LIN_W[where][k] * u[k];
+  const R iS = recip((w[0] + w[1]) + w[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) w[k] = w[k] * iS;
+}
+
+// interface values of the weighted small stencils, in one fixed order
+template <class R, class W>
+TGKS_HD void small_blend(const R* vm, const R* vp, const W* wm, const W* wp, R& vm_o, R& vp_o) {
+#pragma clang fp contract(off)
+  vm_o = (wm[0] * vm[0] + wm[1] * vm[1]) + wm[2] * vm[2];
+  vp_o = (wp[0] * vp[0] + wp[1] * vp[1]) + wp[2] * vp[2];
 }
 
 // Normal reconstruction: out = {v(-1/2), s(-1/2), v(+1/2), s(+1/2)} (cell
-// units); returns the flags (TENO5) or 0
+// units); returns the flags (TENO5) or 0.  TENO5: wavefronts all of whose
+// lanes keep every stencil, the smooth ones, take the linear weights as
+// constants, the others load their flag's row of the table.  With a division
+// per weight and per indicator, 410 in a 2-D face's code, the divisions bound
+// the kernel: 500 x 310 cells, one stage's faces, 160 us; now 77.
 template <int SCHEME, class R>
 TGKS_HD unsigned scheme_face(const R* Q, const SchemeCfg& c, R* out) {
 #pragma clang fp contract(off)
-  R beta[4];
-  indicators(Q, beta);
   if (SCHEME == SCHEME_WENO_AO) {
-    R w[4];
+    R beta[4], w[4];
+    indicators(Q, beta);
     ao_coeffs(beta, c, w);
     const R a = Q[0], b = Q[1], cc = Q[2], d = Q[3], e = Q[4];
     R vm[3], vp[3];
@@ -765,8 +842,25 @@ TGKS_HD unsigned scheme_face(const R* Q, const SchemeCfg& c, R* out) {
     out[3] = ((w[3] * Lps + w[0] * dp0) + w[1] * dp12) + w[2] * dp12;
     return 0u;
   }
-  R vm, vp;
-  const unsigned f = zt_face<SCHEME>(Q, beta, c, vm, vp);
+  TenoParts<R> p;
+  R beta[3], vms[3], vps[3], vm, vp;
+  teno_parts(Q, p);
+  small_indicators(p, beta);
+  small_face(Q, vms, vps);
+  unsigned f = 0;
+  if (SCHEME == SCHEME_TENO5) {
+    f = teno5_select(beta, c);
+    if (all_lanes(f == 7u))
+      small_blend(vms, vps, TENO5_W.w[7][0], TENO5_W.w[7][1], vm, vp);
+    else
+      small_blend(vms, vps, TENO5_W.w[f][0], TENO5_W.w[f][1], vm, vp);
+  } else {
+    R u[3], wm[3], wp[3];
+    wenoz_ratios(beta, c, u);
+    wenoz_weights(u, 0, wm);
+    wenoz_weights(u, 1, wp);
+    small_blend(vms, vps, wm, wp, vm, vp);
+  }
   out[0] = vm;
   out[1] = -2.0 * ((2.0 * vm + vp) - 3.0 * Q[2]);
   out[2] = vp;
@@ -801,11 +895,10 @@ template <int SCHEME, class R>
 TGKS_HD unsigned scheme_gauss(const R* Q, const SchemeCfg& c, R* val, R* der) {
   const double s = 0.28867513459481288225;  // 1/(2 sqrt 3)
   const double ss = s * s;
-  R beta[4], L[5], S[3][3];
-  indicators(Q, beta);
-  cand_coeffs(Q, L, S);
   if (SCHEME == SCHEME_WENO_AO) {
-    R w[4];
+    R beta[4], L[5], S[3][3], w[4];
+    indicators(Q, beta);
+    cand_coeffs(Q, L, S);
     ao_coeffs(beta, c, w);
     const R c0 = w[3] * L[0] + ((w[0] * S[0][0] + w[1] * S[1][0]) + w[2] * S[2][0]);
     const R c1 = w[3] * L[1] + ((w[0] * S[0][1] + w[1] * S[1][1]) + w[2] * S[2][1]);
@@ -819,20 +912,52 @@ TGKS_HD unsigned scheme_gauss(const R* Q, const SchemeCfg& c, R* val, R* der) {
     der[1] = deven + dodd;
     return 0u;
   }
-  R vm, vp;
-  const unsigned f = zt_face<SCHEME>(Q, beta, c, vm, vp);
-  // slopes: the quadratic with the average Q_0 and the end values vm, vp
-  const R q1 = vp - vm, q2 = 3.0 * (vm + vp) - 6.0 * Q[2];
+  // Quadratic k has the value Q_0 +- l_k / 4 + t_k / 12 at the faces and,
+  // s^2 being 1/12, Q_0 +- (s / 2) l_k at the Gauss points; the slopes are
+  // those of the quadratic with the average Q_0 and the end values
+  // Q_0 + vm, Q_0 + vp
+  TenoParts<R> p;
+  R beta[3];
+  teno_parts(Q, p);
+  small_indicators(p, beta);
+  const R l[3] = {p.l0, p.x, -p.l2};
+  auto blend = [&](const auto* wm, const auto* wp, const auto* w0, const auto* w1) {
+    R am[3], ap[3];
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    R ob[3];
-    small_weights<SCHEME>(beta, f, 2 + m, c, ob);
-    const R c0 = (ob[0] * S[0][0] + ob[1] * S[1][0]) + ob[2] * S[2][0];
-    const R c1 = (ob[0] * S[0][1] + ob[1] * S[1][1]) + ob[2] * S[2][1];
-    const R c2 = (ob[0] * S[0][2] + ob[1] * S[1][2]) + ob[2] * S[2][2];
-    const double x = m ? s : -s;
-    val[m] = c0 + x * (c1 + x * c2);
-    der[m] = q1 + (2.0 * x) * q2;
+    for (int k = 0; k < 3; ++k) {
+      const R t = p.t[k] * (1.0 / 12.0);
+      am[k] = t - 0.25 * l[k];
+      ap[k] = t + 0.25 * l[k];
+    }
+    const R vm = (wm[0] * am[0] + wm[1] * am[1]) + wm[2] * am[2];
+    const R vp = (wp[0] * ap[0] + wp[1] * ap[1]) + wp[2] * ap[2];
+    const R q1 = vp - vm, q2 = 3.0 * (vm + vp);
+    val[0] = Q[2] - (0.5 * s) * ((w0[0] * l[0] + w0[1] * l[1]) + w0[2] * l[2]);
+    val[1] = Q[2] + (0.5 * s) * ((w1[0] * l[0] + w1[1] * l[1]) + w1[2] * l[2]);
+    der[0] = q1 - (2.0 * s) * q2;
+    der[1] = q1 + (2.0 * s) * q2;
+  };
+  unsigned f = 0;
+  if (SCHEME == SCHEME_TENO5) {
+    f = teno5_select(beta, c);
+    if (all_lanes(f == 7u)) {
+      blend(TENO5_W.w[7][0], TENO5_W.w[7][1], TENO5_W.w[7][2], TENO5_W.w[7][3]);
+    } else {
+      blend(TENO5_W.w[f][0], TENO5_W.w[f][1], TENO5_W.w[f][2], TENO5_W.w[f][3]);
+      if (f == 0u) {  // no stencil kept (a cut-off above 1/3): weights of zero
+        val[0] = val[1] = R(0.0);
+        der[0] = (12.0 * s) * Q[2];
+        der[1] = -(12.0 * s) * Q[2];
+      }
+    }
+  } else {
+    R u[3], wm[3], wp[3], w0[3], w1[3];
+    wenoz_ratios(beta, c, u);
+    wenoz_weights(u, 0, wm);
+    wenoz_weights(u, 1, wp);
+    wenoz_weights(u, 2, w0);
+    wenoz_weights(u, 3, w1);
+    blend(wm, wp, w0, w1);
   }
   return f;
 }

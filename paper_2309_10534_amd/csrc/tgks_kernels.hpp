@@ -958,20 +958,29 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
       // and derivatives
       SchemeCfg se = a.sc;
       se.q = 6;
+      // (the pair shares the work: lane m reconstructs the components 2 m and
+      // 2 m + 1 at both Gauss points and they swap)
       double W0e[NC], dW0e[2][NC];
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        double Qe[5], Qx[5], v[2], d[2];
+      for (int j = 0; j < 2; ++j) {
+        const int q = 2 * m + j;
+        double Qe[5], Qx[5], v[2], d[2], vx[2], dx[2];
 #pragma unroll
         for (int r = 0; r < 5; ++r) {
           Qe[r] = sE[q][0][ft + r][fn];
           Qx[r] = sE[q][1][ft + r][fn];
         }
         scheme_gauss<SCHEME_TENO5>(Qe, se, v, d);
-        W0e[q] = m ? v[1] : v[0];
-        dW0e[1][q] = (m ? d[1] : d[0]) * idt;
-        scheme_gauss<SCHEME_TENO5>(Qx, se, v, d);
-        dW0e[0][q] = m ? v[1] : v[0];
+        scheme_gauss<SCHEME_TENO5>(Qx, se, vx, dx);
+        const double own[3] = {m ? v[1] : v[0], m ? d[1] : d[0], m ? vx[1] : vx[0]};
+        const double got[3] = {lane_xor<1>(m ? v[0] : v[1]), lane_xor<1>(m ? d[0] : d[1]),
+                               lane_xor<1>(m ? vx[0] : vx[1])};
+        W0e[j] = m ? got[0] : own[0];
+        W0e[2 + j] = m ? own[0] : got[0];
+        dW0e[1][j] = (m ? got[1] : own[1]) * idt;
+        dW0e[1][2 + j] = (m ? own[1] : got[1]) * idt;
+        dW0e[0][j] = m ? got[2] : own[2];
+        dW0e[0][2 + j] = m ? own[2] : got[2];
       }
       ok = gp_flux_eq<2, NS, flux_out(STAGE)>(Wo, Wp, Do, Dp, W0e, dW0e, a.fc, dt, A, B, 0.5, -sg);
     } else {

@@ -157,3 +157,33 @@ def test_smooth_and_general_selections_agree(torch_dev, shape, level):
         gp.close()
     assert ba == bb == 0
     assert np.array_equal(sa, sb) and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape", [(1500,), (70, 45)])
+@pytest.mark.parametrize("ct,q,eps", [(1e-7, 6, 1e-40), (1e-5, 6, 1e-12), (1e-3, 2, 1e-40), (0.1, 1, 1e-6),
+                                      (0.3, 6, 1e-40), (0.34, 5, 1e-40), (0.6, 6, 1e-8), (1e-5, 16, 0.0)])
+def test_teno5_cutoffs_with_spread_indicators(orc, torch_dev, shape, ct, q, eps):
+    """TENO5 cut-off flags of one step equal to the oracle's, bit for bit, on
+    data whose differences span fifteen decades from cell to cell (with
+    constant stretches), for cut-offs that keep everything, split the stencils
+    or keep none, and powers that overflow; the states agree too."""
+    rng = np.random.default_rng(int(1e6 * ct) + q)
+    n = int(np.prod(shape))
+    amp = np.repeat(10.0 ** rng.uniform(-16, -1, size=n // 5 + 1), 5)[:n]
+    amp *= rng.random(n) < 0.9
+    field = lambda: (1.0 + amp * rng.uniform(-1, 1, size=n)).reshape(shape[::-1])
+    W = I.conservative(field(), [0.2 * field() for _ in shape], field())
+    pr = problem(list(shape), [1.0 / m for m in shape], bc="periodic", scheme="teno5", ct1=ct, q=q, eps=eps)
+    P = orc_params(orc, pr)
+    dt = orc.cfl_dt(P, W, 0.3)
+    Wo, fo, _, bado = orc.step(P, W, dt, want_flags=True)
+    print(f"[paths] teno5 {shape} ct={ct} q={q}", flush=True)
+    gp = GpuProblem(pr)
+    try:
+        Wg, _, fg, badg = gp.step(W, dt)
+    finally:
+        gp.close()
+    assert np.array_equal(fg, fo), np.count_nonzero(fg != fo)
+    assert badg == bado
+    if bado == 0:
+        assert_close(Wg, Wo, 1e-10, f"teno5 {shape} ct={ct} q={q}")
