@@ -65,6 +65,7 @@ __device__ __forceinline__ StageArgs batch_stage(const BatchArgs& b, const Batch
   a.fbc = nullptr;  // fallbacks are not counted in batches
   a.t0 = 0.0;
   a.tclk = nullptr;
+  a.ck = StepClock{};
   return a;
 }
 
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(256) void batch_line_kernel(BatchArgs b) {
   l.mu = I.mu;
   l.idx = 1.0 / I.g.dx[0];
   // (an instance's clock, partial minima and step count)
-  l.ck = StepClock{b.prev ? b.prev + 2 * w.x : nullptr, b.clock + 2 * w.x, b.partial + I.blk0, b.steps + w.x, I.nblk,
+  l.s.ck = StepClock{b.prev ? b.prev + 2 * w.x : nullptr, b.clock + 2 * w.x, b.partial + I.blk0, b.steps + w.x, I.nblk,
                    b.cfl, b.t_end};
   line_body<STAGE, NS, false, STAGE == 2, CHAR, EX>(l, (w.y * 4 + (int)(threadIdx.x >> 6)) * LINE_CELLS,
                                                      b.partial + I.blk0 + w.y);

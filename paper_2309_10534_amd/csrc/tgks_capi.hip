@@ -13,10 +13,9 @@ using namespace tgks;
 
 // one stage of a 1-D step
 int launch_line(tgks_ctx* c, int stage, const double* W, const double* base, double* o1, double* o2, const double* dt,
-                uint8_t* flags, bool cfl, const StepClock* ck) {
+                uint8_t* flags, bool cfl) {
   const bool fl = flags != nullptr && stage == 1;
-  LineArgs l{};
-  if (ck) l.ck = *ck;
+  LineArgs l;
   l.s = stage_args(c, W, 0, dt);
   if (fl) l.s.nflags = flags;
   l.base = base;
@@ -443,23 +442,18 @@ static int enqueue_run(tgks_ctx* c, double* W, int n_steps, double cfl, double t
   double* src = W;
   double* dst = c->W2;
   double* clk = c->clock;  // the clock of the last step
-  // 1-D: a step's stage 1 takes the clock from the step before (two clocks in
-  // turn), as long as its wavefronts read the partial minima in a few loads
-  const bool own_clock = c->g.D == 1 && c->nblk <= CLOCK_NBLK;
+  // 1-D and 2-D: a step's stage 1 takes the clock from the step before (two
+  // clocks in turn), as long as its wavefronts read the partial minima in a few
+  // loads
+  const bool own_clock = c->g.D <= 2 && c->nblk <= CLOCK_NBLK;
   for (int s = 0; s < n_steps; ++s) {
-    if (own_clock) {
-      StepClock ck{nullptr, nullptr, c->partial, nullptr, c->nblk, use_cfl ? cfl : 0.0, t_end};
-      if (s > 0) {
-        ck.prev = clk;
-        clk = ck.next = c->clock + 2 * (s & 1);
-      }
-      c->tclk = clk;  // the state of each step is that of time t0 + clk[0]
-      if ((r = launch_line(c, 1, src, src, c->Ws, c->P, clk + 1, nullptr, false, &ck))) break;
-      if ((r = launch_line(c, 2, c->Ws, c->P, dst, nullptr, clk + 1, nullptr, use_cfl))) break;
-    } else {
-      c->tclk = clk;
-      if ((r = do_step(c, src, dst, clk + 1, nullptr, use_cfl))) break;
+    if (own_clock && s > 0) {
+      double* next = c->clock + 2 * (s & 1);
+      c->ck = StepClock{clk, next, c->partial, nullptr, c->nblk, use_cfl ? cfl : 0.0, t_end};
+      clk = next;
     }
+    c->tclk = clk;  // the state of each step is that of time t0 + clk[0]
+    if ((r = do_step(c, src, dst, clk + 1, nullptr, use_cfl))) break;
     if (!own_clock || s == n_steps - 1)
       if ((r = launch_finalize(c, cfl, 0.0, t_end, clk, nullptr, use_cfl ? 1 : 2))) break;
     double* t = src;
@@ -467,6 +461,7 @@ static int enqueue_run(tgks_ctx* c, double* W, int n_steps, double cfl, double t
     dst = t;
   }
   c->tclk = nullptr;
+  c->ck = StepClock{};
   if (r) return r;
   if (src != W)
     HIPCHK(hipMemcpyAsync(W, src, (size_t)c->nc * c->ncell * sizeof(double), hipMemcpyDeviceToDevice, c->stream));

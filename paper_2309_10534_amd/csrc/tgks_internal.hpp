@@ -42,6 +42,7 @@ struct tgks_ctx {
   double* partial = nullptr;
   int nblk = 0;          // CFL partial minima (blocks of the updates)
   int per = 256;         // cells per block
+  StepClock ck{};        // within tgks_run: the clock of the next stage 1 (see StepClock)
   int line_waves = 1;    // 1-D: wavefronts per block of the line kernel
   double* clock = nullptr;
   unsigned long long* fail = nullptr;
@@ -200,6 +201,7 @@ inline StageArgs stage_args(tgks_ctx* c, const double* W, int ax, const double* 
   a.tclk = c->tclk;
   a.fallback = c->p.fallback;
   a.fbc = c->fail + 1;  // the context's second counter
+  a.ck = c->ck;
   return a;
 }
 
@@ -216,7 +218,7 @@ int launch_scheme_faces(tgks_ctx* c, const StageArgs* a, int stage, bool fl);
 // = P (stage 1); W: the state the fluxes are computed from, base: what they
 // are subtracted from
 int launch_line(tgks_ctx* c, int stage, const double* W, const double* base, double* o1, double* o2, const double* dt,
-                uint8_t* flags, bool cfl, const StepClock* ck = nullptr);
+                uint8_t* flags, bool cfl);
 template <int SCHEME>
 int launch_scheme_line(tgks_ctx* c, const LineArgs& l, int stage, bool fl, bool cfl);
 

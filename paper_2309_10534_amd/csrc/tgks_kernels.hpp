@@ -55,6 +55,22 @@ __device__ __forceinline__ double other_quad(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// The clock {t, dt} of a step taken from the step before: t += dt, the new dt
+// from the partial minima that its stage 2 left (cfl > 0; else the same dt).
+// Every wavefront of the new step's stage 1 evaluates it for itself (few
+// partial minima) and the grid's first writes it down, in another place than
+// the old one: no kernel of its own between the steps.
+constexpr int CLOCK_NBLK = 256;  // partial minima: at most four loads per lane
+
+struct StepClock {
+  const double* prev;     // the clock of the step before; null: none, dt is given
+  double* next;
+  const double* partial;
+  long long* steps;       // counts the steps taken (null: not counted)
+  int nblk;
+  double cfl, t_end;
+};
+
 struct StageArgs {
   Geom g;
   FluxCfg fc;
@@ -76,6 +92,7 @@ struct StageArgs {
   const double* tclk;
   int fallback;     // 1: first-order fallback at non-physical Gauss-point states
   unsigned long long* fbc;  // fallback counter, or null (not counted)
+  StepClock ck;     // stage 1 in 1-D and 2-D: the step's clock from the step before (or dt and tclk as given)
 };
 
 __device__ __forceinline__ long long face_count(const Geom& g, int ax) {
@@ -343,22 +360,6 @@ __device__ __forceinline__ double next_dt(double v, double cfl, double t, double
   return dt;
 }
 
-// The clock {t, dt} of a step taken from the step before: t += dt, the new dt
-// from the partial minima that its stage 2 left (cfl > 0; else the same dt).
-// Every wavefront of the new step's stage 1 evaluates it for itself (few
-// partial minima) and the grid's first writes it down, in another place than
-// the old one: no kernel of its own between the steps.
-constexpr int CLOCK_NBLK = 256;  // partial minima: at most four loads per lane
-
-struct StepClock {
-  const double* prev;     // the clock of the step before; null: none, dt is given
-  double* next;
-  const double* partial;
-  long long* steps;       // counts the steps taken (null: not counted)
-  int nblk;
-  double cfl, t_end;
-};
-
 __device__ __forceinline__ void step_clock(const StepClock& k, bool write, double& t, double& dt) {
   double v = INFINITY;
   bool nan = false;
@@ -403,7 +404,6 @@ struct LineArgs {
   double* out1;        // stage 1: W*; stage 2: W^{n+1}
   double* out2;        // stage 1: P
   double mu, idx;      // viscosity; 1 / dx
-  StepClock ck;        // stage 1: the step's clock from the step before (or dt given by s.dt)
 };
 
 // value of the lane below (UP = false) or above (UP = true)
@@ -442,8 +442,8 @@ __device__ __forceinline__ void line_body(const LineArgs& l, int first, double* 
 #pragma unroll
   for (int c = 0; c < 3; ++c) w[c] = l.base[(long long)c * n + fc];
   double dt, t = 0.0;
-  if (STAGE == 1 && l.ck.prev) {
-    step_clock(l.ck, first == 0, t, dt);
+  if (STAGE == 1 && a.ck.prev) {
+    step_clock(a.ck, first == 0, t, dt);
     t += a.t0;
   } else {
     dt = *a.dt;
@@ -601,14 +601,19 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   constexpr int LN = TN + 5, LT = TT + 4, RN = TN + 1;
   double(*sW)[LT][LN] = reinterpret_cast<double(*)[LT][LN]>(lds);
   double(*sR)[LT][RN][4] = reinterpret_cast<double(*)[LT][RN][4]>(lds + NC * LT * LN);
-  const double dt = *a.dt;
+  double dt, t_prev = 0.0;
+  const bool clocked = STAGE == 1 && a.ck.prev != nullptr;
+  if (clocked)
+    step_clock(a.ck, AX == 0 && blockIdx.x == 0 && threadIdx.x < 64, t_prev, dt);
+  else
+    dt = *a.dt;
   if (!(dt > 0.0)) return;
   const Geom& g = a.g;
   const int TA = 1 - AX;  // tangential axis
   const int nN = g.n[AX], nT = g.n[TA];
   const int f0 = bx * TN, t0 = by * TT;
   const int tid = threadIdx.x;
-  const double tb = EX ? boundary_time(a, STAGE, dt) : 0.0;
+  const double tb = !EX ? 0.0 : clocked ? a.t0 + t_prev : boundary_time(a, STAGE, dt);
 
   // 1. cells of the tile, ghost cells by the index map or prescribed states;
   //    without prescribed sides one thread per cell maps it once and loads
