@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void batch_update_kernel(BatchArgs b) {
   u.gamma = I.gamma;
   u.mu = I.mu;
   u.partial = nullptr;
-  update_body<D, STAGE, CFL>(u, (long long)w.y * 256 + threadIdx.x, CFL ? b.partial + I.blk0 + w.y : nullptr);
+  update_body<D, STAGE, CFL, true>(u, (long long)w.y * 256 + threadIdx.x, CFL ? b.partial + I.blk0 + w.y : nullptr);
 }
 
 template <int D>

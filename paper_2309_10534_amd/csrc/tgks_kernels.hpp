@@ -1414,8 +1414,13 @@ struct UpdateArgs {
   double* partial;    // stage 2 with CFL: one minimum per block, or null
 };
 
-// cell id of this thread; the block's CFL minimum goes to *partial
-template <int D, int STAGE, bool CFL>
+// cell id of this thread; the block's CFL minimum goes to *partial.  Large grids
+// move the face fluxes at 5 TB/s, the rate of a copy; a small grid waits:
+// hence 32-bit index arithmetic (a 64-bit quotient takes some hundred
+// instructions) and loads that do not wait for the time step.  STOP: for
+// batches, in which instances stop: the fluxes are not read then.  97 x 61, one
+// update: 4.6 -> 4.1 us.
+template <int D, int STAGE, bool CFL, bool STOP = false>
 __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, double* partial) {
   constexpr int NC = D + 2;
   const Geom& g = u.g;
@@ -1424,9 +1429,18 @@ __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, d
   const bool adv = dt > 0.0;
   double w1[NC];
   if (live) {
-    const int i = (int)(id % g.n[0]);
-    const int j = D >= 2 ? (int)((id / g.n[0]) % g.n[1]) : 0;
-    const int k = D >= 3 ? (int)(id / ((long long)g.n[0] * g.n[1])) : 0;
+    int i, j, k;
+    if (g.ncell <= 0x7fffffffLL) {
+      const unsigned n0 = (unsigned)g.n[0], q = (unsigned)id / n0;
+      i = (int)((unsigned)id - q * n0);
+      k = D >= 3 ? (int)(q / (unsigned)g.n[1]) : 0;
+      j = (int)q - k * g.n[1];
+    } else {
+      const long long q = id / g.n[0];
+      i = (int)(id - q * g.n[0]);
+      k = D >= 3 ? (int)(q / g.n[1]) : 0;
+      j = (int)(q - (long long)k * g.n[1]);
+    }
     long long lo[3], hi[3], nf[3];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -1439,7 +1453,7 @@ __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, d
     for (int c = 0; c < NC; ++c) {
       const double w = u.W[(long long)c * g.ncell + id];
       double a = w, b = w;
-      if (adv) {
+      if (adv || !STOP) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
           const double* FA = u.FA[d] + (long long)c * nf[d];
@@ -1450,8 +1464,9 @@ __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, d
           }
         }
       }
+      a = adv ? a : w;
       u.out1[(long long)c * g.ncell + id] = a;
-      if (STAGE == 1) u.out2[(long long)c * g.ncell + id] = b;
+      if (STAGE == 1) u.out2[(long long)c * g.ncell + id] = adv ? b : w;
       w1[c] = a;
     }
   }
