@@ -60,7 +60,13 @@ __device__ __forceinline__ double other_quad(double v) {
 // Every wavefront of the new step's stage 1 evaluates it for itself (few
 // partial minima) and the grid's first writes it down, in another place than
 // the old one: no kernel of its own between the steps.
-constexpr int CLOCK_NBLK = 256;  // partial minima: at most four loads per lane
+//
+// Up to 256 partial minima, four loads per lane, issued together: eight steps
+// of 400 cells 135 us with a kernel between the steps, 119 without; of 14,000
+// cells (242 partial minima) 128 and 117; of 64 x 64 291 and 277; of 256 x 256
+// (256 partial minima) 624 and 615, where reading them in every block takes up
+// most of the gain.
+constexpr int CLOCK_NBLK = 256;
 
 struct StepClock {
   const double* prev;     // the clock of the step before; null: none, dt is given
@@ -363,12 +369,19 @@ __device__ __forceinline__ double next_dt(double v, double cfl, double t, double
 __device__ __forceinline__ void step_clock(const StepClock& k, bool write, double& t, double& dt) {
   double v = INFINITY;
   bool nan = false;
-  if (k.cfl > 0.0)
-    for (int i = threadIdx.x & 63; i < k.nblk; i += 64) {
-      const double p = k.partial[i];
-      nan = nan || !(p == p);
-      v = fmin(v, p);
+  if (k.cfl > 0.0) {
+    double p[CLOCK_NBLK / 64];  // loaded together: one latency
+#pragma unroll
+    for (int r = 0; r < CLOCK_NBLK / 64; ++r) {
+      const int i = (threadIdx.x & 63) + 64 * r;
+      p[r] = i < k.nblk ? k.partial[i] : INFINITY;
     }
+#pragma unroll
+    for (int r = 0; r < CLOCK_NBLK / 64; ++r) {
+      nan = nan || !(p[r] == p[r]);
+      v = fmin(v, p[r]);
+    }
+  }
   t = k.prev[0];
   const double used = k.prev[1];
   if (used > 0.0) t += used;
@@ -1536,10 +1549,10 @@ __device__ __forceinline__ void finalize_body(const double* partial, int nblk, d
   }
 }
 
-// the whole CFL step of a small state in one block, at most sixteen cells per
-// thread: one launch instead of two (time step and step of 100 cells: 15 us,
-// 18 with two)
-constexpr int CFL_ONE = 16384;
+// The whole CFL step of a small state in one block: one launch instead of two
+// as long as the block's threads pass over few cells.  400 cells 5.5 us (7.7 in
+// two launches), 4,096 cells 6.5 (7.6), 14,000 cells 13.9 (7.8).
+constexpr int CFL_ONE = 4096;
 
 template <int D>
 __global__ __launch_bounds__(1024) void cfl_one_kernel(Geom g, const double* W, double gamma, double mu, double cfl,

@@ -2,7 +2,7 @@
 data where each begins and ends: 1-D grids around the cells that one wavefront
 (58) and one block (232 above 59,392 cells) own, the steps that take their
 clock from the step before (up to 256 partial minima), the time step of small
-grids in one block (up to 16,384 cells), and the smooth / general forms of the
+grids in one block (up to 4,096 cells), and the smooth / general forms of the
 tangential selections, which must agree to the bit."""
 import numpy as np
 import pytest
@@ -32,7 +32,7 @@ def field_1d(n, seed):
 
 
 @pytest.mark.parametrize("n", [3, 4, 57, 58, 59, 60, 61, 62, 63, 64, 115, 116, 117, 123, 124, 125, 174, 175, 186, 187,
-                               14848, 14849, 16384, 16385, 59392, 59393, 63488, 63489])
+                               4096, 4097, 14848, 14849, 59392, 59393, 63488, 63489])
 def test_line_kernel_sizes(orc, torch_dev, n):
     """One step with flags and three CFL steps of tgks_run against the
     oracle, every boundary pair, and the failure counter of a state that is
