@@ -32,13 +32,13 @@ FP64_PEAK_TFLOPS = 78.6  # MI355X FP64 vector peak (256 CU x 2.4 GHz x 128 flop/
 # --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, mean of the stage-1
 # and stage-2 launches of the merged x/y face kernel, tile shape 2), each
 # scaled by what the counter reads for a 32 MiB device-to-device copy
-# (FETCH_SIZE 16398 KiB: factor 32768/16398; WRITE_SIZE 32768 KiB: factor 1).
+# (FETCH_SIZE 16402 KiB: factor 32768/16402; WRITE_SIZE 32768 KiB: factor 1).
 # Valid only for the kernel sources they were taken with (sha256 prefix of
 # the three files below); the bench reports null traffic otherwise.
 TRAFFIC_SOURCES = ("paper_2309_10534_amd/csrc/tgks_device.hpp", "paper_2309_10534_amd/csrc/tgks_kernels.hpp",
                    "paper_2309_10534_amd/csrc/tgks_face2d.hip")
-TRAFFIC = {"sha": "d7e54452bb98aad7", "tile": 2, "fetch_factor": 32768.0 / 16397.8, "write_factor": 1.0,
-           "face_xy": {"fetch_kib": 45272.2, "write_kib": 99971.95}}
+TRAFFIC = {"sha": "239dfd07ba6c6f69", "tile": 2, "fetch_factor": 32768.0 / 16401.6, "write_factor": 1.0,
+           "face_xy": {"fetch_kib": 43366.0, "write_kib": 98639.15}}
 
 
 def measured_traffic(kernel, tile):
