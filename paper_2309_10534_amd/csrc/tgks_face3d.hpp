@@ -20,19 +20,28 @@ int launch_face3d_ax(tgks_ctx* c, const StageArgs& a, int stage, bool fl) {
   {
     Timer tm(c, AX);
     const int n1 = c->g.n[(AX + 1) % 3], n2 = c->g.n[(AX + 2) % 3];
-    const long long nbl = (long long)(c->g.n[AX] + 1) * ((n1 + B3_1 - 1) / B3_1) * ((n2 + B3_2 - 1) / B3_2);
-    const dim3 grid((unsigned)(8 * ((nbl + 7) / 8))), blk3(L3 * B3_1 * B3_2);
-#define F3L(...) hipLaunchKernelGGL((face3d_kernel<__VA_ARGS__>), grid, blk3, 0, c->stream, a)
+    const auto blocks = [&](int k) {
+      return (long long)(c->g.n[AX] + 1) * ((n1 + tile3_1(k) - 1) / tile3_1(k)) * ((n2 + tile3_2(k) - 1) / tile3_2(k));
+    };
+    const int tile = 33 * blocks(1) < 32 * blocks(0) ? 1 : 0;  // (see the kernel's tile shapes)
+    const dim3 grid((unsigned)(8 * ((blocks(tile) + 7) / 8))), blk3(L3 * tile3_1(tile) * tile3_2(tile));
+#define F3T(...) hipLaunchKernelGGL((face3d_kernel<__VA_ARGS__>), grid, blk3, 0, c->stream, a)
+#define F3L(...)              \
+  if (tile == 0) {            \
+    F3T(__VA_ARGS__, 0);      \
+  } else {                    \
+    F3T(__VA_ARGS__, 1);      \
+  }
 #define F3(EXV)                                  \
   if (stage == 1 && fl) {                        \
-    if (c->ns) F3L(AX, 1, true, EXV, true);      \
-    else F3L(AX, 1, false, EXV, true);           \
+    if (c->ns) { F3L(AX, 1, true, EXV, true) }   \
+    else { F3L(AX, 1, false, EXV, true) }        \
   } else if (stage == 1) {                       \
-    if (c->ns) F3L(AX, 1, true, EXV, false);     \
-    else F3L(AX, 1, false, EXV, false);          \
+    if (c->ns) { F3L(AX, 1, true, EXV, false) }  \
+    else { F3L(AX, 1, false, EXV, false) }       \
   } else {                                       \
-    if (c->ns) F3L(AX, 2, true, EXV, false);     \
-    else F3L(AX, 2, false, EXV, false);          \
+    if (c->ns) { F3L(AX, 2, true, EXV, false) }  \
+    else { F3L(AX, 2, false, EXV, false) }       \
   }
     // c->ex: the first-order fallback (3-D grids have no prescribed sides)
     if (c->ex) {
@@ -42,6 +51,7 @@ int launch_face3d_ax(tgks_ctx* c, const StageArgs& a, int stage, bool fl) {
     }
 #undef F3
 #undef F3L
+#undef F3T
   }
   HIPCHK(hipGetLastError());
   return TGKS_OK;

@@ -1126,11 +1126,21 @@ __global__ __launch_bounds__(256) void recon3d_kernel(StageArgs a) {
 // W, 1: W_n), then sweep 2 as [20 + ((m1*3 + kind)*2 + side)*5 + c] (kind 0:
 // W, 1: dW/dt1, 2: W_n at T1 Gauss point m1), c the global component, each a
 // plane of faces indexed like a state whose axis AX has n + 1 entries.
-constexpr int B3_1 = 2, B3_2 = 16, L3 = 8;
+//
+// Tile shapes (faces along T1 x T2, 32 faces in 256 threads): 0 = 2 x 16, 1 =
+// 4 x 8.  Shape 0 has the smaller halo in sweep 1 (400 items against 480) and
+// is 0.7 % faster where both fill their tiles (128^3: 18.8 and 18.95 ms for two
+// steps); shape 1 fills planes better whose T2 extent is small or just above a
+// multiple of 16.  The shape with fewer blocks is taken, shape 1 if it saves
+// more than one block in 32: 29 x 35 x 22, Navier-Stokes, 1096 us with shape 0
+// alone, 1009 with shape 1 alone, 997 by the rule.
+constexpr int L3 = 8;
+__host__ __device__ constexpr int tile3_1(int k) { return k == 0 ? 2 : 4; }
+__host__ __device__ constexpr int tile3_2(int k) { return k == 0 ? 16 : 8; }
 
-template <int AX, int STAGE, bool NS, bool EX = false, bool FLAGS = false>
-__global__ __launch_bounds__(L3 * B3_1 * B3_2, 3) void face3d_kernel(StageArgs a) {
-  constexpr int NC = 5, B1 = B3_1, B2 = B3_2, NT = L3 * B1 * B2;
+template <int AX, int STAGE, bool NS, bool EX = false, bool FLAGS = false, int TILE = 0>
+__global__ __launch_bounds__(L3 * tile3_1(TILE) * tile3_2(TILE), 3) void face3d_kernel(StageArgs a) {
+  constexpr int NC = 5, B1 = tile3_1(TILE), B2 = tile3_2(TILE), NT = L3 * B1 * B2;
   constexpr int L1 = B1 + 4, L2 = B2 + 4;
   constexpr int T1 = (AX + 1) % 3, T2 = (AX + 2) % 3;
   __shared__ double sR[2][NC][2][L2][L1];      // [side][c][value, normal slope][t2][t1]

@@ -3,7 +3,8 @@ data where each begins and ends: 1-D grids around the cells that one wavefront
 (58) and one block (232 above 59,392 cells) own, the steps that take their
 clock from the step before (up to 256 partial minima), the time step of small
 grids in one block (up to 4,096 cells), and the smooth / general forms of the
-tangential selections, which must agree to the bit."""
+tangential selections, which must agree to the bit; the two tile shapes of the
+3-D face kernel."""
 import numpy as np
 import pytest
 
@@ -187,3 +188,34 @@ def test_teno5_cutoffs_with_spread_indicators(orc, torch_dev, shape, ct, q, eps)
     assert badg == bado
     if bado == 0:
         assert_close(Wg, Wo, 1e-10, f"teno5 {shape} ct={ct} q={q}")
+
+
+@pytest.mark.parametrize("ns", [False, True])
+@pytest.mark.parametrize("shape", [(32, 32, 32), (29, 35, 22), (7, 17, 9), (18, 4, 24), (3, 3, 3), (5, 33, 40)])
+def test_tile_shapes_3d(orc, torch_dev, shape, ns):
+    """3-D grids whose directions take either tile shape (planes that fill
+    2 x 16 or 4 x 8 faces, remainders of both): one step with flags against the
+    oracle, and two steps of tgks_run equal to stepping without flags."""
+    rng = np.random.default_rng(sum(shape))
+    field = lambda: 1.0 + 0.1 * rng.uniform(-1, 1, size=shape[::-1])
+    W = I.conservative(field(), [0.2 * field() for _ in range(3)], field())
+    kw = dict(tau="viscous", mu=1e-3, prandtl=0.72) if ns else {}
+    pr = problem(list(shape), [1.0 / n for n in shape],
+                 bc=[("periodic", "periodic"), ("reflective", "transmissive"), ("noslip", "reflective")], **kw)
+    P = orc_params(orc, pr)
+    dt = orc.cfl_dt(P, W, 0.3)
+    Wo, fo, Wso, bado = orc.step(P, W, dt, want_flags=True, want_wstar=True)
+    print(f"[paths] 3-D tiles {shape} ns={ns}", flush=True)
+    gp = GpuProblem(pr)
+    try:
+        Wg, Wsg, fg, badg = gp.step(W, dt)
+        Wr, _, badr = gp.run(W, 2, fixed_dt=dt)
+        W1 = gp.step(W, dt, flags=False)[0]
+        W2 = gp.step(W1, dt, flags=False)[0]
+    finally:
+        gp.close()
+    assert badg == bado == 0 and badr == 0
+    assert np.array_equal(fg, fo)
+    assert_close(Wsg, Wso, 1e-10, f"W* {shape}")
+    assert_close(Wg, Wo, 1e-10, f"{shape}")
+    assert np.array_equal(W1, Wg) and np.array_equal(Wr, W2)
