@@ -1132,7 +1132,7 @@ __global__ __launch_bounds__(256) void recon3d_kernel(StageArgs a) {
 // is 0.7 % faster where both fill their tiles (128^3: 18.8 and 18.95 ms for two
 // steps); shape 1 fills planes better whose T2 extent is small or just above a
 // multiple of 16.  The shape with fewer blocks is taken, shape 1 if it saves
-// more than one block in 32: 29 x 35 x 22, Navier-Stokes, 1096 us with shape 0
+// more than one block in 32: 29 x 35 x 22, Euler, four steps, 1096 us with shape 0
 // alone, 1009 with shape 1 alone, 997 by the rule.
 constexpr int L3 = 8;
 __host__ __device__ constexpr int tile3_1(int k) { return k == 0 ? 2 : 4; }
