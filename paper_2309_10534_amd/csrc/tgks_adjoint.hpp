@@ -8,218 +8,9 @@
 // mode, the equilibrium pressure); a branch (tau == 0, the sign of a pressure
 // jump, +1 for equal pressures) keeps the forward's choice.
 #pragma once
-#include "tgks_device.hpp"
+#include "tgks_flux_face.hpp"
 
 namespace tgks {
-
-// ---------------------------------------------------------------------------
-// The forward pieces that the reverse differentiates: tables of every
-// monomial's moments in the face frame, the linear micro-slope solves and the
-// closed-form equilibrium moments (the kernels' forward flux evaluates the
-// same moments in the frame of the tangential velocity).
-// ---------------------------------------------------------------------------
-constexpr int NMT = 6;  // tangential tables <u_t^n>, n = 0..5
-
-template <class R>
-TGKS_HD void full_table(R U, R h, R* m, int n) {
-  m[0] = R(1.0);
-  m[1] = U;
-  for (int k = 1; k + 1 < n; ++k) m[k + 1] = U * m[k] + ((double)k * h) * m[k - 1];
-}
-
-template <int D, class R>
-struct MomSet {
-  R m1[NM1];
-  R mt[D > 1 ? D - 1 : 1][NMT];
-  R xi1, xi2;  // <xi^2>, <xi^4>
-};
-
-template <int D, class R>
-TGKS_HD R mono(const MomSet<D, R>& S, int i, int j, int k) {
-  R v = S.m1[i];
-  if (D >= 2) v = v * S.mt[0][j];
-  if (D >= 3) v = v * S.mt[D >= 3 ? 1 : 0][k];
-  return v;
-}
-
-// g[alpha] = <psi_alpha u1^i u2^j u3^k xi^(2l)>, l in {0, 1}
-template <int D, class R>
-TGKS_HD void gpsi(const MomSet<D, R>& S, int i, int j, int k, int l, R* g) {
-  const R base = mono(S, i, j, k);
-  g[0] = l == 0 ? base : base * S.xi1;
-  g[1] = l == 0 ? mono(S, i + 1, j, k) : mono(S, i + 1, j, k) * S.xi1;
-  if (D >= 2) g[2] = l == 0 ? mono(S, i, j + 1, k) : mono(S, i, j + 1, k) * S.xi1;
-  if (D >= 3) g[D >= 3 ? 3 : 0] = l == 0 ? mono(S, i, j, k + 1) : mono(S, i, j, k + 1) * S.xi1;
-  R e = mono(S, i + 2, j, k);
-  if (D >= 2) e = e + mono(S, i, j + 2, k);
-  if (D >= 3) e = e + mono(S, i, j, k + 2);
-  g[D + 1] = l == 0 ? 0.5 * (e + base * S.xi1) : 0.5 * (e * S.xi1 + base * S.xi2);
-}
-
-// out[alpha] (+)= s * <psi_alpha a(psi) u1^i u2^j u3^k>
-template <int D, bool ACC, class R>
-TGKS_HD void mpsia(const MomSet<D, R>& S, const R* a, int i, int j, int k, R s, R* out) {
-  constexpr int NC = D + 2;
-  R g[NC], t[NC], r[NC];
-  gpsi<D>(S, i, j, k, 0, g);
-#pragma unroll
-  for (int q = 0; q < NC; ++q) r[q] = a[0] * g[q];
-  gpsi<D>(S, i + 1, j, k, 0, g);
-#pragma unroll
-  for (int q = 0; q < NC; ++q) r[q] += a[1] * g[q];
-  if (D >= 2) {
-    gpsi<D>(S, i, j + 1, k, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) r[q] += a[2] * g[q];
-  }
-  if (D >= 3) {
-    gpsi<D>(S, i, j, k + 1, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) r[q] += a[D >= 3 ? 3 : 0] * g[q];
-  }
-  gpsi<D>(S, i + 2, j, k, 0, t);
-  if (D >= 2) {
-    gpsi<D>(S, i, j + 2, k, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) t[q] += g[q];
-  }
-  if (D >= 3) {
-    gpsi<D>(S, i, j, k + 2, 0, g);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) t[q] += g[q];
-  }
-  gpsi<D>(S, i, j, k, 1, g);
-  const R ae = 0.5 * a[NC - 1];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    const R v = r[q] + ae * (t[q] + g[q]);
-    if (ACC)
-      out[q] += s * v;
-    else
-      out[q] = s * v;
-  }
-}
-
-// closed-form solution a of <a psi> = b (per unit density) over the full
-// Maxwellian (U, lambda), N = K + D.
-template <int D, class R>
-TGKS_HD void micro_solve(const Gas<D, R>& g, double N, const R* b, R* a) {
-  R ub = R(0.0), u2 = R(0.0);
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    ub += g.U[d] * b[d + 1];
-    u2 += g.U[d] * g.U[d];
-  }
-  const R lam = g.lam;
-  const R aE = ((4.0 / N) * (lam * lam)) * ((2.0 * b[D + 1] - 2.0 * ub) + (u2 - N * g.h) * b[0]);
-  R ua = R(0.0);
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    a[d + 1] = (2.0 * lam) * (b[d + 1] - g.U[d] * b[0]) - g.U[d] * aE;
-    ua += g.U[d] * a[d + 1];
-  }
-  a[D + 1] = aE;
-  a[0] = (b[0] - ua) - (0.5 * aE) * (u2 + N * g.h);
-}
-
-template <int D, class R>
-TGKS_HD void tangential_tables(const Gas<D, R>& g, MomSet<D, R>& S) {
-#pragma unroll
-  for (int d = 1; d < D; ++d) full_table(g.U[d], g.h, S.mt[d - 1], NMT);
-}
-
-template <int D, class R>
-TGKS_HD void xi_moments(const Gas<D, R>& g, double K, MomSet<D, R>& S) {
-  S.xi1 = K * g.h;
-  S.xi2 = (K * (K + 2.0)) * (g.h * g.h);
-}
-
-// (i, j, k) exponents of u_d
-TGKS_HD void unit(int d, int& i, int& j, int& k) {
-  i = d == 0;
-  j = d == 1;
-  k = d == 2;
-}
-
-// Directional derivatives of closed-form moments of a Maxwellian g(W).
-// The derivative of g along a change dW of its conservative variables is
-// g a(psi) with <a psi> = dW / rho, so every full-space moment of g a(psi)
-// is the directional derivative of the corresponding moment of g:
-//   rho <u_k psi a>      = J_k(W) dW     (Euler flux F_k = rho <u_k psi>)
-//   rho <u_1 u_d psi a>  = dG_1d(W) dW   (G_1d = rho <u_1 u_d psi>)
-// which replaces micro-slope solves and moment sums over the full space.
-template <int D, class R>
-struct Prim {
-  R dU[D], dp, dh;
-};
-
-template <int D, class R>
-TGKS_HD void prim_dir(const Gas<D, R>& g, double N, const R* dW, Prim<D, R>& o) {
-  R udm = R(0.0), u2 = R(0.0);
-#pragma unroll
-  for (int e = 0; e < D; ++e) {
-    o.dU[e] = (dW[e + 1] - g.U[e] * dW[0]) * g.irho;
-    udm += g.U[e] * dW[e + 1];
-    u2 += g.U[e] * g.U[e];
-  }
-  // p = (2/N)(E - rho |U|^2 / 2)
-  o.dp = (2.0 / N) * ((dW[D + 1] - udm) + (0.5 * u2) * dW[0]);
-  o.dh = (o.dp - g.h * dW[0]) * g.irho;
-}
-
-// out = J_k(W) dW, the Euler flux along frame axis k differentiated along dW
-template <int D, class R>
-TGKS_HD void euler_jvp(const Gas<D, R>& g, R E, int k, const R* dW, const Prim<D, R>& d, R* out) {
-  const R p = g.rho * g.h;
-  const R mk = g.rho * g.U[k];
-  out[0] = dW[k + 1];
-#pragma unroll
-  for (int e = 0; e < D; ++e) {
-    R v = dW[k + 1] * g.U[e] + mk * d.dU[e];
-    if (e == k) v += d.dp;
-    out[e + 1] = v;
-  }
-  out[D + 1] = d.dU[k] * (E + p) + g.U[k] * (dW[D + 1] + d.dp);
-}
-
-// out = dG_1d(W) dW with G_1d = rho <u_1 u_d psi> (frame axis 0 normal):
-//   alpha 0: rho U1 Ud + p [d=0]
-//   alpha e: rho U1 Ud Ue + p (U1 [d=e] + Ud [e=0] + Ue [d=0])
-//   alpha E: rho U1 Ud (|U|^2 + (N+4) h)/2 + [d=0] p (|U|^2 + (N+2) h)/2
-template <int D, class R>
-TGKS_HD void g1d_jvp(const Gas<D, R>& g, double N, int d, const R* dW, const Prim<D, R>& q, R* out) {
-  const R p = g.rho * g.h;
-  const R dp = q.dp;
-  R u2 = R(0.0), udu = R(0.0);
-#pragma unroll
-  for (int e = 0; e < D; ++e) {
-    u2 += g.U[e] * g.U[e];
-    udu += g.U[e] * q.dU[e];
-  }
-  const R A = g.U[0] * g.U[d];
-  const R dA = q.dU[0] * g.U[d] + g.U[0] * q.dU[d];
-  const R dr = dW[0];
-  const R rdA = dr * A + g.rho * dA;  // d(rho A)
-  out[0] = d == 0 ? rdA + dp : rdA;
-  const R rA = g.rho * A;
-#pragma unroll
-  for (int e = 0; e < D; ++e) {
-    R v = rdA * g.U[e] + rA * q.dU[e];
-    if (d == e) v += dp * g.U[0] + p * q.dU[0];
-    if (e == 0) v += dp * g.U[d] + p * q.dU[d];
-    if (d == 0) v += dp * g.U[e] + p * q.dU[e];
-    out[e + 1] = v;
-  }
-  const R Q = u2 + (N + 4.0) * g.h;
-  const R dQ = 2.0 * udu + (N + 4.0) * q.dh;
-  R vE = rdA * Q + rA * dQ;
-  if (d == 0) {
-    const R Rr = u2 + (N + 2.0) * g.h;
-    const R dRr = 2.0 * udu + (N + 2.0) * q.dh;
-    vE += dp * Rr + p * dRr;
-  }
-  out[D + 1] = 0.5 * vE;
-}
 
 template <int D, class R>
 struct GasBar {

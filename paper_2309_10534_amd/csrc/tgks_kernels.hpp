@@ -10,7 +10,7 @@
 // The update kernels apply the flux differences; the stage-2 update also
 // reduces the CFL time step of the new state (Sec. 5 preamble).
 #pragma once
-#include "tgks_device.hpp"
+#include "tgks_flux_face.hpp"
 
 namespace tgks {
 
@@ -679,7 +679,8 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
     // in cell slot fn (high face), its right state in slot fn + 1 (low face).
     double(*sV)[LT][TN][4] = reinterpret_cast<double(*)[LT][TN][4]>(lds + tile2_lds(TILE));
     double(*sM)[TN][16] = reinterpret_cast<double(*)[TN][16]>(lds + tile2_lds(TILE) + NC * LT * TN * 4);
-    for (int L = tid; L < 2 * LT * TN; L += NT) {
+    auto project = [&](int L, auto mode) {
+      constexpr int MODE = decltype(mode)::value;
       const int fn = L % TN;
       const int tl = (L / TN) % LT;
       const int sd = L / (TN * LT);
@@ -700,7 +701,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         double V[5];
 #pragma unroll
         for (int r = 0; r < 5; ++r) V[r] = char_dot<NC>(Lm[k], sd == 0 ? C[r] : C[r + 1]);
-        const unsigned fl = teno_flag<SEL_FILTER, true>(V, a.tn);
+        const unsigned fl = teno_flag<MODE, true>(V, a.tn);
         double o[4];
         teno_face(V, fl, o);
         if (sd == 0) {
@@ -723,7 +724,13 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         for (int q = 0; q < NC; ++q)
 #pragma unroll
           for (int k = 0; k < NC; ++k) sM[tl][fn][q * NC + k] = Rm[q][k];
-    }
+    };
+    // (the exact weights alone where the certain decisions are off: a form of
+    // its own, so that they share the values' sums and nothing is formed twice)
+    if (a.tn.fast & TENO_FILTER_OK)
+      for (int L = tid; L < 2 * LT * TN; L += NT) project(L, std::integral_constant<int, SEL_FILTER>());
+    else
+      for (int L = tid; L < 2 * LT * TN; L += NT) project(L, std::integral_constant<int, SEL_EXACT>());
     __syncthreads();
     for (int L = tid; L < NC * LT * TN; L += NT) {
       const int fn = L % TN;
@@ -804,7 +811,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   //    flux at its Gauss point m and the pair sums the two.  The flux takes
   //    the lane's own side first, with its sign (+1 left, -1 right): the two
   //    sides' shares are added in either order with the same result, so no
-  //    lane has to sort them.
+  //    lane has to sort them (CHAR: left side first, see gp_flux_face).
   const int m = tid & 1;
   const int fi = tid >> 1;
   const int fn = fi % TN, ft = fi / TN;
@@ -813,7 +820,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   const long long nf = face_count(g, AX);
   const long long fidx = AX == 0 ? (long long)t * (g.n[0] + 1) + f : (long long)f * g.n[0] + t;
   const double idt = 1.0 / g.dx[TA];
-  double Wo[NC], Do[2][NC], Wp[NC], Dp[2][NC];  // own and partner's side; slopes [axis n/t][q]
+  double Wo[NC], Do[2][NC], Wp[NC], Dp[2][NC];  // own and partner's side (CHAR: left and right); slopes [axis n/t][q]
   const double sg = m ? 1.0 : -1.0;             // sign of the lane's Gauss point; -sg: of its side
   const int nr = m == 0 ? fn : fn + 1;
   const int vo = m == 0 ? 2 : 0;
@@ -828,7 +835,8 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
     if (CHAR) {
       // fields of the basis along the face at this face's reference state
       // (cells f-1 and f of row t); each field of W and of W_n is selected,
-      // evaluated and projected back
+      // evaluated and projected back.  MODE: SEL_FILTER, or SEL_EXACT where
+      // the certain decisions are off
 #pragma unroll
       for (int q = 0; q < NC; ++q) gV[q][0] = gV[q][1] = gD[q][0] = gD[q][1] = gN[q][0] = gN[q][1] = 0.0;
       double Wb[NC], Lt[NC][NC], Rt[NC][NC];
@@ -852,19 +860,20 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
           Qw[r] = char_dot<NC>(Lt[k], xw);
           Qn[r] = char_dot<NC>(Lt[k], xn);
         }
-        TenoPoly<double> w, n;
-        if (MODE == SEL_GIVEN)
-          given |= (teno_exact_cold(Qw, a.tt) << (8 * k)) | (teno_exact_cold(Qn, a.tt) << (8 * k + 4));
-        const unsigned fw = select_poly<MODE>(Qw, a.tt, w, sure, (given >> (8 * k)) & 15u);
-        const unsigned fq = select_poly<MODE>(Qn, a.tt, n, sure, (given >> (8 * k + 4)) & 15u);
-        if (MODE == SEL_SMOOTH && !all_lanes(sure)) return false;
+        const unsigned fw = teno_flag<MODE, true>(Qw, a.tt), fq = teno_flag<MODE, true>(Qn, a.tt);
         if (FLAGS) {
           a.tflags[((long long)(0 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fw;
           a.tflags[((long long)(1 * 2 + m) * NC + k) * nf + fidx] = (uint8_t)fq;
         }
-        const double v[2] = {fma(sg, w.odd, w.base), fma(-sg, w.odd, w.base)};
-        const double dv[2] = {fma(sg, w.od, w.ev), fma(-sg, w.od, w.ev)};
-        const double vn[2] = {fma(sg, n.odd, n.base), fma(-sg, n.odd, n.base)};
+        double pv[2], pd[2], qv[2], qd[2], v[2], dv[2], vn[2];
+        teno_gauss_powers(Qw, fw, pv, pd);
+        teno_gauss_powers(Qn, fq, qv, qd);
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          v[gp] = m ^ gp ? pv[1] : pv[0];
+          dv[gp] = m ^ gp ? pd[1] : pd[0];
+          vn[gp] = m ^ gp ? qv[1] : qv[0];
+        }
         {
           // back-projection: dense sums in field order, no contraction
 #pragma clang fp contract(off)
@@ -926,20 +935,23 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
     return sure;
   };
   if (live) {
-    if (SCHEME != SCHEME_TENO_D) {
+    if (CHAR) {
+      if (a.tt.fast & TENO_FILTER_OK)
+        tangential(std::integral_constant<int, SEL_FILTER>());
+      else
+        tangential(std::integral_constant<int, SEL_EXACT>());
+    } else if (SCHEME != SCHEME_TENO_D) {
       tangential(std::integral_constant<int, SEL_GIVEN>());
     } else {
       bool sure = false;
       if (!FLAGS && (a.tt.fast & TENO_RATIO_OK)) sure = tangential(std::integral_constant<int, SEL_SMOOTH>());
       if (!sure && (a.tt.fast & TENO_FILTER_OK)) sure = tangential(std::integral_constant<int, SEL_FILTER>());
       if (!sure) {
-        // characteristic fields take their flags as they are projected
-        if (!CHAR)
-          given = exact_flags(2 * NC, a.tt, [&](int i, double* Q) {
-            const int q = i >> 1, c = q == 1 ? perm[1] : q == 2 ? perm[2] : q;  // mass and energy in place
+        given = exact_flags(2 * NC, a.tt, [&](int i, double* Q) {
+          const int q = i >> 1, c = q == 1 ? perm[1] : q == 2 ? perm[2] : q;  // mass and energy in place
 #pragma unroll
-            for (int r = 0; r < 5; ++r) Q[r] = sR[c][ft + r][nr][vo + (i & 1)];
-          });
+          for (int r = 0; r < 5; ++r) Q[r] = sR[c][ft + r][nr][vo + (i & 1)];
+        });
         tangential(std::integral_constant<int, SEL_GIVEN>());
       }
     }
@@ -947,22 +959,24 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
 #pragma unroll
     for (int q = 0; q < NC; ++q) gV[q][0] = gV[q][1] = gD[q][0] = gD[q][1] = gN[q][0] = gN[q][1] = 0.0;
   }
+  const bool sw = CHAR && m;  // the face frame's flux takes the left side first
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    Wo[q] = gV[q][0];
-    Do[0][q] = gN[q][0];
-    Do[1][q] = gD[q][0] * idt;
-    Wp[q] = lane_xor<1>(gV[q][1]);
-    Dp[0][q] = lane_xor<1>(gN[q][1]);
-    Dp[1][q] = lane_xor<1>(gD[q][1]) * idt;
+    const double pv = lane_xor<1>(gV[q][1]), pd = lane_xor<1>(gD[q][1]), pn = lane_xor<1>(gN[q][1]);
+    Wo[q] = sw ? pv : gV[q][0];
+    Do[0][q] = sw ? pn : gN[q][0];
+    Do[1][q] = (sw ? pd : gD[q][0]) * idt;
+    Wp[q] = sw ? gV[q][0] : pv;
+    Dp[0][q] = sw ? gN[q][0] : pn;
+    Dp[1][q] = (sw ? gD[q][0] : pd) * idt;
   }
   double A[NC] = {0, 0, 0, 0}, B[NC] = {0, 0, 0, 0};
   if (EX && live && a.fallback) {
     double Co[NC], Cp[NC];  // the cells of the lane's own and of its partner's side
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      Co[q] = sW[perm[q]][ft + 2][fn + 2 + m];
-      Cp[q] = sW[perm[q]][ft + 2][fn + 3 - m];
+      Co[q] = sW[perm[q]][ft + 2][fn + 2 + (CHAR ? 0 : m)];
+      Cp[q] = sW[perm[q]][ft + 2][fn + 3 - (CHAR ? 0 : m)];
     }
     const int nfb = fallback_side<NC, 2>(Wo, Do, Co, a.gamma) + fallback_side<NC, 2>(Wp, Dp, Cp, a.gamma);
     if (nfb && a.fbc) atomicAdd(a.fbc, (unsigned long long)nfb);
@@ -1001,6 +1015,10 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
         dW0e[0][2 + j] = m ? own[2] : got[2];
       }
       ok = gp_flux_eq<2, NS, flux_out(STAGE)>(Wo, Wp, Do, Dp, W0e, dW0e, a.fc, dt, A, B, 0.5, -sg);
+    } else if constexpr (CHAR) {
+      double Fdt[NC], Fh[NC];
+      ok = gp_flux_face<2, NS>(Wo, Wp, Do, Dp, a.fc, dt, Fdt, Fh);
+      combine_times<STAGE, NC>(Fdt, Fh, 0.5, A, B);
     } else {
       ok = gp_flux<2, NS, flux_out(STAGE)>(Wo, Wp, Do, Dp, a.fc, dt, A, B, 0.5, -sg);
     }

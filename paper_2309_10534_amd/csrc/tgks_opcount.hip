@@ -170,8 +170,8 @@ long long count_face_char(const tgks_ctx* c, int stage, tgks_opcount::Tally* det
           Qw[r] = char_dot<NC>(L[k], X[r]);
           Qn[r] = char_dot<NC>(L[k], Xn[r]);
         }
-        teno_gauss(Qw, teno_flag<SEL_EXACT>(Qw, c->tt), v, dv);
-        teno_gauss(Qn, teno_flag<SEL_EXACT>(Qn, c->tt), vn, dvn);
+        teno_gauss_powers(Qw, teno_flag<SEL_EXACT>(Qw, c->tt), v, dv);
+        teno_gauss_powers(Qn, teno_flag<SEL_EXACT>(Qn, c->tt), vn, dvn);
         for (int q = 0; q < NC; ++q)
           for (int g = 0; g < 2; ++g) {
             aV[q][g] = k == 0 ? R[q][k] * v[g] : aV[q][g] + R[q][k] * v[g];
@@ -194,6 +194,14 @@ long long count_face_char(const tgks_ctx* c, int stage, tgks_opcount::Tally* det
   const double w = 1.0 / NG;
   for (int m = 0; m < NG; ++m) {
     F Fa[NC], Fb[NC];
+    if constexpr (D == 2) {
+      gp_flux_face<D, NS>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb);
+      if (stage == 1)
+        combine_times<1, NC>(Fa, Fb, w, A, B);
+      else
+        combine_times<2, NC>(Fa, Fb, w, A, B);
+      continue;
+    }
     if (stage == 1)
       gp_flux<D, NS, FLUX_STAGE1>(Wg[m][0], Wg[m][1], Dg[m][0], Dg[m][1], fc, dt, Fa, Fb, w);
     else
