@@ -386,7 +386,7 @@ TGKS_HD TenoSel teno_select(const R* Q, const TenoParts<R>& p, const TenoCfg& c)
 template <int MODE = SEL_EXACT, bool COLD = false, class R>
 TGKS_HD unsigned teno_flag(const R* Q, const TenoCfg& c) {
   TenoParts<R> p;
-  if constexpr (MODE != SEL_EXACT) teno_parts(Q, p);
+  if constexpr (MODE != SEL_EXACT && std::is_same_v<R, double>) teno_parts(Q, p);
   return teno_select<MODE, COLD>(Q, p, c).flag();
 }
 
