@@ -164,15 +164,16 @@ TGKS_HD void teno_parts(const R* Q, TenoParts<R>& p) {
 // kept (ratio 4 of teno_cfg).  N >= 2^-29 |c| keeps the rounding of every
 // indicator (20 ulps of the values, here and in the oracle's order) below
 // 2^-18 N, far inside the margin; data with less variation than that is left
-// to the general evaluation.
+// to the general evaluation, and so is data whose indicators leave the range
+// of teno_cfg (N^2 < 1e39: all four are then below 1e39; beyond 1e154 the
+// squares here would be infinite and any data pass for smooth).
 template <bool EQ>
 TGKS_HD bool teno_smooth(const TenoParts<double>& p) {
 #pragma clang fp contract(off)
   const double ea = p.t[1] - p.t[0], eb = p.t[2] - p.t[1];
-  const double n = fma(13.0 / 3.0, p.t[1] * p.t[1], p.x * p.x);
-  const double e = fmax(fabs(ea), fabs(eb)), cs = p.c * 0x1p-29;
-  // (the sum, not the larger of the two, would be a NaN for a NaN: e - e)
-  const bool small = (e * e <= 0.01 * n) & (ea + eb == ea + eb);
+  const double n = fma(13.0 / 3.0, p.t[1] * p.t[1], p.x * p.x), cs = p.c * 0x1p-29;
+  // both within r N: by the sum of their squares, which a NaN in either fails
+  const bool small = (fma(eb, eb, ea * ea) <= 0.01 * n) & (n < 1e39);
   const bool seen = cs * cs <= n;
   return EQ ? small & (seen | (n == 0.0)) : small & seen;
 }
