@@ -156,15 +156,23 @@ int launch_update(tgks_ctx* c, int stage, const double* W, double* o1, double* o
   UpdateArgs u = update_args(c, W, o1, o2, dt, c->partial);
   dim3 grid((unsigned)c->nblk);
   Timer tm(c, stage == 1 ? 4 : 5);
-#define UPD(DV)                                                                 \
-  if (stage == 1) LAUNCH((update_kernel<DV, 1, false>), grid, dim3(256), u);    \
-  else if (cfl) LAUNCH((update_kernel<DV, 2, true>), grid, dim3(256), u);       \
-  else LAUNCH((update_kernel<DV, 2, false>), grid, dim3(256), u);
+  const bool stop = c->nblk > CLOCK_NBLK;  // (see update_body)
+#define UPDS(DV, SV)                                                             \
+  if (stage == 1) LAUNCH((update_kernel<DV, 1, false, SV>), grid, dim3(256), u); \
+  else if (cfl) LAUNCH((update_kernel<DV, 2, true, SV>), grid, dim3(256), u);    \
+  else LAUNCH((update_kernel<DV, 2, false, SV>), grid, dim3(256), u);
+#define UPD(DV)     \
+  if (stop) {       \
+    UPDS(DV, true)  \
+  } else {          \
+    UPDS(DV, false) \
+  }
   if (c->g.D == 2) {
     UPD(2)
   } else {
     UPD(3)
   }
+#undef UPDS
 #undef UPD
   HIPCHK(hipGetLastError());
   return TGKS_OK;

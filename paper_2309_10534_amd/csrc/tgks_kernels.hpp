@@ -1458,9 +1458,13 @@ struct UpdateArgs {
 // cell id of this thread; the block's CFL minimum goes to *partial.  Large grids
 // move the face fluxes at 5 TB/s, the rate of a copy; a small grid waits:
 // hence 32-bit index arithmetic (a 64-bit quotient takes some hundred
-// instructions) and loads that do not wait for the time step.  STOP: for
-// batches, in which instances stop: the fluxes are not read then.  97 x 61, one
-// update: 4.6 -> 4.1 us.
+// instructions) and loads that do not wait for the time step (97 x 61, one
+// update: 4.6 -> 4.1 us).  STOP: the fluxes are read only where the step
+// advances: batches, in which instances stop, and single grids beyond
+// CLOCK_NBLK blocks, where other wavefronts hide the wait and a step after the
+// end time costs its traffic (1000 x 1000, 20 such steps: 1.77 ms, 2.60 with
+// the fluxes read; four steps that advance 2.46 and 2.47 ms; at 256 x 256, below
+// the line, 0.37 and 0.32 ms either way).
 template <int D, int STAGE, bool CFL, bool STOP = false>
 __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, double* partial) {
   constexpr int NC = D + 2;
@@ -1518,10 +1522,10 @@ __device__ __forceinline__ void update_body(const UpdateArgs& u, long long id, d
   }
 }
 
-template <int D, int STAGE, bool CFL>
+template <int D, int STAGE, bool CFL, bool STOP>
 __global__ __launch_bounds__(256) void update_kernel(UpdateArgs u) {
-  update_body<D, STAGE, CFL>(u, (long long)blockIdx.x * blockDim.x + threadIdx.x,
-                            CFL ? u.partial + blockIdx.x : nullptr);
+  update_body<D, STAGE, CFL, STOP>(u, (long long)blockIdx.x * blockDim.x + threadIdx.x,
+                                   CFL ? u.partial + blockIdx.x : nullptr);
 }
 
 // CFL partial minima of a state (no update); id: the thread's cell, if live
