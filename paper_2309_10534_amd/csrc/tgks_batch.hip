@@ -163,24 +163,22 @@ static int batch_line(tgks_batch* b, int stage, const double* W, const double* b
 }
 
 static int batch_faces(tgks_batch* b, const double* W, int stage) {
-  {
-    for (int ax = 0; ax < 2; ++ax) {
-      if (b->chr || b->fb) {  // one tile shape on the characteristic / fallback path
-        if (b->chr && b->fb) batch_face2d<CHAR_TILE2, true, true>(b, W, ax, stage);
-        else if (b->chr) batch_face2d<CHAR_TILE2, true>(b, W, ax, stage);
-        else batch_face2d<CHAR_TILE2, false, true>(b, W, ax, stage);
-        continue;
-      }
-      switch (b->tile2) {
-        case 1:
-          batch_face2d<1>(b, W, ax, stage);
-          break;
-        case 2:
-          batch_face2d<2>(b, W, ax, stage);
-          break;
-        default:
-          batch_face2d<0>(b, W, ax, stage);
-      }
+  for (int ax = 0; ax < 2; ++ax) {
+    if (b->chr || b->fb) {  // one tile shape on the characteristic / fallback path
+      if (b->chr && b->fb) batch_face2d<CHAR_TILE2, true, true>(b, W, ax, stage);
+      else if (b->chr) batch_face2d<CHAR_TILE2, true>(b, W, ax, stage);
+      else batch_face2d<CHAR_TILE2, false, true>(b, W, ax, stage);
+      continue;
+    }
+    switch (b->tile2) {
+      case 1:
+        batch_face2d<1>(b, W, ax, stage);
+        break;
+      case 2:
+        batch_face2d<2>(b, W, ax, stage);
+        break;
+      default:
+        batch_face2d<0>(b, W, ax, stage);
     }
   }
   HIPCHK(hipGetLastError());

@@ -113,21 +113,14 @@ int launch_faces(tgks_ctx* c, const double* W, const double* dt, int stage, uint
     const bool fl = flags != nullptr && stage == 1;
     if (fl) {
       a.nflags = flags;
-      if (D == 3) {
-        // tangential flags of 3-D faces: 16 nc planes per direction
-        long long off = (long long)D * c->nc * c->ncell;
-        for (int d = 0; d < ax; ++d) off += 16LL * c->nc * c->nface[d];
-        a.tflags = flags + off;
-      }
+      // tangential flags of 3-D faces: 16 nc planes per direction
+      long long off = (long long)D * c->nc * c->ncell;
+      for (int d = 0; d < ax; ++d) off += 16LL * c->nc * c->nface[d];
+      a.tflags = flags + off;
     }
-    if (D == 2) {
-      Timer tm(c, ax);
-      launch_face2d_any(c, a, ax, stage, fl);
-    } else {
-      int r = ax == 0 ? launch_face3d_ax<0>(c, a, stage, fl)
-                      : (ax == 1 ? launch_face3d_ax<1>(c, a, stage, fl) : launch_face3d_ax<2>(c, a, stage, fl));
-      if (r) return r;
-    }
+    const int r = ax == 0 ? launch_face3d_ax<0>(c, a, stage, fl)
+                          : (ax == 1 ? launch_face3d_ax<1>(c, a, stage, fl) : launch_face3d_ax<2>(c, a, stage, fl));
+    if (r) return r;
   }
   HIPCHK(hipGetLastError());
   return TGKS_OK;

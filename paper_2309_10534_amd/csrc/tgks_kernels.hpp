@@ -616,7 +616,7 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
   double(*sR)[LT][RN][4] = reinterpret_cast<double(*)[LT][RN][4]>(lds + NC * LT * LN);
   double dt, t_prev = 0.0;
   const bool clocked = STAGE == 1 && a.ck.prev != nullptr;
-  if (clocked)
+  if (clocked)  // (written by the launch's first block: a tile of the x faces)
     step_clock(a.ck, AX == 0 && blockIdx.x == 0 && threadIdx.x < 64, t_prev, dt);
   else
     dt = *a.dt;
@@ -1037,12 +1037,6 @@ __device__ __forceinline__ void face2d_tile(const StageArgs& a, int bx, int by, 
       if (STAGE == 1) a.FB[(long long)perm[q] * nf + fidx] = B[q];
     }
   }
-}
-
-template <int AX, int STAGE, bool NS, bool FLAGS, int TILE>
-__global__ __launch_bounds__(2 * tile2_tn(TILE) * tile2_tt(TILE), 2) void face2d_kernel(StageArgs a) {
-  __shared__ double lds[tile2_lds(TILE)];
-  face2d_tile<AX, STAGE, NS, FLAGS, TILE>(a, blockIdx.x, blockIdx.y, lds);
 }
 
 // Both directions in one launch: the first blocks take the x-face tiles,
