@@ -241,7 +241,11 @@ int tgks_fallback_count(tgks_ctx* ctx, int64_t* count);
 /* Per-kernel timing with HIP events recorded on the context's stream around
  * every launch while enabled.  kind: 0 face fluxes along x, 1 along y, 2
  * along z, 3 normal reconstruction (3-D), 4 stage-1 update, 5 stage-2
- * update, 6 CFL reduction.  tgks_kernel_time synchronises and returns the
+ * update, 6 CFL reduction.  2-D grids launch both directions together, as
+ * kind 0 (kind 1 counts nothing); 1-D grids evaluate faces and update of a
+ * stage in one kernel, as kind 0 (kinds 4 and 5 count nothing); a time step
+ * that a stage-1 kernel takes from the step before (tgks_run) is part of that
+ * kernel's kind.  tgks_kernel_time synchronises and returns the
  * summed milliseconds and launch count of one kind since it was enabled. */
 int tgks_timing(tgks_ctx* ctx, int32_t enable);
 int tgks_kernel_time(tgks_ctx* ctx, int32_t kind, double* ms, int64_t* launches);

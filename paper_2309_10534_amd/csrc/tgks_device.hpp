@@ -64,8 +64,9 @@ struct TenoCfg {
 //
 // TENO_FILTER_OK, the weights' comparisons multiplied out, with a margin
 // (teno_select): q = 7, 1e-40 <= eps < 1e40 and 1e-20 <= C_T1, C_T2 <= 1/2
-// (an indicator more than 2048 times the smallest is cut there, which stands
-// for weights below 2048^-7 = 6.6e-24 of the largest: far below any cut-off).
+// (the smallest indicator is scaled into [1, 2) and all are cut at 2048, so one
+// is cut from 1024 times the smallest on, at a weight below 1024^-7 = 8.5e-22 of
+// the largest: a twelfth of the smallest cut-off allowed).
 inline TenoCfg teno_cfg(double ct1, double ct2, double eps, int q) {
   const double d = 1e-9;
   const bool ok = q == 7 && eps >= 1e-40 && ct1 * (1.0 + d) <= 1.0 / (3.0 * 16384.0 + 1.0) &&
