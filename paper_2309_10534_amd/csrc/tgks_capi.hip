@@ -334,9 +334,12 @@ void init_ctx_host(tgks_ctx* c, const tgks_params* p, void* stream) {
     c->nface[d] = d < D ? nf : 0;
   }
   if (D == 1) {
-    // one wavefront per block spreads a small grid over the chip (400 cells:
-    // 7 compute units); four keep the partial minima of a large one few
-    c->line_waves = g.ncell <= 1024LL * LINE_CELLS ? 1 : 4;
+    // one wavefront per block spreads a small grid over the chip, as long as
+    // its partial minima still hand the clock on (CLOCK_NBLK); four keep the
+    // partial minima of a larger one few.  20 steps, one / four per block, us:
+    // 4,000 cells 276 / 290, 14,848 269 / 325, 20,000 328 / 320, 59,392 361 /
+    // 297, 200,000 788 / 709, 4 million 9510 / 8355
+    c->line_waves = g.ncell <= (long long)CLOCK_NBLK * LINE_CELLS ? 1 : 4;
     c->per = LINE_CELLS * c->line_waves;
   }
   c->nblk = (int)((g.ncell + c->per - 1) / c->per);

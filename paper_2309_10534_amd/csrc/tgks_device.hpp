@@ -1295,7 +1295,9 @@ TGKS_HD void half_seed(R U, R lam, double sgn, R& m0, R& m1) {
 // frame at the end.  Tables of every monomial's moments in the face frame, a
 // linear solve per slope and sums of products took 209 more instructions per
 // lane of the 2-D face kernel (of 2,500) and 225 registers where this takes
-// 145, which is three wavefronts per SIMD instead of two: 20 steps of the
+// 145, which is three wavefronts per SIMD instead of two (Euler; with the
+// Navier-Stokes terms 165 in stage 1, and 169 in stage 2, one more than three
+// wavefronts have): 20 steps of the
 // 2-D four-quadrant problem at 1024^2 15.5 ms (18.2 before), 2 steps of the
 // 3-D Taylor-Green vortex at 128^3 22.3 ms (24.4).
 // ---------------------------------------------------------------------------

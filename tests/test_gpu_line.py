@@ -1,5 +1,5 @@
 """The 1-D kernel's options at the sizes where its wavefronts (58 cells) and
-blocks (one wavefront, four above 59,392 cells) begin and end: characteristic
+blocks (one wavefront, four above 14,848 cells) begin and end: characteristic
 variables, prescribed sides at both ends, the first-order fallback with the cell
 that needs it beside a wavefront's first and last faces, Navier-Stokes, the
 comparison schemes.  One step with flags against the oracle, and three CFL steps
@@ -14,7 +14,7 @@ from paper_2309_10534_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [3, 4, 57, 58, 59, 61, 62, 115, 116, 117, 232, 233, 59392, 59393]
+SIZES = [3, 4, 57, 58, 59, 61, 62, 115, 116, 117, 232, 233, 14848, 14849, 59392, 59393]
 NS = dict(tau="viscous", mu=1e-3, prandtl=0.72)
 
 
