@@ -431,10 +431,11 @@ TGKS_HD void face_flux_combine(const R* W0, const Gas<D, R>& g0, const SidePart<
 // the first-order fallback): 40 survive with this pair, 31 with these values
 // and the flux of gp_flux, 9 with the values of teno_poly and this flux, 13
 // with teno_poly and gp_flux; the run from the unchanged data reaches t = 1
-// with this pair and stopped at t = 0.144 with the last.  teno_poly's values
-// are the more exact ones (a constant stays one to the bit): what helps is the
-// half ulp that the power series leaves on them.  Eight steps take 1.78 ms with
-// this pair and 1.44 with the last.
+// with this pair and stopped at t = 0.144 with the last.  The two forms agree to
+// rounding and teno_poly's is the more exact one (a constant stays one to the
+// bit), so the loss is no error of its values; why its rounding suits these
+// runs less is not known.  Eight steps take 1.78 ms with this pair and 1.44
+// with the last.
 template <int D, bool NS, class R>
 TGKS_HD bool gp_flux_face(const R* Wl, const R* Wr, const R (*dWl)[D + 2], const R (*dWr)[D + 2], const FluxCfg& P,
                           R dt, R* Fdt, R* Fh) {
